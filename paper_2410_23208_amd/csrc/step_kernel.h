@@ -1,0 +1,1613 @@
+// step_kernel.h -- the fused multi-step kernel (k2d.hip describes what it computes and how it is mapped).
+// Every capacity class instantiates it in a translation unit of its own.
+#pragma once
+
+#include <type_traits>
+
+#include "common.h"
+
+// Phase clocks (builds with -DK2D_PHASE_TIMERS only; the product library has none of this): every
+// wavefront adds up the shader clocks it spends in each phase of a substep and leaves the sums, followed
+// by its totals of collision and joint dependency levels, in a caller-owned device buffer
+// (k2d_debug_set_phase_buffer), kPhaseSlots 64-bit words per wavefront.
+#ifdef K2D_PHASE_TIMERS
+#define K2D_T(i) { const long long t_now_ = clock64(); t_acc[i] += t_now_ - t_last; t_last = t_now_; }
+#else
+#define K2D_T(i)
+#endif
+
+namespace k2d_impl {
+
+constexpr float kCullMargin = 1e-3f;   // by how much every bounding box is grown before the overlap test
+
+// Compile-time description of one capacity class under one lane mapping, and of its LDS image.
+template <int P_, int C_, int J_, int T_, int G_>
+struct Cfg {
+  static constexpr int P = P_, C = C_, J = J_, T = T_, G = G_;   // G lanes per environment
+  static constexpr int N = P + C, NP = N * (N - 1) / 2, A = J + T;
+  static constexpr int EPW = 64 / G;           // environments per wavefront
+  static constexpr int M = N + (N & 1);        // tournament size (an odd N gets a phantom that sits out)
+  static constexpr int R = M - 1;              // rounds
+  static constexpr int PPR = M / 2;            // pairs per round
+  static_assert((G == 8 || G == 16) && N <= 16 && J <= G && T <= G && R <= 15, "lane mapping");
+  // Work items of a lane: shapes k, k + G, ...; one vertex of polygons k / 4, k / 4 + G / 4, ... (four
+  // neighbouring lanes share a polygon); entries k, k + G, ... of the list of eligible pairs.
+  static constexpr int NS = (N + G - 1) / G, QT = (4 * P + G - 1) / G, ET = (NP + G - 1) / G;
+  static constexpr int TSP = ET <= 4 ? 4 : ET <= 8 ? 8 : 16;   // bytes of a lane's pair states
+  static_assert(ET <= 16, "pair states of a lane");
+  // Active pairs are numbered 0, 1, ... as the narrowphase finds them.  Pairs below NREG live in
+  // registers (lane k holds pairs k and G + k): the lane that found the manifold leaves it in an LDS
+  // staging slot, the lane that keeps the pair derives the substep constants from it.  Pairs beyond them
+  // live as full records in a small LDS pool (POOL records, as many as the LDS budget of the class has
+  // room for, eight at most) or, past that, in the HBM record.
+  static constexpr int NREG = 2 * G < NP ? 2 * G : NP;
+  static constexpr bool TWO = NP > G;          // a lane may have to hold a second pair
+  static constexpr int LISTED = NP - NREG;     // pairs that may have to live outside the registers
+  static constexpr int LAMN = NREG < 62 ? NREG : 62;   // pairs whose accumulated impulses wait in LDS for the next substep
+  static constexpr k2d_layout L = make_layout(P, C, J, T);
+  static constexpr int REC_WORDS = record_words(L), G_SPILL = spill_offset(L), SPILL = spill_records(NP);
+  // LDS image of one environment.  What a visit of a constraint reads of a body is one 16-byte word:
+  // position with cos and sin, velocities with the rotation angle, mass properties.  Entry N of the first two
+  // swallows what is stored for shapes no impulse moves.
+  static constexpr int X_POS = 0;                          // float4 [N + 1]: x, y, cos, sin
+  static constexpr int X_VEL = X_POS + 4 * (N + 1);        // float4 [N + 1]: vx, vy, omega, theta
+  static constexpr int X_PROP = X_VEL + 4 * (N + 1);       // float4 [N]: inverse mass, inverse inertia, friction, restitution
+  static constexpr int X_BOX = X_PROP + 4 * N;             // float4 [N]: bounding box (min x, min y, max x, max y), grown by kCullMargin
+  static constexpr int X_JOINED = X_BOX, X_JINFO = X_BOX + N;   // (episode set-up only) bit j of word i: joined; joints' shapes
+  static constexpr int X_LT = X_BOX;                       // (boxes are done with) 16-bit [LISTED]: shapes of the pairs not held in registers
+  static_assert(N + J <= 4 * N && (LISTED + 1) / 2 <= 4 * N, "what shares the boxes' LDS");
+  static constexpr int WSTRIDE = 20;                       // a polygon's world vertices and normals: 16 words in 20, so that
+                                                           // the lanes' 16-byte reads of different polygons spread over the banks
+  static constexpr int X_WV = X_BOX + 4 * N;
+  static constexpr int X_TAKEN = X_WV;                     // (world polygons are done with) 16-bit [N]: levels taken at a shape
+  static constexpr int X_LVL = X_TAKEN + (N + 1) / 2;      // bytes [LISTED]: level of a pair not held in registers
+  static constexpr int LCAP = 16;                          // a level holds at most one pair per movable shape
+  static constexpr int X_SCHED = X_LVL + (LISTED + 3) / 4; // bytes [R][LCAP]: the pairs not held in registers, level by level
+  static_assert(X_SCHED + R * LCAP / 4 <= X_WV + WSTRIDE * P, "what shares the world polygons' LDS");
+  static constexpr int X_LIST = X_WV + WSTRIDE * P;        // 16-bit [NP]: candidate pairs, one shape-type mix after the other
+  static constexpr int X_ELIG = X_LIST;                    // (episode set-up only) bytes [NP]: eligible pairs
+  static constexpr int X_PSB = X_LIST;                     // (write-back only) bytes [NP]: pair states in lexicographic pair order
+  static constexpr int X_PST = align_up(X_LIST + (NP + 1) / 2, 4);   // bytes [G][TSP]: state of every eligible pair (see pair_byte)
+  static constexpr int X_CNT = X_PST + G * TSP / 4;        // candidates counted so far, eight bits per shape-type mix
+  static constexpr int X_RAD = X_CNT + 1;                  // radii of the circles
+  static constexpr int X_LAM = align_up(X_RAD + C, 4);     // float4 [LAMN]: accumulated impulses of the register-held pairs
+  static constexpr int kManW = 12;                         // words of a staged manifold (nine used; 16-byte aligned, spread over banks)
+  static constexpr int STAGE_N = NREG < 2 * G ? 2 * G : NREG;   // (a batch of A.8 stages up to 2 G impulses there)
+  static constexpr int X_STAGE = X_LAM + 4 * LAMN;
+  static constexpr int X_POOL = X_STAGE + STAGE_N * kManW;
+  // LDS budget of one environment: a CU's 160 KiB shared by the lanes of eight wavefronts' worth of
+  // 16-lane environments (or four wavefronts' worth of 8-lane ones): 1280 words.  The stride is an odd
+  // multiple of G words, so that the same word of different environments falls into different banks.
+  static constexpr int MAX_STRIDE = (1280 / G - ((1280 / G) % 2 == 0 ? 1 : 0)) * G;
+  static constexpr int POOL_WANT = LISTED < 8 ? LISTED : 8;
+  static constexpr int POOL_FIT = MAX_STRIDE > X_POOL ? (MAX_STRIDE - X_POOL) / kRecW : 0;
+  static constexpr int POOL = POOL_WANT < POOL_FIT ? POOL_WANT : POOL_FIT;
+  static_assert(NP - NREG - POOL <= SPILL, "spill room of the record");
+  static constexpr int LDS_WORDS = X_POOL + POOL * kRecW;
+  static constexpr int LDS_STRIDE = align_up(LDS_WORDS - G, 2 * G) + G;
+  static_assert(LDS_STRIDE >= LDS_WORDS && (LDS_STRIDE / G) % 2 == 1 && LDS_STRIDE <= MAX_STRIDE, "stride rule");
+  static constexpr int LDS_BYTES = LDS_STRIDE * EPW * 4;
+};
+
+#define K2D_DPP(v, ctrl) __builtin_amdgcn_update_dpp(0, (int)(v), ctrl, 0xf, 0xf, true)
+#define K2D_DPPF(v, ctrl) __int_as_float(K2D_DPP(__float_as_int(v), ctrl))
+enum {   // DPP controls: exchanges within four neighbouring lanes
+  kQuadNext = 0x39,    // lane i reads lane i + 1 (mod 4)
+  kQuadXor1 = 0xB1, kQuadXor2 = 0x4E
+};
+
+// OR over the lanes of an environment's group.  A group of 16 is one DPP row (rotations reach every lane);
+// a group of 8 is half a row: exchanges within a quad and the mirror of the half row.
+template <int G>
+__device__ __forceinline__ unsigned group_or(unsigned v) {
+  if constexpr (G == 16) {
+    v |= (unsigned)K2D_DPP(v, 0x121);
+    v |= (unsigned)K2D_DPP(v, 0x122);
+    v |= (unsigned)K2D_DPP(v, 0x124);
+    v |= (unsigned)K2D_DPP(v, 0x128);
+  } else {
+    v |= (unsigned)K2D_DPP(v, kQuadXor1);
+    v |= (unsigned)K2D_DPP(v, kQuadXor2);
+    v |= (unsigned)K2D_DPP(v, 0x141);
+  }
+  return v;
+}
+// Lane q of the own group, for all lanes (q a compile-time constant).
+template <int G, int q>
+__device__ __forceinline__ unsigned group_bcast(unsigned v, int g) {
+  if constexpr (G == 16) return (unsigned)K2D_DPP(v, 0x150 + q);
+  else {
+    const unsigned lo = (unsigned)K2D_DPP(v, 0x150 + q), hi = (unsigned)K2D_DPP(v, 0x150 + q + 8);
+    return (g & 1) ? hi : lo;
+  }
+}
+
+// A workgroup of the step kernel is one wavefront, and the memory operations of one wavefront are
+// performed in the order they are issued: lanes that exchange data through LDS need no hardware barrier
+// and no wait, only a point that the compiler does not move memory accesses across.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+// Stores of one lane to HBM that another lane of the wavefront is to read.
+__device__ __forceinline__ void hbm_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// Two-term products round once: a.b = fma(ax, bx, ay*by), a x b = fma(ax, by, -(ay*bx)); an impulse is
+// applied as v = fma(1/m, j, v).  Everything else is one operation, one rounding (contraction is off).
+__device__ __forceinline__ float dot2(float ax, float ay, float bx, float by) { return fmaf(ax, bx, ay * by); }
+__device__ __forceinline__ float cross2(float ax, float ay, float bx, float by) { return fmaf(ax, by, -(ay * bx)); }
+// a + b with `a` as the first operand of the instruction.  For numbers the order is nothing; where both are NaN (an
+// environment that blew up) the first one's sign survives, and the records of such an environment should not
+// depend on how a compiler happens to arrange a commutative addition.
+__device__ __forceinline__ float add_ordered(float a, float b) {
+  float d;
+  asm("v_add_f32_e32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+// an impulse (jx, jy) at offset (rx, ry) from the centre of mass (A.2); v = (vx, vy, omega, -)
+__device__ __forceinline__ void apply_impulse(float4& v, float im, float ii, float jx, float jy, float rx, float ry) {
+  v.x = fmaf(im, jx, v.x);
+  v.y = fmaf(im, jy, v.y);
+  v.z = fmaf(ii, cross2(rx, ry, jx, jy), v.z);
+}
+
+// One active pair of the current substep.  An active pair has one or two active manifold points; the first
+// of them is slot 0 of the record, so that a visit has a branch on the second only.
+struct PairRec {
+  float nx, ny, mu, corr;        // unit normal a->b; friction coefficient; positional-correction length
+  int ab;                        // a | b<<8 | kTwo | kSwapped
+  float rax[2], ray[2], rbx[2], rby[2], mass_n[2], mass_t[2], bias[2], rest[2], lam_n[2], lam_t[2];
+};
+constexpr int kTwo = 1 << 16;        // both points are active
+constexpr int kSwapped = 1 << 17;    // slot 0 is manifold point 1 (point 0 is not active)
+
+// State byte of an eligible pair: bits 0, 1 = manifold points active at the last substep; bits 2..7 = where
+// its accumulated impulses are: the number the pair had (its place in the LDS array), or kInRecord.
+constexpr int kInRecord = 63;
+
+// LDS pointers are passed with their address space spelled out, so that a record access can never
+// degrade into a flat access when the LDS and the HBM (spill) variants of a code path are merged.
+using LdsF = __attribute__((address_space(3))) float*;
+using LdsCF = const __attribute__((address_space(3))) float*;
+__device__ __forceinline__ LdsF to_lds(float* p) { return (LdsF)p; }
+
+template <class Ptr>
+__device__ __forceinline__ void rec_store(Ptr p, const PairRec& r) {
+  p[0] = r.nx; p[1] = r.ny; p[2] = r.mu; p[3] = r.corr; p[4] = i2f(r.ab);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    auto q = p + 5 + 10 * k;
+    q[0] = r.rax[k]; q[1] = r.ray[k]; q[2] = r.rbx[k]; q[3] = r.rby[k]; q[4] = r.mass_n[k];
+    q[5] = r.mass_t[k]; q[6] = r.bias[k]; q[7] = r.rest[k]; q[8] = r.lam_n[k]; q[9] = r.lam_t[k];
+  }
+}
+template <class Ptr>
+__device__ __forceinline__ void rec_load(Ptr p, PairRec& r) {
+  r.nx = p[0]; r.ny = p[1]; r.mu = p[2]; r.corr = p[3]; r.ab = f2i(p[4]);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    auto q = p + 5 + 10 * k;
+    r.rax[k] = q[0]; r.ray[k] = q[1]; r.rbx[k] = q[2]; r.rby[k] = q[3]; r.mass_n[k] = q[4];
+    r.mass_t[k] = q[5]; r.bias[k] = q[6]; r.rest[k] = q[7]; r.lam_n[k] = q[8]; r.lam_t[k] = q[9];
+  }
+}
+// accumulated impulses (n0, t0, n1, t1) of a record, by manifold point
+__device__ __forceinline__ float4 lam_of(int ab, float n0, float t0, float n1, float t1) {
+  return (ab & kSwapped) ? make_float4(0.f, 0.f, n0, t0) : make_float4(n0, t0, n1, t1);
+}
+
+// Collision manifold (Table 2) of one pair: unit normal from a to b, up to two points.
+struct Manifold {
+  float nx = 0.f, ny = 0.f;
+  float px[2] = {0.f, 0.f}, py[2] = {0.f, 0.f}, pen[2] = {0.f, 0.f};
+  bool valid[2] = {false, false};
+};
+
+template <class K>
+struct Step {
+  static constexpr k2d_layout L = K::L;
+  static constexpr int N = K::N, P = K::P, G = K::G, M = K::M, R = K::R;
+
+  // ---- LDS accessors (E = base of this environment's image) ----
+  static __device__ __forceinline__ float4& pos4(float* E, int i) { return *reinterpret_cast<float4*>(E + K::X_POS + 4 * i); }
+  static __device__ __forceinline__ float4& vel4(float* E, int i) { return *reinterpret_cast<float4*>(E + K::X_VEL + 4 * i); }
+  static __device__ __forceinline__ float4& prop4(float* E, int i) { return *reinterpret_cast<float4*>(E + K::X_PROP + 4 * i); }
+  static __device__ __forceinline__ float4& box4(float* E, int i) { return *reinterpret_cast<float4*>(E + K::X_BOX + 4 * i); }
+  static __device__ __forceinline__ float2 xy(float* E, int i) { return *reinterpret_cast<float2*>(E + K::X_POS + 4 * i); }
+  // world vertex / outward unit edge normal i of polygon p
+  static __device__ __forceinline__ float2& wv(float* E, int i, int p) { return *reinterpret_cast<float2*>(E + K::X_WV + K::WSTRIDE * p + 2 * i); }
+  static __device__ __forceinline__ float2& wn(float* E, int i, int p) { return *reinterpret_cast<float2*>(E + K::X_WV + K::WSTRIDE * p + 8 + 2 * i); }
+  // all four of a polygon (`what` = 0: vertices, 8: normals)
+  static __device__ __forceinline__ void load4(float* E, int p, int what, float2 (&o)[4]) {
+    const float4* q = reinterpret_cast<const float4*>(E + K::X_WV + K::WSTRIDE * p + what);
+    const float4 u = q[0], v = q[1];
+    o[0] = make_float2(u.x, u.y); o[1] = make_float2(u.z, u.w); o[2] = make_float2(v.x, v.y); o[3] = make_float2(v.z, v.w);
+  }
+
+  // Pair k of round r of the round-robin tournament; returns false for the phantom's pair.
+  static __device__ __forceinline__ bool sched_pair(int r, int k, int& a, int& b) {
+    int x, y;
+    if (k == 0) {
+      x = M - 1;
+      y = r;
+    } else {
+      x = r + k;
+      if (x >= M - 1) x -= M - 1;
+      y = r - k;
+      if (y < 0) y += M - 1;
+    }
+    a = min(x, y);
+    b = max(x, y);
+    return b < N;
+  }
+  // The round a pair (a < b) plays in: a and b add up to twice the round, modulo M - 1 (an odd number, whose
+  // inverse of two is M / 2).
+  static __device__ __forceinline__ int round_of(int a, int b) { return b == M - 1 ? a : ((a + b) * (M / 2)) % (M - 1); }
+  static __device__ __forceinline__ int pair_index(int a, int b) { return a * (2 * N - a - 1) / 2 + (b - a - 1); }
+
+  // ---- A.3.2: circle a, circle b ----
+  static __device__ __forceinline__ void manifold_cc(float pax, float pay, float ra, float pbx, float pby, float rb,
+                                                     Manifold& m) {
+    float dx = pbx - pax, dy = pby - pay;
+    float len = sqrtf(dot2(dx, dy, dx, dy));
+    bool ok = len > 1e-9f;
+    m.nx = ok ? dx / len : 1.f;
+    m.ny = ok ? dy / len : 0.f;
+    m.px[0] = pax + ra * m.nx;
+    m.py[0] = pay + ra * m.ny;
+    m.pen[0] = ra + rb - len;
+    m.valid[0] = true;
+  }
+
+  // ---- A.3.3: polygon a (tri_a: a triangle), circle b ----
+  // W neighbouring lanes share the pair: lane h of them looks at edges h * 4 / W ..., the first one is left
+  // with the result.  (Edges are compared with "strictly better", the earlier lane holding the earlier edges:
+  // the lowest edge index wins ties.)
+  template <int W>
+  static __device__ __forceinline__ void manifold_pc(float* E, int h, int pa, bool tri_a, float cx, float cy, float rb,
+                                                     Manifold& m) {
+    float best_d2 = INFINITY, qx = 0.f, qy = 0.f;
+    float smax = -INFINITY, snx = 0.f, sny = 0.f;
+    constexpr int EDGES = 4 / W;
+    const int i0 = h * EDGES;
+    float2 v = wv(E, i0, pa);
+    // (vertex slot 3 of a triangle repeats vertex 0; its fourth "edge" is computed and thrown away, so
+    // that the loop has no branch)
+#pragma unroll
+    for (int z = 0; z < EDGES; ++z) {
+      const int i = i0 + z;
+      const bool real = i < 3 || !tri_a;
+      float2 v1 = wv(E, (i + 1) & 3, pa);
+      float2 nr = wn(E, i, pa);
+      float ex = v1.x - v.x, ey = v1.y - v.y;
+      float rx = cx - v.x, ry = cy - v.y;
+      float t = dot2(rx, ry, ex, ey) / dot2(ex, ey, ex, ey);
+      t = fminf(fmaxf(t, 0.f), 1.f);
+      float qix = v.x + t * ex, qiy = v.y + t * ey;
+      float dqx = cx - qix, dqy = cy - qiy;
+      float d2 = dot2(dqx, dqy, dqx, dqy);
+      if (real && d2 < best_d2) { best_d2 = d2; qx = qix; qy = qiy; }
+      float s = dot2(nr.x, nr.y, rx, ry);
+      if (real && s > smax) { smax = s; snx = nr.x; sny = nr.y; }
+      v = v1;
+    }
+    auto take = [&](auto ctrl) {   // from the lane with the later edges
+      constexpr int c = decltype(ctrl)::value;
+      const float d = K2D_DPPF(best_d2, c), x = K2D_DPPF(qx, c), y = K2D_DPPF(qy, c);
+      if (d < best_d2) { best_d2 = d; qx = x; qy = y; }
+      const float s = K2D_DPPF(smax, c), nx = K2D_DPPF(snx, c), ny = K2D_DPPF(sny, c);
+      if (s > smax) { smax = s; snx = nx; sny = ny; }
+    };
+    if constexpr (W >= 2) take(std::integral_constant<int, kQuadXor1>{});
+    if constexpr (W == 4) take(std::integral_constant<int, kQuadXor2>{});
+    if (smax <= 0.f) {   // centre inside the polygon: the face of largest signed distance
+      m.nx = snx; m.ny = sny;
+      m.pen[0] = rb - smax;
+      m.px[0] = cx - smax * snx;
+      m.py[0] = cy - smax * sny;
+    } else {
+      float dist = sqrtf(best_d2);
+      float dqx = cx - qx, dqy = cy - qy;
+      m.nx = dqx / dist; m.ny = dqy / dist;
+      m.pen[0] = rb - dist;
+      m.px[0] = qx; m.py[0] = qy;
+    }
+    m.valid[0] = true;
+  }
+
+  // Largest over X's faces of the smallest signed distance of Y's vertices to the face (A.3.4).
+  static __device__ __forceinline__ void face_query(const float2 (&xw)[4], const float2 (&xn)[4], bool tri_x,
+                                                    const float2 (&yw)[4], float& best, int& idx) {
+    best = -INFINITY;
+    idx = 0;
+    // (vertex slot 3 of a triangle repeats vertex 0, which leaves the minimum over Y's vertices as it is;
+    // the fourth "face" of a triangle X is computed and thrown away: no branch in the loops)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float smin = INFINITY;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        float s = dot2(xn[i].x, xn[i].y, yw[k].x - xw[i].x, yw[k].y - xw[i].y);
+        smin = (s < smin) ? s : smin;
+      }
+      if ((i < 3 || !tri_x) && smin > best) { best = smin; idx = i; }
+    }
+  }
+
+  // ---- A.3.4: polygon a, polygon b ----
+  // W = 1: one lane per pair.  W = 2: two neighbouring lanes, one asks a's faces, the other b's; the first is
+  // left with the result.
+  template <int W>
+  static __device__ __forceinline__ void manifold_pp(float* E, int h, int pa, bool tri_a, int pb, bool tri_b, float tie_eps,
+                                                     Manifold& m) {
+    float sa, sb;
+    int ia, ib;
+    if constexpr (W == 1) {
+      float2 aw[4], bw[4], xn[4];
+      load4(E, pa, 0, aw); load4(E, pb, 0, bw);
+      load4(E, pa, 8, xn);
+      face_query(aw, xn, tri_a, bw, sa, ia);
+      load4(E, pb, 8, xn);
+      face_query(bw, xn, tri_b, aw, sb, ib);
+    } else {
+      const int px = h ? pb : pa, py = h ? pa : pb;
+      float2 xw[4], yw[4], xn[4];
+      load4(E, px, 0, xw); load4(E, py, 0, yw); load4(E, px, 8, xn);
+      face_query(xw, xn, h ? tri_b : tri_a, yw, sa, ia);
+      sb = K2D_DPPF(sa, kQuadXor1);
+      ib = K2D_DPP(ia, kQuadXor1);
+    }
+    if (fmaxf(sa, sb) >= 0.f) return;   // a separating axis exists
+    bool ref_b = sb > sa + tie_eps;
+    int pr = ref_b ? pb : pa, ir = ref_b ? ib : ia;
+    int pi = ref_b ? pa : pb;
+    const bool tri_r = ref_b ? tri_b : tri_a, tri_i = ref_b ? tri_a : tri_b;
+    float2 nref = wn(E, ir, pr);
+    float2 r1 = wv(E, ir, pr);
+    float2 r2 = wv(E, (ir + 1 == (tri_r ? 3 : 4)) ? 0 : ir + 1, pr);
+    int jinc = 0;
+    float dmin = INFINITY;
+    float2 in[4];
+    load4(E, pi, 8, in);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      float d = dot2(in[j].x, in[j].y, nref.x, nref.y);
+      if ((j < 3 || !tri_i) && d < dmin) { dmin = d; jinc = j; }
+    }
+    float2 v0 = wv(E, jinc, pi);
+    float2 v1 = wv(E, (jinc + 1 == (tri_i ? 3 : 4)) ? 0 : jinc + 1, pi);
+    float tx = -nref.y, ty = nref.x;
+    float u0 = dot2(tx, ty, v0.x - r1.x, v0.y - r1.y);
+    float u1 = dot2(tx, ty, v1.x - r1.x, v1.y - r1.y);
+    float len = dot2(tx, ty, r2.x - r1.x, r2.y - r1.y);
+    if ((u0 < 0.f && u1 < 0.f) || (u0 > len && u1 > len)) return;
+    m.nx = ref_b ? -nref.x : nref.x;
+    m.ny = ref_b ? -nref.y : nref.y;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      float uk = k ? u1 : u0;
+      float uc = fminf(fmaxf(uk, 0.f), len);
+      float x = k ? v1.x : v0.x, y = k ? v1.y : v0.y;
+      if (uc != uk) {
+        float s = (uc - u0) / (u1 - u0);
+        x = v0.x + s * (v1.x - v0.x);
+        y = v0.y + s * (v1.y - v0.y);
+      }
+      m.px[k] = x; m.py[k] = y;
+      m.pen[k] = -dot2(nref.x, nref.y, x - r1.x, y - r1.y);
+      m.valid[k] = true;
+    }
+  }
+
+  // Relative velocity of the contact points, v_a + w_a x r_a - v_b - w_b x r_b (A.3.5).
+  static __device__ __forceinline__ void rel_vel(const float4& va, float rax, float ray, const float4& vb, float rbx,
+                                                 float rby, float& x, float& y) {
+    x = fmaf(vb.z, rby, fmaf(-va.z, ray, va.x) - vb.x);
+    y = fmaf(-vb.z, rbx, fmaf(va.z, rax, va.y) - vb.y);
+  }
+
+  // One visit of an active pair in a solver sweep: per point, normal impulse then friction impulse,
+  // accumulated and clamped (A.3.5, A.3.6, A.7), on the velocities of its two bodies.
+  static __device__ __forceinline__ void solve_slot(PairRec& rc, int k, float ima, float iia, float imb, float iib,
+                                                    float4& va, float4& vb) {
+    const float tx = -rc.ny, ty = rc.nx;
+    float rx, ry;
+    rel_vel(va, rc.rax[k], rc.ray[k], vb, rc.rbx[k], rc.rby[k], rx, ry);
+    float vn = dot2(rc.nx, rc.ny, rx, ry);
+    float dl = rc.mass_n[k] * (vn + rc.rest[k] + rc.bias[k]);
+    float ln = fmaxf(rc.lam_n[k] + dl, 0.f);
+    dl = ln - rc.lam_n[k];
+    rc.lam_n[k] = ln;
+    float jx = (-dl) * rc.nx, jy = (-dl) * rc.ny;
+    apply_impulse(va, ima, iia, jx, jy, rc.rax[k], rc.ray[k]);
+    apply_impulse(vb, imb, iib, -jx, -jy, rc.rbx[k], rc.rby[k]);
+    rel_vel(va, rc.rax[k], rc.ray[k], vb, rc.rbx[k], rc.rby[k], rx, ry);
+    float vt = dot2(tx, ty, rx, ry);
+    float dt_ = -rc.mass_t[k] * vt;
+    float lim = rc.mu * ln;
+    float lt = fminf(fmaxf(rc.lam_t[k] + dt_, -lim), lim);
+    dt_ = lt - rc.lam_t[k];
+    rc.lam_t[k] = lt;
+    float fx = dt_ * tx, fy = dt_ * ty;
+    apply_impulse(va, ima, iia, fx, fy, rc.rax[k], rc.ray[k]);
+    apply_impulse(vb, imb, iib, -fx, -fy, rc.rbx[k], rc.rby[k]);
+  }
+  static __device__ __forceinline__ void solve_points(PairRec& rc, bool two, float ima, float iia, float imb, float iib,
+                                                      float4& va, float4& vb) {
+    solve_slot(rc, 0, ima, iia, imb, iib, va, vb);
+    if (two) solve_slot(rc, 1, ima, iia, imb, iib, va, vb);
+  }
+  // Batched schedule (A.8): slot q of a pair solved on private copies of the two bodies' velocities (the
+  // arithmetic of solve_slot); returns the normal impulse (jx, jy) and the friction impulse (fx, fy)
+  // that a receives, for the batch to apply afterwards, and the contact arms.  (With more than one batch
+  // the two points of a pair never share a batch, so one visit handles at most one of them: its
+  // constants are picked by q, which keeps the record in registers.)
+  static __device__ __forceinline__ void point_impulses(PairRec& rc, bool q, float ima, float iia, float imb, float iib,
+                                                        float4 va, float4 vb, float& jx, float& jy, float& fx,
+                                                        float& fy, float& rax, float& ray, float& rbx, float& rby) {
+    const float tx = -rc.ny, ty = rc.nx;
+    rax = q ? rc.rax[1] : rc.rax[0]; ray = q ? rc.ray[1] : rc.ray[0];
+    rbx = q ? rc.rbx[1] : rc.rbx[0]; rby = q ? rc.rby[1] : rc.rby[0];
+    const float mass_n = q ? rc.mass_n[1] : rc.mass_n[0], mass_t = q ? rc.mass_t[1] : rc.mass_t[0];
+    const float rest = q ? rc.rest[1] : rc.rest[0], bias = q ? rc.bias[1] : rc.bias[0];
+    const float lam_n = q ? rc.lam_n[1] : rc.lam_n[0], lam_t = q ? rc.lam_t[1] : rc.lam_t[0];
+    float rx, ry;
+    rel_vel(va, rax, ray, vb, rbx, rby, rx, ry);
+    float vn = dot2(rc.nx, rc.ny, rx, ry);
+    float dl = mass_n * (vn + rest + bias);
+    float ln = fmaxf(lam_n + dl, 0.f);
+    dl = ln - lam_n;
+    jx = (-dl) * rc.nx; jy = (-dl) * rc.ny;
+    apply_impulse(va, ima, iia, jx, jy, rax, ray);
+    apply_impulse(vb, imb, iib, -jx, -jy, rbx, rby);
+    rel_vel(va, rax, ray, vb, rbx, rby, rx, ry);
+    float vt = dot2(tx, ty, rx, ry);
+    float dt_ = -mass_t * vt;
+    float lim = rc.mu * ln;
+    float lt = fminf(fmaxf(lam_t + dt_, -lim), lim);
+    dt_ = lt - lam_t;
+    fx = dt_ * tx; fy = dt_ * ty;
+    if (q) { rc.lam_n[1] = ln; rc.lam_t[1] = lt; }
+    else { rc.lam_n[0] = ln; rc.lam_t[0] = lt; }
+  }
+  // Where the slots of a pair fall in the batched schedule: the manifold points, two per pair in tournament
+  // order, are dealt in turn over n_b batches.  Returns batch | place<<8 of slot 0, the same <<16 of slot 1.
+  static __device__ __forceinline__ int batch_places(int ab, int n_b) {
+    constexpr int odd = N & 1;   // the phantom's pair (place 0 of every round) is not a pair
+    const int a = ab & 0xff, b = (ab >> 8) & 0xff, r = round_of(a, b);
+    int kk = 0;
+    if (b != M - 1) {
+      kk = a - r;
+      if (kk < 0) kk += M - 1;
+      if (kk > M / 2 - 1) kk = M - 1 - kk;
+    }
+    const int s0 = 2 * (r * (K::PPR - odd) + kk - odd);
+    const int j0 = s0 / n_b, b0 = s0 - j0 * n_b;
+    int b1 = b0 + 1, j1 = j0;
+    if (b1 == n_b) { b1 = 0; j1 = j0 + 1; }
+    const int p0 = b0 | (j0 << 8), p1 = b1 | (j1 << 8);
+    return (ab & kSwapped) ? p1 : p0 | (p1 << 16);
+  }
+  // Warm starting of one pair (A.7): re-apply the kept accumulated impulses.
+  static __device__ __forceinline__ void warm_slot(const PairRec& rc, int k, float ima, float iia, float imb, float iib,
+                                                   float4& va, float4& vb) {
+    const float tx = -rc.ny, ty = rc.nx;
+    float jx = (-rc.lam_n[k]) * rc.nx + rc.lam_t[k] * tx;
+    float jy = (-rc.lam_n[k]) * rc.ny + rc.lam_t[k] * ty;
+    apply_impulse(va, ima, iia, jx, jy, rc.rax[k], rc.ray[k]);
+    apply_impulse(vb, imb, iib, -jx, -jy, rc.rbx[k], rc.rby[k]);
+  }
+  static __device__ __forceinline__ void warm_points(const PairRec& rc, bool two, float ima, float iia, float imb,
+                                                     float iib, float4& va, float4& vb) {
+    warm_slot(rc, 0, ima, iia, imb, iib, va, vb);
+    if (two) warm_slot(rc, 1, ima, iia, imb, iib, va, vb);
+  }
+
+  // A pair whose record is not held in registers (LDS pool or HBM): velocities through LDS, the bodies'
+  // constants looked up per visit.  WARM selects warm starting instead of a solver visit.
+  template <bool WARM>
+  static __device__ __forceinline__ void visit_pair(float* E, PairRec& rc, unsigned fixed) {
+    const int a = rc.ab & 0xff, b = (rc.ab >> 8) & 0xff;
+    float4 va = vel4(E, a), vb = vel4(E, b);
+    const float4 qa = prop4(E, a), qb = prop4(E, b);
+    if (WARM) warm_points(rc, rc.ab & kTwo, qa.x, qa.y, qb.x, qb.y, va, vb);
+    else solve_points(rc, rc.ab & kTwo, qa.x, qa.y, qb.x, qb.y, va, vb);
+    if (!((fixed >> a) & 1u)) vel4(E, a) = va;
+    if (!((fixed >> b) & 1u)) vel4(E, b) = vb;
+  }
+
+  // An active pair that a lane keeps in registers for one substep.
+  struct Own {
+    PairRec rc;
+    float ima, iia, imb, iib;
+    int pa, pb;   // shape indices
+    int sa, sb;   // where results go back: the shape itself, or entry N if no impulse moves it
+    bool have;
+    int lv;       // dependency level of this substep, -1 = nothing held
+  };
+  // Substep constants of an active pair from its manifold (A.3.5-A.3.7) and the accumulated impulses it
+  // keeps (A.7).  `w` packs a | b<<4 | active0<<8 | active1<<9 | active bits of the previous substep<<10;
+  // `lam` holds the stored impulses (n0, t0, n1, t1).
+  static __device__ __forceinline__ void presolve(float* E, const Params& prm, const Manifold& m, int w, float4 lam,
+                                                  PairRec& rc, float& ima, float& iia, float& imb, float& iib) {
+    const int a = w & 15, b = (w >> 4) & 15;
+    const bool swapped = !((w >> 8) & 1), two = ((w >> 8) & 3) == 3;
+    const unsigned prev = (unsigned)(w >> 10) & 3u;
+    rc.nx = m.nx; rc.ny = m.ny;
+    rc.ab = a | (b << 8) | (two ? kTwo : 0) | (swapped ? kSwapped : 0);
+    const float4 qa = prop4(E, a), qb = prop4(E, b);
+    ima = qa.x; iia = qa.y; imb = qb.x; iib = qb.y;
+    const float e = fminf(qa.w, qb.w);                                       // A.3.5
+    rc.mu = sqrtf(qa.z * qa.z + qb.z * qb.z);                                // A.3.6
+    const float2 pa = xy(E, a), pb = xy(E, b);
+    const float4 va = vel4(E, a), vb = vel4(E, b);
+    const float tx = -m.ny, ty = m.nx;
+    rc.rax[1] = rc.ray[1] = rc.rbx[1] = rc.rby[1] = rc.mass_n[1] = rc.mass_t[1] = rc.bias[1] = rc.rest[1] = 0.f;
+    rc.lam_n[1] = rc.lam_t[1] = 0.f;
+    auto slot = [&](int q, float px, float py, float pen, bool had, float ln, float lt) {
+      rc.rax[q] = px - pa.x; rc.ray[q] = py - pa.y;
+      rc.rbx[q] = px - pb.x; rc.rby[q] = py - pb.y;
+      float ran = cross2(rc.rax[q], rc.ray[q], m.nx, m.ny), rbn = cross2(rc.rbx[q], rc.rby[q], m.nx, m.ny);
+      float rat = cross2(rc.rax[q], rc.ray[q], tx, ty), rbt = cross2(rc.rbx[q], rc.rby[q], tx, ty);
+      float kn = ima + imb + ran * ran * iia + rbn * rbn * iib;
+      float kt = ima + imb + rat * rat * iia + rbt * rbt * iib;
+      rc.mass_n[q] = 1.f / kn;
+      rc.mass_t[q] = 1.f / kt;
+      rc.bias[q] = prm.alpha * fmaxf(pen - prm.slop, 0.f);                   // A.3.7
+      // restitution target -e*v_r (A.3.5), v_r sampled here: after motors and thrusters,
+      // before any constraint impulse; slow approaches take e = 0
+      float rx, ry;
+      rel_vel(va, rc.rax[q], rc.ray[q], vb, rc.rbx[q], rc.rby[q], rx, ry);
+      float vn0 = dot2(m.nx, m.ny, rx, ry);
+      rc.rest[q] = (vn0 > prm.rest_thr) ? e * vn0 : 0.f;
+      const bool keep = prm.warm_start && had;                                // A.7
+      rc.lam_n[q] = keep ? ln : 0.f;
+      rc.lam_t[q] = keep ? lt : 0.f;
+    };
+    const float pen0 = swapped ? m.pen[1] : m.pen[0];
+    slot(0, swapped ? m.px[1] : m.px[0], swapped ? m.py[1] : m.py[0], pen0, (swapped ? prev >> 1 : prev) & 1u,
+         swapped ? lam.z : lam.x, swapped ? lam.w : lam.y);
+    float pen = fmaxf(0.f, pen0);
+    if (two) {
+      slot(1, m.px[1], m.py[1], m.pen[1], prev >> 1, lam.z, lam.w);
+      pen = fmaxf(pen, m.pen[1]);
+    }
+    rc.corr = prm.beta * fmaxf(pen - prm.slop, 0.f) / (ima + imb);          // A.3.7
+  }
+  template <bool WARM>
+  static __device__ __forceinline__ void visit_own(float* E, Own& o) {
+    float4 va = vel4(E, o.pa), vb = vel4(E, o.pb);
+    const bool two = o.rc.ab & kTwo;
+    if (WARM) warm_points(o.rc, two, o.ima, o.iia, o.imb, o.iib, va, vb);
+    else solve_points(o.rc, two, o.ima, o.iia, o.imb, o.iib, va, vb);
+    vel4(E, o.sa) = va;
+    vel4(E, o.sb) = vb;
+  }
+};
+
+// RESET: after step s an environment e with reset_level[s * n_envs + e] = l >= 0 starts a new episode from
+// record l of `levels` (what k2d_reset does between launches, without leaving the kernel).
+// BATCHED: the collision constraints of a sweep are solved in the batches of A.8 instead of level by level.
+template <class K, bool RESET, bool BATCHED>
+__global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
+    k2d_step_kernel(float* __restrict__ state, const float* __restrict__ actions, int n_envs, int n_steps, Params prm,
+                    const float* __restrict__ levels, int n_level_records, const int32_t* __restrict__ reset_level,
+                    const int32_t* __restrict__ order
+#ifdef K2D_PHASE_TIMERS
+                    , unsigned long long* __restrict__ phase_clocks
+#endif
+                    ) {
+  using S = Step<K>;
+  using Own = typename S::Own;
+  constexpr k2d_layout L = K::L;
+  constexpr int N = K::N, P = K::P, J = K::J, T = K::T, G = K::G, R = K::R, A = K::A;
+  constexpr int NS = K::NS, QT = K::QT, ET = K::ET, TSP = K::TSP;
+  extern __shared__ __align__(16) float lds[];
+
+  const int lane = threadIdx.x;
+  const int g = lane / G, k = lane % G;
+  // the bits of a ballot that belong to this lane's environment, and how many of them lie below this lane
+  auto group_bits = [&](unsigned long long bal) { return (unsigned)(bal >> (g * G)) & ((1u << G) - 1u); };
+  const unsigned below = (1u << k) - 1u;
+  // which environment this lane works for: a launch may come with an ordering of the environments
+  // (slot -> environment, -1 = none) that puts similar ones together; without one, slot s is environment s
+  const int slot = blockIdx.x * K::EPW + g;
+  const int env = order ? order[slot] : (slot < n_envs ? slot : -1);
+  const bool env_ok = env >= 0;
+  float* E = lds + g * K::LDS_STRIDE;
+  float* Rg = state + (size_t)(env_ok ? env : 0) * K::REC_WORDS;   // this environment's HBM record
+  float* pool = E + K::X_POOL;
+  float* spill = Rg + K::G_SPILL;
+  unsigned char* pst = reinterpret_cast<unsigned char*>(E + K::X_PST);
+  unsigned short* cand_list = reinterpret_cast<unsigned short*>(E + K::X_LIST);
+  unsigned short* lt = reinterpret_cast<unsigned short*>(E + K::X_LT);
+  unsigned short* taken = reinterpret_cast<unsigned short*>(E + K::X_TAKEN);
+  unsigned char* lvl = reinterpret_cast<unsigned char*>(E + K::X_LVL);
+  unsigned char* sched = reinterpret_cast<unsigned char*>(E + K::X_SCHED);
+  float4* lam_store = reinterpret_cast<float4*>(E + K::X_LAM);
+  const float h = prm.h;
+
+#ifdef K2D_PHASE_TIMERS
+  long long t_acc[kT_Count] = {};
+  long long t_last = clock64();
+  unsigned long long t_pair_levels = 0, t_joint_levels = 0;
+#endif
+
+  // ---- what a lane keeps for a whole episode ----
+  unsigned sh_act = 0u, sh_fall = 0u;          // bit s: shape k + s * G is active / gravity acts on it
+  float c_radius[NS];                          // radius of shape k + s * G, if it is a circle
+  float lx[QT], ly[QT];                        // local coordinates of the lane's polygon vertices
+  unsigned static_mask = 0u, tri_mask = 0u;    // environment: shapes that no impulse can move; triangles
+  bool j_live = false, j_fixed = false, j_motor = false, j_limited = false, ja_fix = false, jb_fix = false;
+  int ja = 0, jb = 0, j_level = 0, n_levels = 0;
+  float j_aax = 0.f, j_aay = 0.f, j_abx = 0.f, j_aby = 0.f, j_thf = 0.f, j_speed = 0.f, j_power = 0.f, j_lo = 0.f, j_hi = 0.f;
+  float j_accx = 0.f, j_accy = 0.f, j_acca = 0.f;
+  float j_ima = 0.f, j_iia = 0.f, j_imb = 0.f, j_iib = 0.f, j_angm = 0.f, j_cf = 0.f;
+  bool t_live = false;
+  int t_body = 0;
+  float t_px = 0.f, t_py = 0.f, t_dx = 0.f, t_dy = 0.f, t_power = 0.f, t_im = 0.f, t_ii = 0.f;
+  int n_elig = 0;                              // eligible pairs of the environment; the lane's share of them:
+  unsigned my_ab[(ET + 3) / 4];                // shapes a | b << 4 of the lane's entries, a byte each
+  unsigned elig = 0u, pp_mask = 0u, pc_mask = 0u;
+  int held_a = -1, held_b = -1;                // shapes a | b << 8 of the pairs whose impulses wait in lam_store[k], [G + k]
+#pragma unroll
+  for (int i = 0; i < (ET + 3) / 4; ++i) my_ab[i] = 0u;
+#pragma unroll
+  for (int i = 0; i < NS; ++i) c_radius[i] = 0.f;
+#pragma unroll
+  for (int i = 0; i < QT; ++i) lx[i] = ly[i] = 0.f;
+
+  int step = 0;
+  bool fresh = true;                           // this lane's environment begins an episode (or the launch)
+  const float* src = Rg;                       // where its scene description is read from
+  do {   // (one pass, unless environments are re-initialised on the way)
+  // ---- episode set-up ----
+  if (fresh) {
+    const bool first = src == Rg;
+    auto word = [&](int w) { return env_ok ? src[w] : 0.f; };   // (padding environments: everything inactive)
+    unsigned act_bits = 0u, static_bits = 0u, tri_bits = 0u;
+    sh_act = 0u; sh_fall = 0u;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const int i = k + s * G;
+      bool act = false, fixed = true, tri = false;
+      if (i < N) {
+        const float im = word(L.inv_mass + i), ii = word(L.inv_inertia + i), th = word(L.theta + i);
+        act = f2i(word(L.shape_flags + i)) & 1;
+        fixed = !act || (im == 0.f && ii == 0.f);
+        if (act) sh_act |= 1u << s;
+        if (act && im > 0.f) sh_fall |= 1u << s;
+        float sn, cs;
+        k2d_sincos(th, sn, cs);
+        S::pos4(E, i) = make_float4(word(L.pos_x + i), word(L.pos_y + i), cs, sn);
+        S::vel4(E, i) = make_float4(word(L.vel_x + i), word(L.vel_y + i), word(L.omega + i), th);
+        S::prop4(E, i) = make_float4(im, ii, word(L.friction + i), word(L.restitution + i));
+        E[K::X_JOINED + i] = i2f(0);
+        if (i < P) tri = f2i(word(L.n_verts + i)) == 3;
+        else { c_radius[s] = word(L.radius + (i - P)); E[K::X_RAD + (i - P)] = c_radius[s]; }
+      }
+      act_bits |= group_bits(__ballot(act)) << (s * G);
+      static_bits |= group_bits(__ballot(fixed)) << (s * G);
+      tri_bits |= group_bits(__ballot(tri)) << (s * G);
+    }
+    static_mask = static_bits;
+    tri_mask = tri_bits;
+#pragma unroll
+    for (int q = 0; q < QT; ++q) {
+      const int p = q * (G / 4) + k / 4, v = k & 3;
+      if (p < P) {
+        const int vv = (v == 3 && ((tri_bits >> p) & 1u)) ? 0 : v;   // a triangle's spare slot repeats vertex 0: the manifold
+        lx[q] = word(L.verts + (2 * vv) * P + p);                    // code can then run over four vertices
+        ly[q] = word(L.verts + (2 * vv + 1) * P + p);
+      }
+    }
+    // joints: lane j of the group owns joint j for the whole episode
+    j_live = false;
+    ja = 0; jb = 0;
+    wave_sync();
+    if (k < J) {
+      const int fl = f2i(word(L.joint_flags + k));
+      ja = f2i(word(L.joint_a + k));
+      jb = f2i(word(L.joint_b + k));
+      const bool idx_ok = ja >= 0 && ja < N && jb >= 0 && jb < N && ja != jb;
+      if (!idx_ok) { ja = 0; jb = 0; }
+      const float4 qa = S::prop4(E, ja), qb = S::prop4(E, jb);
+      j_ima = qa.x; j_iia = qa.y; j_imb = qb.x; j_iib = qb.y;
+      j_fixed = (fl >> 1) & 1;
+      j_motor = (fl >> 2) & 1;
+      j_limited = ((fl >> 4) & 1) && !j_fixed;
+      j_live = (fl & 1) && idx_ok && ((act_bits >> ja) & 1u) && ((act_bits >> jb) & 1u) && (j_ima + j_imb) > 0.f;
+      j_aax = word(L.anchor_a_x + k); j_aay = word(L.anchor_a_y + k);
+      j_abx = word(L.anchor_b_x + k); j_aby = word(L.anchor_b_y + k);
+      j_thf = word(L.theta_f + k); j_speed = word(L.motor_speed + k); j_power = word(L.motor_power + k);
+      j_lo = word(L.limit_lo + k); j_hi = word(L.limit_hi + k);
+      j_accx = j_accy = j_acca = 0.f;
+      if (first) {
+        j_accx = word(L.acc_x + k); j_accy = word(L.acc_y + k); j_acca = word(L.acc_ang + k);
+        if (!j_live) { j_accx = 0.f; j_accy = 0.f; j_acca = 0.f; }
+        if (!j_fixed) j_acca = 0.f;
+      }
+      const float is = j_iia + j_iib;
+      j_angm = (is > 0.f) ? 1.f / is : 0.f;
+      j_cf = prm.joint_beta / (j_ima + j_imb);
+      if (j_live) {   // A.4: joined shapes do not collide
+        atomicOr(reinterpret_cast<unsigned*>(E + K::X_JOINED + ja), 1u << jb);
+        atomicOr(reinterpret_cast<unsigned*>(E + K::X_JOINED + jb), 1u << ja);
+      }
+      E[K::X_JINFO + k] = i2f(ja | (jb << 8) | (j_live ? 1 << 16 : 0));
+    }
+    ja_fix = (static_mask >> ja) & 1u;
+    jb_fix = (static_mask >> jb) & 1u;
+    wave_sync();
+    // dependency levels of the joints: a joint runs one level after the last earlier joint that shares a
+    // movable shape with it, so joints sharing a shape keep their index order, the others run side by side
+    j_level = 0; n_levels = 0;
+    {
+      unsigned long long last = 0ull;   // 4 bits per shape: next free level
+#pragma unroll
+      for (int q = 0; q < J; ++q) {
+        const int info = f2i(E[K::X_JINFO + q]);
+        if (info & (1 << 16)) {
+          const int a = info & 255, b = (info >> 8) & 255;
+          const bool da = !((static_mask >> a) & 1u), db = !((static_mask >> b) & 1u);
+          const int la = da ? (int)((last >> (4 * a)) & 15ull) : 0, lb = db ? (int)((last >> (4 * b)) & 15ull) : 0;
+          const int lv = max(la, lb);
+          if (q == k) j_level = lv;
+          n_levels = max(n_levels, lv + 1);
+          if (da) last = (last & ~(15ull << (4 * a))) | ((unsigned long long)(lv + 1) << (4 * a));
+          if (db) last = (last & ~(15ull << (4 * b))) | ((unsigned long long)(lv + 1) << (4 * b));
+        }
+      }
+    }
+    // thrusters: lane t of the group owns thruster t
+    t_live = false;
+    if (k < T) {
+      const int fl = f2i(word(L.thr_flags + k));
+      t_body = f2i(word(L.thr_body + k));
+      const bool idx_ok = t_body >= 0 && t_body < N;
+      if (!idx_ok) t_body = 0;
+      t_live = (fl & 1) && idx_ok && ((act_bits >> t_body) & 1u);
+      t_px = word(L.thr_pos_x + k); t_py = word(L.thr_pos_y + k);
+      k2d_sincos(word(L.thr_angle + k), t_dy, t_dx);
+      t_power = word(L.thr_power + k);
+      const float4 q = S::prop4(E, t_body);
+      t_im = q.x; t_ii = q.y;
+    }
+    // The eligible pairs (both shapes active, not joined, not both of infinite mass) are listed in tournament
+    // order and dealt over the lanes: a pair that can never collide costs the cull nothing.
+    {
+      unsigned char* list = reinterpret_cast<unsigned char*>(E + K::X_ELIG);
+      n_elig = 0;
+      for (int q0 = 0; q0 < R * K::PPR; q0 += G) {
+        const int q = q0 + k;
+        int a = 0, b = 0;
+        bool ok = q < R * K::PPR && S::sched_pair(q / K::PPR, q % K::PPR, a, b);
+        if (ok) {
+          ok = ((act_bits >> a) & 1u) && ((act_bits >> b) & 1u) && !((f2i(E[K::X_JOINED + a]) >> b) & 1) &&
+               (S::prop4(E, a).x + S::prop4(E, b).x) > 0.f;
+        }
+        const unsigned bits = group_bits(__ballot(ok));
+        if (ok) list[n_elig + __popc(bits & below)] = (unsigned char)(a | (b << 4));
+        n_elig += __popc(bits);
+      }
+      wave_sync();
+      elig = 0u; pp_mask = 0u; pc_mask = 0u;
+#pragma unroll
+      for (int i = 0; i < (ET + 3) / 4; ++i) my_ab[i] = 0u;
+#pragma unroll
+      for (int t = 0; t < TSP; ++t) {
+        unsigned char ps = 0;
+        const int e = t * G + k;
+        if (t < ET && e < n_elig) {
+          const int ab = list[e], a = ab & 15, b = ab >> 4;
+          my_ab[t >> 2] |= (unsigned)ab << (8 * (t & 3));
+          elig |= 1u << t;
+          if (b < P) pp_mask |= 1u << t;
+          else if (a < P) pc_mask |= 1u << t;
+          if (first) {
+            ps = reinterpret_cast<const unsigned char*>(Rg + L.pair_state)[S::pair_index(a, b)] & 3;
+            if (ps) ps |= kInRecord << 2;
+          }
+        }
+        pst[k * TSP + t] = ps;
+      }
+    }
+    held_a = -1; held_b = -1;
+    fresh = false;
+  }
+  wave_sync();
+  // levels and list lengths are per environment; the wavefront walks as many as its largest one has
+  int wave_levels = 0, cull_trips = 0;
+#pragma unroll
+  for (int lv = 1; lv <= J; ++lv)
+    if (__any(n_levels >= lv)) wave_levels = lv;
+#pragma unroll
+  for (int t = 0; t < ET; ++t)
+    if (__any(n_elig > t * G)) cull_trips = t + 1;
+  const bool any_motor = __any(j_live && j_motor && !j_fixed);
+  const bool any_angular = __any(j_live && (j_fixed || j_limited));
+  // where a joint's results go: the shape, or the entry that swallows them if no impulse moves the shape
+  const int jsa = ja_fix ? N : ja, jsb = jb_fix ? N : jb;
+  // Dependency levels of the collision constraints are kept from one substep to the next: they depend
+  // only on which pairs collide and which lane keeps which pair, and both are the same in most consecutive
+  // substeps.  Likewise the list of candidate pairs (it stays in LDS) while no lane's candidates change.
+  int wave_clevels = 0;       // levels of the wavefront's deepest environment
+  int lv_a = -1, lv_b = -1;   // levels of the lane's pairs
+  bool levels_valid = false;  // false until the levels of the current set of colliding pairs are worked out
+  unsigned prev_cand = 0u, kind_tot = 0u;
+  bool list_valid = false;
+
+  for (; step < n_steps; ++step) {
+    float act_m = 0.f, act_t = 0.f;
+    int new_level = -1;
+    if (env_ok) {
+      const size_t row = (size_t)step * n_envs + env;
+      if (k < J) act_m = actions[row * A + k];
+      if (k < T) act_t = actions[row * A + J + k];
+      if (RESET) new_level = reset_level[row];
+    }
+    if (prm.clip_thr) act_t = fminf(fmaxf(act_t, 0.f), 1.f);
+
+    K2D_T(kT_Actions);
+    for (int sub = 0; sub < prm.n_substeps; ++sub) {
+      // ---- gravity (Alg. 1), bounding boxes of the circles ----
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const int i = k + s * G;
+        if ((sh_fall >> s) & 1u) {
+          float* vy = E + K::X_VEL + 4 * i + 1;
+          *vy = *vy + prm.gravity_y * h;
+        }
+        if (i >= P && i < N) {
+          const float2 p = S::xy(E, i);
+          const float r = c_radius[s] + kCullMargin;
+          S::box4(E, i) = make_float4(p.x - r, p.y - r, p.x + r, p.y + r);
+        }
+      }
+      // ---- world-frame polygons: four neighbouring lanes share one, each has a vertex and the edge behind it ----
+#pragma unroll
+      for (int q = 0; q < QT; ++q) {
+        const int p = q * (G / 4) + k / 4, v = k & 3;
+        if (p < P) {
+          const float4 f = S::pos4(E, p);   // x, y, cos, sin
+          const float wx = f.x + fmaf(f.z, lx[q], -(f.w * ly[q]));
+          const float wy = f.y + fmaf(f.w, lx[q], f.z * ly[q]);
+          const float ex = K2D_DPPF(wx, kQuadNext) - wx, ey = K2D_DPPF(wy, kQuadNext) - wy;
+          const float len = sqrtf(dot2(ex, ey, ex, ey));
+          S::wv(E, v, p) = make_float2(wx, wy);
+          S::wn(E, v, p) = make_float2(ey / len, -ex / len);
+          float x0 = fminf(wx, K2D_DPPF(wx, kQuadXor1)), x1 = fmaxf(wx, K2D_DPPF(wx, kQuadXor1));
+          float y0 = fminf(wy, K2D_DPPF(wy, kQuadXor1)), y1 = fmaxf(wy, K2D_DPPF(wy, kQuadXor1));
+          x0 = fminf(x0, K2D_DPPF(x0, kQuadXor2)); x1 = fmaxf(x1, K2D_DPPF(x1, kQuadXor2));
+          y0 = fminf(y0, K2D_DPPF(y0, kQuadXor2)); y1 = fmaxf(y1, K2D_DPPF(y1, kQuadXor2));
+          if (v == 0) S::box4(E, p) = make_float4(x0 - kCullMargin, y0 - kCullMargin, x1 + kCullMargin, y1 + kCullMargin);
+        }
+      }
+      wave_sync();
+
+      K2D_T(kT_Shapes);
+      // ---- joint constants of this substep; motor and thruster impulses from the same velocities ----
+      float j_rax = 0.f, j_ray = 0.f, j_rbx = 0.f, j_rby = 0.f, j_k11 = 0.f, j_k12 = 0.f, j_k22 = 0.f;
+      float j_idet = 0.f, j_bx = 0.f, j_by = 0.f, j_angb = 0.f, j_exc = 0.f, motor = 0.f;
+      if (k < J && j_live) {
+        if (!prm.warm_start) { j_accx = 0.f; j_accy = 0.f; j_acca = 0.f; }
+        const float4 fa = S::pos4(E, ja), fb = S::pos4(E, jb);
+        const float4 va = S::vel4(E, ja), vb = S::vel4(E, jb);
+        j_rax = fmaf(fa.z, j_aax, -(fa.w * j_aay)); j_ray = fmaf(fa.w, j_aax, fa.z * j_aay);
+        j_rbx = fmaf(fb.z, j_abx, -(fb.w * j_aby)); j_rby = fmaf(fb.w, j_abx, fb.z * j_aby);
+        const float ms = j_ima + j_imb;
+        j_k11 = ms + j_iia * j_ray * j_ray + j_iib * j_rby * j_rby;
+        j_k22 = ms + j_iia * j_rax * j_rax + j_iib * j_rbx * j_rbx;
+        j_k12 = -j_iia * j_rax * j_ray - j_iib * j_rbx * j_rby;
+        j_idet = 1.f / (j_k11 * j_k22 - j_k12 * j_k12);
+        const float sx = (fa.x + j_rax) - (fb.x + j_rbx);
+        const float sy = (fa.y + j_ray) - (fb.y + j_rby);
+        j_bx = prm.joint_alpha * sx; j_by = prm.joint_alpha * sy;
+        j_angb = prm.gamma * (va.w - vb.w - j_thf);
+        if (j_limited) {   // A.4.3: rotation beyond a limit, decided once per substep
+          const float rel = va.w - vb.w;
+          if (rel > j_hi) j_exc = rel - j_hi;
+          else if (rel < j_lo) j_exc = rel - j_lo;
+          j_angb = prm.gamma * j_exc;
+        }
+        if (!j_fixed && j_motor) {   // A.5
+          const float arg = (va.z - vb.z - j_speed * act_m) * prm.rho;
+          motor = j_power * k2d_tanh(arg) * h;
+        }
+      }
+      float t_ix = 0.f, t_iy = 0.f, t_rx = 0.f, t_ry = 0.f;
+      if (k < T && t_live) {   // A.6
+        const float4 f = S::pos4(E, t_body);
+        const float dx = fmaf(f.z, t_dx, -(f.w * t_dy)), dy = fmaf(f.w, t_dx, f.z * t_dy);
+        t_rx = fmaf(f.z, t_px, -(f.w * t_py)); t_ry = fmaf(f.w, t_px, f.z * t_py);
+        const float force = t_power * act_t * h;
+        t_ix = force * dx; t_iy = force * dy;
+      }
+      K2D_T(kT_JointConstants);
+      wave_sync();
+      if (any_motor)
+        for (int lv = 0; lv < wave_levels; ++lv) {
+          if (k < J && j_live && j_level == lv && motor != 0.f) {
+            float *wa = E + K::X_VEL + 4 * ja + 2, *wb = E + K::X_VEL + 4 * jb + 2;
+            if (!ja_fix) *wa = *wa - j_iia * motor;
+            if (!jb_fix) *wb = *wb + j_iib * motor;
+          }
+          wave_sync();
+        }
+      for (int t = 0; t < T; ++t) {
+        if (k == t && t_live) {
+          float4 v = S::vel4(E, t_body);
+          apply_impulse(v, t_im, t_ii, t_ix, t_iy, t_rx, t_ry);
+          S::vel4(E, t_body) = v;
+        }
+        wave_sync();
+      }
+
+      K2D_T(kT_External);
+      // ---- collision manifolds of all eligible pairs (A.3.1-A.3.4) and their substep constants ----
+      // 1. the cheap test for all of this lane's pairs: bounding boxes (of the very world vertices and
+      //    centres the manifolds use, grown by a margin a thousand times the rounding error of a
+      //    coordinate) that do not overlap mean no manifold point can have positive penetration;
+      // 2. the surviving pairs of the environment are gathered into one list, one shape-type mix
+      //    after the other, so that the group's lanes share them evenly and a wavefront runs one kind
+      //    of manifold code per trip;
+      // 3. the manifold of every active pair is staged in LDS for the lane that keeps the pair in
+      //    registers for the rest of the substep (pairs beyond two per lane become records in LDS / HBM).
+      unsigned cand = 0u;
+      bool set_changed = false;   // a pair of this lane collides now and did not one substep ago, or the reverse
+#pragma unroll
+      for (int t = 0; t < ET; ++t)
+        if (t < cull_trips) {
+          const unsigned ab = my_ab[t >> 2] >> (8 * (t & 3));
+          const float4 ba = S::box4(E, ab & 15), bb = S::box4(E, (ab >> 4) & 15);
+          if (ba.x <= bb.z && bb.x <= ba.z && ba.y <= bb.w && bb.y <= ba.w) cand |= 1u << t;
+        }
+      cand &= elig;
+      {   // pairs that were colliding and are not even candidates now: their points are no longer active
+        unsigned nz = 0u;
+#pragma unroll
+        for (int i = 0; i < TSP / 4; ++i) {
+          const unsigned w = reinterpret_cast<const unsigned*>(pst)[k * (TSP / 4) + i];
+          const unsigned m = (w | (w >> 1)) & 0x01010101u;               // bit 8 j: entry 4 i + j was colliding
+          nz |= ((m * 0x01020408u) >> 24) << (4 * i);
+        }
+        const unsigned gone = nz & ~cand;
+        set_changed = gone != 0u;
+        for (unsigned st = gone; st != 0u; st &= st - 1u) pst[k * TSP + (__ffs(st) - 1)] = 0;
+      }
+      const bool same_list = list_valid && !__any(cand != prev_cand);
+      prev_cand = cand;
+      list_valid = true;
+      if (!same_list) {
+        unsigned* cnt = reinterpret_cast<unsigned*>(E + K::X_CNT);
+        if (k == 0) *cnt = 0u;
+        wave_sync();
+        const unsigned m0 = cand & pp_mask, m1 = cand & pc_mask, m2 = cand & ~(pp_mask | pc_mask);
+        const unsigned mine = (unsigned)__popc(m0) | ((unsigned)__popc(m1) << 8) | ((unsigned)__popc(m2) << 16);
+        const unsigned at = atomicAdd(cnt, mine);   // the lane's places among the candidates of each mix
+        wave_sync();
+        kind_tot = *cnt;
+        const int w0 = (int)(at & 255), w1 = (int)(kind_tot & 255) + (int)((at >> 8) & 255);
+        const int w2 = (int)(kind_tot & 255) + (int)((kind_tot >> 8) & 255) + (int)((at >> 16) & 255);
+        auto put = [&](unsigned m, int w) {
+          for (; m != 0u; m &= m - 1u) {
+            const int t = __ffs(m) - 1;
+            unsigned ab = my_ab[0];
+#pragma unroll
+            for (int i = 1; i < (ET + 3) / 4; ++i) ab = (t >> 2) == i ? my_ab[i] : ab;
+            ab = (ab >> (8 * (t & 3))) & 255u;
+            cand_list[w++] = (unsigned short)(ab | ((k * TSP + t) << 8));
+          }
+        };
+        put(m0, w0);
+        put(m1, w1);
+        put(m2, w2);
+      }
+      wave_sync();
+      K2D_T(kT_Cull);
+      int n_act = 0;   // active pairs of the environment so far
+      // `lead`: this lane has the manifold m of candidate e (a pair that lanes share: the first of them)
+      auto emit = [&](bool lead, const Manifold& m, unsigned e, int prev) {
+        const bool act0 = lead && m.valid[0] && m.pen[0] > 0.f, act1 = lead && m.valid[1] && m.pen[1] > 0.f;
+        const bool active = act0 || act1;
+        set_changed |= lead && (((prev & 3) != 0) != active);
+        const unsigned bits = group_bits(__ballot(active));
+        const int idx = n_act + __popc(bits & below);
+        n_act += __popc(bits);
+        int now = 0;
+        if (active) {
+          const int ab = e & 255;
+          const int w = ab | ((int)act0 << 8) | ((int)act1 << 9) | (prev << 10);
+          now = (int)act0 | ((int)act1 << 1) | ((idx < K::LAMN ? idx : kInRecord) << 2);
+          if (idx < K::NREG) {   // staged for the lane that keeps it
+            float4* p = reinterpret_cast<float4*>(E + K::X_STAGE + idx * K::kManW);
+            p[0] = make_float4(m.nx, m.ny, m.px[0], m.py[0]);
+            p[1] = make_float4(m.pen[0], m.px[1], m.py[1], m.pen[1]);
+            reinterpret_cast<int*>(p)[8] = w;
+          } else if constexpr (K::LISTED > 0) {   // beyond the register-held pairs: a full record in the LDS pool or in HBM
+            const int a = ab & 15, b = ab >> 4;
+            float4 lam = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (prm.warm_start && (prev & 3)) {
+              if ((prev >> 2) != kInRecord) lam = lam_store[prev >> 2];
+              else lam = *reinterpret_cast<const float4*>(Rg + L.lambda + 4 * S::pair_index(a, b));
+            }
+            PairRec rc;
+            float ima, iia, imb, iib;
+            S::presolve(E, prm, m, w, lam, rc, ima, iia, imb, iib);
+            if (idx < K::NREG + K::POOL) rec_store(to_lds(pool + (idx - K::NREG) * kRecW), rc);
+            else rec_store(spill + (idx - K::NREG - K::POOL) * kRecW, rc);
+            lt[idx - K::NREG] = (unsigned short)ab;
+          }
+        }
+        if (lead) pst[e >> 8] = (unsigned char)now;
+      };
+      const int n_pp = kind_tot & 255, n_pc = (kind_tot >> 8) & 255, n_cc = (kind_tot >> 16) & 255;
+      auto run_pp = [&](auto width) {
+        constexpr int W = decltype(width)::value;
+        for (int base = 0; __any(base < n_pp); base += G / W) {
+          Manifold m;
+          const int c = base + k / W;
+          const bool have = c < n_pp;
+          const unsigned e = have ? cand_list[c] : 0u;
+          const int prev = have ? (int)pst[e >> 8] : 0;
+          if (have) {
+            const int a = e & 15, b = (e >> 4) & 15;
+            S::template manifold_pp<W>(E, k % W, a, (tri_mask >> a) & 1u, b, (tri_mask >> b) & 1u, prm.tie_eps, m);
+          }
+          emit(have && k % W == 0, m, e, prev);
+        }
+      };
+      auto run_pc = [&](auto width) {
+        constexpr int W = decltype(width)::value;
+        for (int base = 0; __any(base < n_pc); base += G / W) {
+          Manifold m;
+          const int c = base + k / W;
+          const bool have = c < n_pc;
+          const unsigned e = have ? cand_list[n_pp + c] : 0u;
+          const int prev = have ? (int)pst[e >> 8] : 0;
+          if (have) {
+            const int a = e & 15, b = (e >> 4) & 15;
+            const float2 p = S::xy(E, b);
+            S::template manifold_pc<W>(E, k % W, a, (tri_mask >> a) & 1u, p.x, p.y, E[K::X_RAD + (b - P)], m);
+          }
+          emit(have && k % W == 0, m, e, prev);
+        }
+      };
+      // polygon pairs: two lanes each while every environment's fit into one trip that way
+      if (!__any(n_pp > G / 2)) run_pp(std::integral_constant<int, 2>{});
+      else run_pp(std::integral_constant<int, 1>{});
+      // polygon-circle pairs: four lanes each while they fit into one trip, else two
+      if (!__any(n_pc > G / 4)) run_pc(std::integral_constant<int, 4>{});
+      else run_pc(std::integral_constant<int, 2>{});
+      for (int base = 0; __any(base < n_cc); base += G) {
+        Manifold m;
+        const int c = base + k;
+        const bool have = c < n_cc;
+        const unsigned e = have ? cand_list[n_pp + n_pc + c] : 0u;
+        const int prev = have ? (int)pst[e >> 8] : 0;
+        if (have) {
+          const int a = e & 15, b = (e >> 4) & 15;
+          const float2 pa = S::xy(E, a), pb = S::xy(E, b);
+          S::manifold_cc(pa.x, pa.y, E[K::X_RAD + (a - P)], pb.x, pb.y, E[K::X_RAD + (b - P)], m);
+        }
+        emit(have, m, e, prev);
+      }
+      wave_sync();
+      K2D_T(kT_Manifolds);
+      // lane k keeps active pairs k and G + k of its environment in registers
+      Own oa, ob;
+      oa.have = false; ob.have = false; oa.lv = -1; ob.lv = -1;
+      oa.rc.ab = 0; ob.rc.ab = 0;
+      auto take = [&](int idx, Own& o) {   // picks a staged manifold up and derives the record in its own registers
+        const float4* p = reinterpret_cast<const float4*>(E + K::X_STAGE + idx * K::kManW);
+        const float4 p0 = p[0], p1 = p[1];
+        const int w = reinterpret_cast<const int*>(p)[8];
+        Manifold m;
+        m.nx = p0.x; m.ny = p0.y; m.px[0] = p0.z; m.py[0] = p0.w;
+        m.pen[0] = p1.x; m.px[1] = p1.y; m.py[1] = p1.z; m.pen[1] = p1.w;
+        const int a = w & 15, b = (w >> 4) & 15, prev = w >> 10;
+        float4 lam = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (prm.warm_start && (prev & 3)) {   // the impulses it accumulated
+          if ((prev >> 2) != kInRecord) lam = lam_store[prev >> 2];
+          else lam = *reinterpret_cast<const float4*>(Rg + L.lambda + 4 * S::pair_index(a, b));
+        }
+        S::presolve(E, prm, m, w, lam, o.rc, o.ima, o.iia, o.imb, o.iib);
+        o.pa = a; o.pb = b;
+        o.sa = ((static_mask >> a) & 1u) ? N : a;
+        o.sb = ((static_mask >> b) & 1u) ? N : b;
+        o.have = true;
+      };
+      if (k < n_act && k < K::NREG) take(k, oa);
+      bool any_b = false;   // a lane of the wavefront holds a second pair
+      if constexpr (K::TWO) {
+        any_b = __any(n_act > G);
+        if (any_b && k + G < n_act && k + G < K::NREG) take(k + G, ob);
+      }
+      const int n_listed = max(n_act - K::NREG, 0);
+      const bool any_listed = K::LISTED > 0 && __any(n_listed > 0);
+      wave_sync();
+      K2D_T(kT_Presolve);
+      // Levels of the active pairs.  The colliding pairs are walked in tournament order (round by round).
+      // k2d_params.sweep_order = K2D_SWEEP_TOURNAMENT: the sweep visits them in that order, and a pair is
+      // placed one level after the last earlier colliding pair that shares a movable shape with it --
+      // pairs that share one keep their order, so sweeping the levels in turn, each level at once, gives
+      // the same bits as the one-after-the-other sweep in tournament order.
+      // K2D_SWEEP_LEVELS: a pair takes the lowest level that no earlier colliding pair sharing a movable
+      // shape with it has taken, and the sweep's order *is* level 0, then level 1, ...: as few trips as
+      // the busiest shape has contacts (or one more).
+      // Either way the pairs of a level touch disjoint movable shapes, everything resting on the static
+      // floor is one level, and a level never exceeds the round.
+      unsigned long long level_cnt = 0ull;   // listed pairs per level, 4 bits each (a level holds fewer than 16)
+      if (!levels_valid || !same_list || any_listed || __any(set_changed)) {
+        auto movable = [&](int a, int b) { return ((1u << a) | (1u << b)) & ~static_mask; };
+        int my_levels = 0;
+        if (!any_b) {
+          // One pair per lane at most: every lane learns which of the environment's pairs come earlier and share
+          // a movable shape with its own (a round's pairs are disjoint, so the order of the rounds decides), and a
+          // pair can be placed once all of those are.
+          const unsigned mine = oa.have ? (unsigned)S::round_of(oa.pa, oa.pb) << 16 | movable(oa.pa, oa.pb) : 0u;
+          unsigned wait = 0u;
+          int most = 0;
+#pragma unroll
+          for (int z = 1; z <= G; ++z)
+            if (__any(n_act >= z)) most = z;
+          auto meet = [&](auto z) {
+            constexpr int q = decltype(z)::value;
+            if (q < most) {
+              const unsigned o = group_bcast<G, q>(mine, g);
+              if ((o & mine & 0xffffu) != 0u && o < mine) wait |= 1u << q;
+            }
+          };
+          meet(std::integral_constant<int, 0>{}); meet(std::integral_constant<int, 1>{}); meet(std::integral_constant<int, 2>{});
+          meet(std::integral_constant<int, 3>{}); meet(std::integral_constant<int, 4>{}); meet(std::integral_constant<int, 5>{});
+          meet(std::integral_constant<int, 6>{}); meet(std::integral_constant<int, 7>{});
+          if constexpr (G == 16) {
+            meet(std::integral_constant<int, 8>{}); meet(std::integral_constant<int, 9>{}); meet(std::integral_constant<int, 10>{});
+            meet(std::integral_constant<int, 11>{}); meet(std::integral_constant<int, 12>{}); meet(std::integral_constant<int, 13>{});
+            meet(std::integral_constant<int, 14>{}); meet(std::integral_constant<int, 15>{});
+          }
+          int lv = oa.have ? -1 : 0;
+          unsigned placed = 0u, busy = 0u;   // pairs placed so far; levels taken by the earlier pairs of the lane's shapes
+          for (int round = 0; __any(lv < 0); ++round) {   // (at least the earliest unplaced pair is placed every time)
+            const bool now = lv < 0 && (wait & ~placed) == 0u;
+            if (now) lv = prm.lowest_free_level ? __ffs((int)~busy) - 1 : round;
+            if (prm.lowest_free_level)
+              for (int l = 0; l <= round; ++l)
+                if (wait & group_bits(__ballot(now && lv == l))) busy |= 1u << l;
+            placed |= group_bits(__ballot(now));
+          }
+          if (oa.have) { oa.lv = lv; my_levels = lv + 1; }
+        } else {
+          // Some lane holds more than one pair: round by round, through the sets of levels taken at every shape
+          // (16-bit words in LDS).  The pairs of a round touch disjoint shapes, so the lanes of a round read and
+          // extend those sets without getting in each other's way, and the rounds follow one another.
+          if (k < (N + 1) / 2) reinterpret_cast<unsigned*>(taken)[k] = 0u;
+          if (G < (N + 1) / 2 && k + G < (N + 1) / 2) reinterpret_cast<unsigned*>(taken)[k + G] = 0u;
+          wave_sync();
+          auto place = [&](int a, int b) {
+            const bool ma = !((static_mask >> a) & 1u), mb = !((static_mask >> b) & 1u);
+            const unsigned ta = ma ? (unsigned)taken[a] : 0u, tb = mb ? (unsigned)taken[b] : 0u;
+            const int lv = prm.lowest_free_level ? __ffs((int)~(ta | tb)) - 1 : 32 - __clz((int)(ta | tb));
+            if (ma) taken[a] = (unsigned short)(ta | (1u << lv));
+            if (mb) taken[b] = (unsigned short)(tb | (1u << lv));
+            my_levels = max(my_levels, lv + 1);
+            return lv;
+          };
+          const int ra = oa.have ? S::round_of(oa.pa, oa.pb) : -1, rb = ob.have ? S::round_of(ob.pa, ob.pb) : -1;
+          for (int r = 0; r < R; ++r) {
+            if (ra == r) oa.lv = place(oa.pa, oa.pb);
+            if (rb == r) ob.lv = place(ob.pa, ob.pb);
+            if (any_listed)
+              for (int q = k; __any(q < n_listed); q += G)
+                if (q < n_listed && S::round_of(lt[q] & 15, lt[q] >> 4) == r) lvl[q] = (unsigned char)place(lt[q] & 15, lt[q] >> 4);
+            wave_sync();
+          }
+        }
+        wave_clevels = 0;
+        for (int lv = 1; lv <= R; ++lv)
+          if (__any(my_levels >= lv)) wave_clevels = lv;
+        levels_valid = true;
+        lv_a = oa.lv; lv_b = ob.lv;
+        // the pairs that are not held in registers are listed level by level (lane s mod G writes entry s)
+        if (any_listed) {
+          for (int q = 0; __any(q < n_listed); ++q)
+            if (q < n_listed) {
+              const int lv = lvl[q];
+              const int slot = (int)((level_cnt >> (4 * lv)) & 15ull);
+              level_cnt += 1ull << (4 * lv);
+              if ((slot & (G - 1)) == k) sched[lv * K::LCAP + slot] = (unsigned char)q;
+            }
+          wave_sync();
+        }
+      }
+      oa.lv = lv_a; ob.lv = lv_b;
+      auto cnt_of = [&](int lv) { return (int)((level_cnt >> (4 * lv)) & 15ull); };
+      // one level at a time: the pairs held in registers (first and second of the lane), then the listed ones
+      auto for_each_level = [&](auto&& f_own, auto&& f_listed) {
+        if (!any_b && !any_listed) {   // the common case, as a loop of its own: one pair per lane, all in registers
+          for (int lv = 0; lv < wave_clevels; ++lv) {
+            if (oa.lv == lv) f_own(oa);
+            wave_sync();
+          }
+          return;
+        }
+        for (int lv = 0; lv < wave_clevels; ++lv) {
+          if (oa.lv == lv) f_own(oa);
+          if constexpr (K::TWO) {
+            if (any_b) {
+              if (ob.lv == lv) f_own(ob);
+            }
+          }
+          if constexpr (K::LISTED > 0) {
+            if (any_listed) {
+              const int c = cnt_of(lv);
+              for (int base = 0; __any(base < c); base += G)
+                if (base + k < c) f_listed((int)sched[lv * K::LCAP + base + k]);
+            }
+          }
+          wave_sync();
+        }
+      };
+
+      K2D_T(kT_Levels);
+#ifdef K2D_PHASE_TIMERS
+      t_pair_levels += wave_clevels; t_joint_levels += wave_levels;
+#endif
+      // ---- warm starting (Alg. 1, A.7): collisions level after level, then joints ----
+      if (prm.warm_start) {
+        for_each_level([&](Own& o) { S::template visit_own<true>(E, o); },
+                       [&](int q) {
+                         PairRec rc;
+                         if (q < K::POOL) rec_load(to_lds(pool + q * kRecW), rc);
+                         else rec_load(spill + (q - K::POOL) * kRecW, rc);
+                         S::template visit_pair<true>(E, rc, static_mask);
+                       });
+        for (int lv = 0; lv < wave_levels; ++lv) {
+          if (k < J && j_live && j_level == lv) {
+            float4 va = S::vel4(E, ja), vb = S::vel4(E, jb);
+            if (j_fixed) {
+              va.z = va.z + j_iia * j_acca;
+              vb.z = vb.z - j_iib * j_acca;
+            }
+            apply_impulse(va, j_ima, j_iia, j_accx, j_accy, j_rax, j_ray);
+            apply_impulse(vb, j_imb, j_iib, -j_accx, -j_accy, j_rbx, j_rby);
+            S::vel4(E, jsa) = va;
+            S::vel4(E, jsb) = vb;
+          }
+          wave_sync();
+        }
+      }
+
+      K2D_T(kT_WarmStart);
+      // ---- solver sweeps (Alg. 1): joints, then collisions ----
+      const int n_b = BATCHED ? prm.n_batches : 1;
+      int oa_bj = 0, ob_bj = 0;   // batched schedule: batch and place of the two slots of the held pairs
+      if constexpr (BATCHED) {
+        if (oa.have) oa_bj = S::batch_places(oa.rc.ab, n_b);
+        if (ob.have) ob_bj = S::batch_places(ob.rc.ab, n_b);
+      }
+      const bool j_ang = j_fixed && j_angm > 0.f;                     // A.4.2: the joint has an angular row
+      const bool j_lim = !j_fixed && j_exc != 0.f && j_angm > 0.f;    // A.4.3: it is beyond a limit
+      for (int it = 0; it < prm.n_iters; ++it) {
+        for (int lv = 0; lv < wave_levels; ++lv) {
+          if (k < J && j_live && j_level == lv) {
+            float4 va = S::vel4(E, ja), vb = S::vel4(E, jb);
+            if (any_angular) {
+              // (both kinds of angular row are worked out and picked by lane: a wavefront that has one pays for no branch)
+              const float w = va.z - vb.z;
+              const bool restoring = (j_exc > 0.f) ? (w < 0.f) : (w > 0.f);   // A.4.3: not while already coming back
+              const float d = -(w + j_angb) * j_angm;
+              const bool on = j_ang || (j_lim && !restoring);
+              va.z = on ? va.z + j_iia * d : va.z;
+              vb.z = on ? vb.z - j_iib * d : vb.z;
+              j_acca = j_ang ? j_acca + d : j_acca;                           // (limits are never accumulated)
+            }
+            float cx, cy;   // A.4.1: point constraint, 2x2 solve
+            S::rel_vel(va, j_rax, j_ray, vb, j_rbx, j_rby, cx, cy);
+            float rx = -(cx + j_bx), ry = -(cy + j_by);
+            float jx = (j_k22 * rx - j_k12 * ry) * j_idet, jy = (j_k11 * ry - j_k12 * rx) * j_idet;
+            apply_impulse(va, j_ima, j_iia, jx, jy, j_rax, j_ray);
+            apply_impulse(vb, j_imb, j_iib, -jx, -jy, j_rbx, j_rby);
+            j_accx = j_accx + jx; j_accy = j_accy + jy;
+            S::vel4(E, jsa) = va;
+            S::vel4(E, jsb) = vb;
+          }
+          wave_sync();
+        }
+        K2D_T(kT_SweepJoints);
+        if constexpr (BATCHED) {
+          // A.8: the points of batch b are solved from the velocities the batch starts with, their impulses
+          // staged by their place in the batch; then lane s applies to shape s, in place order, the
+          // impulses of the points that touch it (so every body sees them in point order).
+          for (int b = 0; b < n_b; ++b) {
+            unsigned pm = 0u;   // places of the batch taken by this lane's points
+            auto stage_point = [&](int j, int ab, float jx, float jy, float fx, float fy, float rax, float ray,
+                                   float rbx, float rby) {
+              float4* p = reinterpret_cast<float4*>(E + K::X_STAGE + j * K::kManW);
+              p[0] = make_float4(jx, jy, fx, fy);
+              p[1] = make_float4(rax, ray, rbx, rby);
+              reinterpret_cast<int*>(p)[8] = ab & 0xffff;
+              pm |= 1u << j;
+            };
+            auto own_points = [&](Own& o, int bj) {
+              const bool hit0 = o.have && (bj & 0xff) == b;
+              const bool hit1 = (o.rc.ab & kTwo) && ((bj >> 16) & 0xff) == b;
+              if (hit0 || hit1) {
+                float jx, jy, fx, fy, rax, ray, rbx, rby;
+                S::point_impulses(o.rc, hit1, o.ima, o.iia, o.imb, o.iib, S::vel4(E, o.pa), S::vel4(E, o.pb), jx, jy, fx,
+                                  fy, rax, ray, rbx, rby);
+                stage_point((bj >> (hit1 ? 24 : 8)) & 0xff, o.rc.ab, jx, jy, fx, fy, rax, ray, rbx, rby);
+              }
+            };
+            own_points(oa, oa_bj);
+            if constexpr (K::TWO) {
+              if (any_b) own_points(ob, ob_bj);
+            }
+            if constexpr (K::LISTED > 0) {
+              if (any_listed) {
+                auto listed_points = [&](auto rp) {
+                  PairRec rc;
+                  rec_load(rp, rc);
+                  const int bj = S::batch_places(rc.ab, n_b);
+                  const bool hit0 = (bj & 0xff) == b;
+                  const bool hit1 = (rc.ab & kTwo) && ((bj >> 16) & 0xff) == b;
+                  if (hit0 || hit1) {
+                    const int a = rc.ab & 0xff, bb = (rc.ab >> 8) & 0xff;
+                    const float4 qa = S::prop4(E, a), qb = S::prop4(E, bb);
+                    float jx, jy, fx, fy, rax, ray, rbx, rby;
+                    S::point_impulses(rc, hit1, qa.x, qa.y, qb.x, qb.y, S::vel4(E, a), S::vel4(E, bb), jx, jy, fx, fy, rax,
+                                      ray, rbx, rby);
+                    stage_point((bj >> (hit1 ? 24 : 8)) & 0xff, rc.ab, jx, jy, fx, fy, rax, ray, rbx, rby);
+                    if (hit1) { rp[15 + 8] = rc.lam_n[1]; rp[15 + 9] = rc.lam_t[1]; }
+                    else { rp[5 + 8] = rc.lam_n[0]; rp[5 + 9] = rc.lam_t[0]; }
+                  }
+                };
+                for (int q = k; __any(q < n_listed); q += G)
+                  if (q < n_listed) {
+                    if (q < K::POOL) listed_points(to_lds(pool + q * kRecW));
+                    else listed_points(spill + (q - K::POOL) * kRecW);
+                  }
+              }
+            }
+            pm = group_or<G>(pm);
+            wave_sync();
+            if (__any(pm != 0u)) {
+#pragma unroll
+              for (int s = 0; s < NS; ++s) {   // lane k applies to shapes k, k + G, ...
+                const int i = k + s * G;
+                if (i < N && !((static_mask >> i) & 1u) && pm != 0u) {
+                  float4 v = S::vel4(E, i);
+                  const float2 q = *reinterpret_cast<const float2*>(E + K::X_PROP + 4 * i);
+                  for (unsigned m = pm; m != 0u; m &= m - 1u) {
+                    const float4* p = reinterpret_cast<const float4*>(E + K::X_STAGE + (__ffs(m) - 1) * K::kManW);
+                    const int ab = reinterpret_cast<const int*>(p)[8];
+                    const float4 j = p[0], r = p[1];
+                    if ((ab & 0xff) == i) {
+                      apply_impulse(v, q.x, q.y, j.x, j.y, r.x, r.y);
+                      apply_impulse(v, q.x, q.y, j.z, j.w, r.x, r.y);
+                    } else if ((ab >> 8) == i) {
+                      apply_impulse(v, q.x, q.y, -j.x, -j.y, r.z, r.w);
+                      apply_impulse(v, q.x, q.y, -j.z, -j.w, r.z, r.w);
+                    }
+                  }
+                  S::vel4(E, i) = v;
+                }
+              }
+              wave_sync();
+            }
+          }
+        } else
+          for_each_level([&](Own& o) { S::template visit_own<false>(E, o); },
+                         [&](int q) {
+                           // (the two branches keep LDS and HBM accesses apart: a merged pointer would turn
+                           // every access into a slow flat one)
+                           PairRec rc;
+                           if (q < K::POOL) {
+                             LdsF rp = to_lds(pool + q * kRecW);
+                             rec_load(rp, rc);
+                             S::template visit_pair<false>(E, rc, static_mask);
+#pragma unroll
+                             for (int z = 0; z < 2; ++z) { rp[5 + 10 * z + 8] = rc.lam_n[z]; rp[5 + 10 * z + 9] = rc.lam_t[z]; }
+                           } else {
+                             float* rp = spill + (q - K::POOL) * kRecW;
+                             rec_load(rp, rc);
+                             S::template visit_pair<false>(E, rc, static_mask);
+#pragma unroll
+                             for (int z = 0; z < 2; ++z) { rp[5 + 10 * z + 8] = rc.lam_n[z]; rp[5 + 10 * z + 9] = rc.lam_t[z]; }
+                           }
+                         });
+        K2D_T(kT_SweepPairs);
+      }
+
+      // ---- Euler step of position and rotation (Alg. 1) ----
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const int i = k + s * G;
+        if ((sh_act >> s) & 1u) {
+          const float4 v = S::vel4(E, i);
+          const float2 p = S::xy(E, i);
+          const float th = add_ordered(v.w, h * v.z);
+          float sn, cs;
+          k2d_sincos(th, sn, cs);
+          S::pos4(E, i) = make_float4(add_ordered(p.x, h * v.x), add_ordered(p.y, h * v.y), cs, sn);
+          E[K::X_VEL + 4 * i + 3] = th;
+        }
+      }
+      wave_sync();
+
+      K2D_T(kT_Euler);
+      // ---- positional corrections (A.3.7, A.4.1) ----
+      // a pair (a, b), its results going to entries da and db
+      auto correct = [&](int a, int b, int da, int db, float ima, float imb, float nx, float ny, float corr) {
+        const float2 p = S::xy(E, a);
+        *reinterpret_cast<float2*>(E + K::X_POS + 4 * da) = make_float2(p.x - (ima * corr) * nx, p.y - (ima * corr) * ny);
+        const float2 q = S::xy(E, b);
+        *reinterpret_cast<float2*>(E + K::X_POS + 4 * db) = make_float2(add_ordered((imb * corr) * nx, q.x), add_ordered((imb * corr) * ny, q.y));
+      };
+      auto correct_listed = [&](float nx, float ny, float corr, int ab, float4 lam) {
+        const int a = ab & 0xff, b = (ab >> 8) & 0xff;
+        // these pairs' accumulated impulses wait for the next substep (A.7) in the HBM record
+        if (env_ok) *reinterpret_cast<float4*>(Rg + L.lambda + 4 * S::pair_index(a, b)) = lam;
+        correct(a, b, ((static_mask >> a) & 1u) ? N : a, ((static_mask >> b) & 1u) ? N : b, S::prop4(E, a).x,
+                S::prop4(E, b).x, nx, ny, corr);
+      };
+      for_each_level([&](Own& o) { correct(o.pa, o.pb, o.sa, o.sb, o.ima, o.imb, o.rc.nx, o.rc.ny, o.rc.corr); },
+                     [&](int q) {
+                       if (q < K::POOL) {
+                         LdsCF rp = to_lds(pool + q * kRecW);
+                         const int ab = f2i(rp[4]);
+                         correct_listed(rp[0], rp[1], rp[3], ab, lam_of(ab, rp[13], rp[14], rp[23], rp[24]));
+                       } else {
+                         const float* rp = spill + (q - K::POOL) * kRecW;
+                         const int ab = f2i(rp[4]);
+                         correct_listed(rp[0], rp[1], rp[3], ab, lam_of(ab, rp[13], rp[14], rp[23], rp[24]));
+                       }
+                     });
+      // the accumulated impulses wait for the next substep (A.7): in LDS, by the pair's number
+      held_a = oa.have ? oa.rc.ab & 0xffff : -1;
+      if (oa.have) lam_store[k] = lam_of(oa.rc.ab, oa.rc.lam_n[0], oa.rc.lam_t[0], oa.rc.lam_n[1], oa.rc.lam_t[1]);
+      if constexpr (K::TWO) {
+        held_b = ob.have ? ob.rc.ab & 0xffff : -1;
+        if (any_b) {
+          if (ob.have) lam_store[G + k] = lam_of(ob.rc.ab, ob.rc.lam_n[0], ob.rc.lam_t[0], ob.rc.lam_n[1], ob.rc.lam_t[1]);
+        }
+      }
+      if (any_listed) hbm_sync();
+      K2D_T(kT_CorrectPairs);
+      for (int lv = 0; lv < wave_levels; ++lv) {
+        if (k < J && j_live && j_level == lv) {
+          const float4 fa = S::pos4(E, ja), fb = S::pos4(E, jb);
+          const float xax = add_ordered(fmaf(fa.z, j_aax, -(fa.w * j_aay)), fa.x);
+          const float xay = add_ordered(fmaf(fa.w, j_aax, fa.z * j_aay), fa.y);
+          const float xbx = add_ordered(fmaf(fb.z, j_abx, -(fb.w * j_aby)), fb.x);
+          const float xby = add_ordered(fmaf(fb.w, j_abx, fb.z * j_aby), fb.y);
+          float cx = j_cf * (xax - xbx), cy = j_cf * (xay - xby);
+          *reinterpret_cast<float2*>(E + K::X_POS + 4 * jsa) = make_float2(fa.x - j_ima * cx, fa.y - j_ima * cy);
+          *reinterpret_cast<float2*>(E + K::X_POS + 4 * jsb) = make_float2(add_ordered(j_imb * cx, fb.x), add_ordered(j_imb * cy, fb.y));
+        }
+        wave_sync();
+      }
+      K2D_T(kT_CorrectJoints);
+    }
+    if (RESET) {   // new episodes (wave-uniform branch: the wavefront leaves the step loop together)
+      if (new_level >= n_level_records) new_level = -1;
+      if (__any(new_level >= 0)) {
+        if (new_level >= 0) {
+          src = levels + (size_t)new_level * L.scene_words;
+          for (int w = k; w < L.scene_words; w += G) {
+            float v = src[w];
+            if (w >= L.acc_x && w < L.thr_flags) v = 0.f;   // accumulated joint impulses start at zero
+            Rg[w] = v;
+          }
+          fresh = true;
+        }
+        ++step;
+        break;
+      }
+    }
+  }
+  } while (RESET && step < n_steps);
+
+#ifdef K2D_PHASE_TIMERS
+  K2D_T(kT_Restart);
+  if (phase_clocks && lane == 0) {
+    unsigned long long* out = phase_clocks + (size_t)blockIdx.x * kPhaseSlots;
+    for (int i = 0; i < kT_Count; ++i) out[i] = (unsigned long long)t_acc[i];
+    out[kT_Count] = t_pair_levels;
+    out[kT_Count + 1] = t_joint_levels;
+  }
+#endif
+  // ---- write back: dynamic shape state, accumulated impulses, pair states ----
+  // (an environment that starts a new episode after the last step has its record written already)
+  if (env_ok) {
+    if (!fresh) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const int i = k + s * G;
+        if (i < N) {
+          const float4 v = S::vel4(E, i);
+          const float2 p = S::xy(E, i);
+          Rg[L.pos_x + i] = p.x; Rg[L.pos_y + i] = p.y; Rg[L.theta + i] = v.w;
+          Rg[L.vel_x + i] = v.x; Rg[L.vel_y + i] = v.y; Rg[L.omega + i] = v.z;
+        }
+      }
+      if (k < J) {
+        Rg[L.acc_x + k] = j_accx; Rg[L.acc_y + k] = j_accy; Rg[L.acc_ang + k] = j_acca;
+      }
+      if (held_a >= 0) *reinterpret_cast<float4*>(Rg + L.lambda + 4 * S::pair_index(held_a & 255, held_a >> 8)) = lam_store[k];
+      if constexpr (K::TWO) {
+        if (held_b >= 0) *reinterpret_cast<float4*>(Rg + L.lambda + 4 * S::pair_index(held_b & 255, held_b >> 8)) = lam_store[G + k];
+      }
+    }
+    constexpr int PSW = (K::NP + 3) / 4;
+    unsigned* out = reinterpret_cast<unsigned*>(E + K::X_PSB);
+    for (int w = k; w < PSW; w += G) out[w] = 0u;
+    wave_sync();
+    if (!fresh) {
+#pragma unroll
+      for (int t = 0; t < ET; ++t)
+        if ((elig >> t) & 1u) {
+          const unsigned ab = my_ab[t >> 2] >> (8 * (t & 3));
+          reinterpret_cast<unsigned char*>(out)[S::pair_index(ab & 15, (ab >> 4) & 15)] = pst[k * TSP + t] & 3;
+        }
+    }
+    wave_sync();
+    for (int w = k; w < PSW; w += G) reinterpret_cast<unsigned*>(Rg + L.pair_state)[w] = out[w];
+  }
+}
+
+template <class K, bool RESET, bool BATCHED>
+int launch_step(const StepLaunch& s) {
+  {   // the kernel's LDS image is larger than the default limit: raise it once per device
+    static bool attr_done[kMaxDevices] = {};
+    static std::mutex mutex;
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return K2D_E_HIP;
+    std::lock_guard<std::mutex> lock(mutex);
+    if (!attr_done[dev]) {
+      if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k2d_step_kernel<K, RESET, BATCHED>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, K::LDS_BYTES) != hipSuccess)
+        return K2D_E_HIP;
+      attr_done[dev] = true;
+    }
+  }
+  const int grid = (s.n_envs + K::EPW - 1) / K::EPW;
+  bool ok = true;
+  if (s.order) {   // (a launch of a few steps is not worth the ordering pass)
+    // action rows that share a 128-byte line (rows of K::A floats; at least one environment per line)
+    const int envs_per_line = K::A > 0 && 32 / K::A > 0 ? 32 / K::A : 1;
+    ok = order_environments(s.state, s.order, s.n_envs, grid, K::EPW, envs_per_line, K::REC_WORDS, K::L, K::J, s.stream);
+  }
+#ifdef K2D_PHASE_TIMERS
+  K2D_LAUNCH(ok, (k2d_step_kernel<K, RESET, BATCHED>), dim3(grid), dim3(64), K::LDS_BYTES, s.stream, s.state, s.actions,
+             s.n_envs, s.n_steps, s.prm, s.levels, s.n_levels, s.reset_level, s.order,
+             grid <= s.phase_waves ? s.phase_clocks : nullptr);
+#else
+  K2D_LAUNCH(ok, (k2d_step_kernel<K, RESET, BATCHED>), dim3(grid), dim3(64), K::LDS_BYTES, s.stream, s.state, s.actions,
+             s.n_envs, s.n_steps, s.prm, s.levels, s.n_levels, s.reset_level, s.order);
+#endif
+  return ok ? K2D_OK : K2D_E_HIP;
+}
+
+template <class K>
+int launch_step_as(const StepLaunch& s) {
+  if (s.reset_level) return s.batched ? launch_step<K, true, true>(s) : launch_step<K, true, false>(s);
+  return s.batched ? launch_step<K, false, true>(s) : launch_step<K, false, false>(s);
+}
+
+// Lane mappings of a capacity class: 16 lanes per environment (four environments per wavefront) and 8 lanes
+// per environment (eight per wavefront: half the instructions per environment, but an LDS image twice as
+// large per wavefront).
+template <int P, int C, int J, int T>
+int launch_step_class(const StepLaunch& s) {
+  using K16 = Cfg<P, C, J, T, 16>;
+  using K8 = Cfg<P, C, J, T, 8>;
+  // the LDS images of a CU's resident wavefronts must fit its 160 KiB: eight (16 lanes) or four (8 lanes) per CU
+  static_assert(K16::LDS_BYTES * 8 <= 160 * 1024 && K8::LDS_BYTES * 4 <= 160 * 1024, "LDS image too large");
+  return s.lanes == 8 ? launch_step_as<K8>(s) : launch_step_as<K16>(s);
+}
+
+}  // namespace k2d_impl
