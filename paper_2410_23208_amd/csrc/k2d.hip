@@ -6,9 +6,9 @@
 // constraints (A.3.5-A.3.7), the Euler step, and the positional corrections (A.3.7, A.4.1).
 //
 // How it is mapped onto CDNA4:
-//   * One environment is owned by a group of G consecutive lanes: G = 16, so that a 64-wide wavefront
-//     steps four environments, or G = 8 and eight environments (chosen per launch: faster for the small
-//     capacity class in large batches).  A workgroup is exactly one wavefront, which makes every
+//   * One environment is owned by a group of G consecutive lanes, G = 64, 32, 16 or 8, so that a 64-wide
+//     wavefront steps one, two, four or eight environments (chosen per launch by the number of environments:
+//     the fewer there are, the more lanes each gets).  A workgroup is exactly one wavefront, which makes every
 //     synchronisation point a wavefront-scope fence and lets the hardware place wavefronts on CUs freely.
 //   * The whole scene of an environment lives in LDS for the entire launch (all steps, substeps and
 //     solver sweeps).  HBM is touched when the launch begins (one coalesced read of the record), once per
@@ -513,6 +513,8 @@ bool g_phase_keep_order = false;                // launches take the environment
 #endif
 // environments beyond which the 8-lane mapping is chosen: what the 16-lane mapping keeps resident at once
 constexpr int kResidentEnvs16 = 256 * 8 * 4;
+// wavefronts of the step kernel that are resident at once: two on every SIMD (registers and LDS allow no more)
+constexpr int kWaveSlots = 256 * 8;
 
 }  // namespace
 
@@ -564,6 +566,18 @@ static Params device_params(const k2d_params& p) {
   return prm;
 }
 
+// Lanes per environment where the batch does not say: as many as leave no environment waiting for a wavefront slot
+// (measured on MI355X, 64 steps, ms with 64 / 32 / 16 / 8 lanes: Large 2048 environments 2.72 / 2.99 / 3.29 / 3.93,
+// 4096: 5.07 / 2.88 / 3.29 / 4.15, 8192: 8.52 / 4.75 / 3.16 / 4.14; Medium 1024: 1.26 / 1.62 / 1.76 / 2.07; Small
+// 256: 0.46 / 0.48 / 0.61 / 0.66, 8192: 1.73 / 1.05 / 0.69 / 0.74).  Beyond what 16 lanes keep resident Small
+// environments take 8 lanes (16384: 1.27 with 16, 0.78 with 8); Medium and Large ones stay at 16, since their
+// 8-lane images leave room for one wavefront per SIMD, whose dependent instructions have nothing to overlap with.
+static int lanes_for(int cls, int n_envs, int batch_size) {
+  if (n_envs <= kWaveSlots) return 64;
+  if (n_envs <= 2 * kWaveSlots) return 32;
+  return (cls == 0 && n_envs > kResidentEnvs16 && batch_size <= 16) ? 8 : 16;
+}
+
 static int step_launch(k2d_batch* b, const float* actions_dev, int n_envs, int n_steps, const float* lv, int n_levels,
                        const int32_t* reset_level_dev, int32_t* order_buf, hipStream_t st) {
   StepLaunch s{};
@@ -584,13 +598,7 @@ static int step_launch(k2d_batch* b, const float* actions_dev, int n_envs, int n
   if (g_phase_keep_order) s.order = nullptr;
   s.phase_clocks = g_phase_clocks; s.phase_waves = g_phase_waves;
 #endif
-  // lane mapping: as set on the batch; else 16 lanes per environment, except for Small environments in
-  // batches larger than that mapping keeps resident at once.  (Measured on MI355X: with 8 lanes the Small
-  // class steps 16384 and more environments 1.5 to 1.7 times faster; the Medium and Large classes are
-  // slower with 8 lanes at every batch size -- their LDS images allow one wavefront of eight environments per
-  // SIMD, whose dependent instructions then have no second wavefront to overlap with.)
-  s.lanes = b->lanes;
-  if (s.lanes == 0) s.lanes = (b->cls == 0 && n_envs > kResidentEnvs16 && b->params.batch_size <= 16) ? 8 : 16;
+  s.lanes = b->lanes ? b->lanes : lanes_for(b->cls, n_envs, b->params.batch_size);
   if (s.lanes == 8 && b->params.batch_size > 16) return K2D_E_ARG;
   return b->cls == 0 ? launch_step_small(s) : b->cls == 1 ? launch_step_medium(s) : launch_step_large(s);
 }

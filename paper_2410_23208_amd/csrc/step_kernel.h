@@ -29,7 +29,7 @@ struct Cfg {
   static constexpr int M = N + (N & 1);        // tournament size (an odd N gets a phantom that sits out)
   static constexpr int R = M - 1;              // rounds
   static constexpr int PPR = M / 2;            // pairs per round
-  static_assert((G == 8 || G == 16) && N <= 16 && J <= G && T <= G && R <= 15, "lane mapping");
+  static_assert((G == 8 || G == 16 || G == 32 || G == 64) && N <= 16 && J <= G && T <= G && R <= 15, "lane mapping");
   // Work items of a lane: shapes k, k + G, ...; one vertex of polygons k / 4, k / 4 + G / 4, ... (four
   // neighbouring lanes share a polygon); entries k, k + G, ... of the list of eligible pairs.
   static constexpr int NS = (N + G - 1) / G, QT = (4 * P + G - 1) / G, ET = (NP + G - 1) / G;
@@ -40,10 +40,11 @@ struct Cfg {
   // staging slot, the lane that keeps the pair derives the substep constants from it.  Pairs beyond them
   // live as full records in a small LDS pool (POOL records, as many as the LDS budget of the class has
   // room for, eight at most) or, past that, in the HBM record.
-  static constexpr int NREG = 2 * G < NP ? 2 * G : NP;
-  static constexpr bool TWO = NP > G;          // a lane may have to hold a second pair
+  static constexpr int NREG_MOST = 62;         // (what a state byte can name, see kInRecord)
+  static constexpr int NREG_WANT = 2 * G < NREG_MOST ? 2 * G : NREG_MOST;
+  static constexpr int NREG = NREG_WANT < NP ? NREG_WANT : NP;
+  static constexpr bool TWO = NREG > G;        // a lane may have to hold a second pair
   static constexpr int LISTED = NP - NREG;     // pairs that may have to live outside the registers
-  static constexpr int LAMN = NREG < 62 ? NREG : 62;   // pairs whose accumulated impulses wait in LDS for the next substep
   static constexpr k2d_layout L = make_layout(P, C, J, T);
   static constexpr int REC_WORDS = record_words(L), G_SPILL = spill_offset(L), SPILL = spill_records(NP);
   // LDS image of one environment.  What a visit of a constraint reads of a body is one 16-byte word:
@@ -70,15 +71,16 @@ struct Cfg {
   static constexpr int X_PST = align_up(X_LIST + (NP + 1) / 2, 4);   // bytes [G][TSP]: state of every eligible pair (see pair_byte)
   static constexpr int X_CNT = X_PST + G * TSP / 4;        // candidates counted so far, eight bits per shape-type mix
   static constexpr int X_RAD = X_CNT + 1;                  // radii of the circles
-  static constexpr int X_LAM = align_up(X_RAD + C, 4);     // float4 [LAMN]: accumulated impulses of the register-held pairs
+  static constexpr int X_LAM = align_up(X_RAD + C, 4);     // float4 [NREG]: accumulated impulses of the register-held pairs
   static constexpr int kManW = 12;                         // words of a staged manifold (nine used; 16-byte aligned, spread over banks)
-  static constexpr int STAGE_N = NREG < 2 * G ? 2 * G : NREG;   // (a batch of A.8 stages up to 2 G impulses there)
-  static constexpr int X_STAGE = X_LAM + 4 * LAMN;
+  static constexpr int BATCH_MOST = G == 8 ? 16 : K2D_MAX_BATCH_SIZE;           // impulses of a batch of A.8 are staged there too
+  static constexpr int STAGE_N = NREG < BATCH_MOST ? BATCH_MOST : NREG;
+  static constexpr int X_STAGE = X_LAM + 4 * NREG;
   static constexpr int X_POOL = X_STAGE + STAGE_N * kManW;
-  // LDS budget of one environment: a CU's 160 KiB shared by the lanes of eight wavefronts' worth of
-  // 16-lane environments (or four wavefronts' worth of 8-lane ones): 1280 words.  The stride is an odd
-  // multiple of G words, so that the same word of different environments falls into different banks.
-  static constexpr int MAX_STRIDE = (1280 / G - ((1280 / G) % 2 == 0 ? 1 : 0)) * G;
+  // LDS budget of one environment: a CU's 160 KiB shared by eight wavefronts (four of those with eight
+  // environments).  The stride is an odd multiple of G words, so that the same word of different environments
+  // falls into different banks.
+  static constexpr int MAX_STRIDE = (G == 8 ? 159 : 79) * G;
   static constexpr int POOL_WANT = LISTED < 8 ? LISTED : 8;
   static constexpr int POOL_FIT = MAX_STRIDE > X_POOL ? (MAX_STRIDE - X_POOL) / kRecW : 0;
   static constexpr int POOL = POOL_WANT < POOL_FIT ? POOL_WANT : POOL_FIT;
@@ -96,15 +98,22 @@ enum {   // DPP controls: exchanges within four neighbouring lanes
   kQuadXor1 = 0xB1, kQuadXor2 = 0x4E
 };
 
+// Bits of a ballot that belong to one environment's group of lanes.
+template <int G>
+using GroupBits = std::conditional_t<G == 64, unsigned long long, unsigned>;
+__device__ __forceinline__ int popc(unsigned v) { return __popc(v); }
+__device__ __forceinline__ int popc(unsigned long long v) { return __popcll(v); }
 // OR over the lanes of an environment's group.  A group of 16 is one DPP row (rotations reach every lane);
 // a group of 8 is half a row: exchanges within a quad and the mirror of the half row.
 template <int G>
 __device__ __forceinline__ unsigned group_or(unsigned v) {
-  if constexpr (G == 16) {
+  if constexpr (G >= 16) {
     v |= (unsigned)K2D_DPP(v, 0x121);
     v |= (unsigned)K2D_DPP(v, 0x122);
     v |= (unsigned)K2D_DPP(v, 0x124);
     v |= (unsigned)K2D_DPP(v, 0x128);
+    if constexpr (G >= 32) v |= (unsigned)__shfl_xor((int)v, 16, 64);
+    if constexpr (G == 64) v |= (unsigned)__shfl_xor((int)v, 32, 64);
   } else {
     v |= (unsigned)K2D_DPP(v, kQuadXor1);
     v |= (unsigned)K2D_DPP(v, kQuadXor2);
@@ -112,7 +121,7 @@ __device__ __forceinline__ unsigned group_or(unsigned v) {
   }
   return v;
 }
-// Lane q of the own group, for all lanes (q a compile-time constant).
+// Lane q of the own group, for all lanes (groups of up to 16 lanes; q a compile-time constant).
 template <int G, int q>
 __device__ __forceinline__ unsigned group_bcast(unsigned v, int g) {
   if constexpr (G == 16) return (unsigned)K2D_DPP(v, 0x150 + q);
@@ -318,28 +327,30 @@ struct Step {
     m.valid[0] = true;
   }
 
-  // Largest over X's faces of the smallest signed distance of Y's vertices to the face (A.3.4).
-  static __device__ __forceinline__ void face_query(const float2 (&xw)[4], const float2 (&xn)[4], bool tri_x,
+  // Largest over X's faces f0 .. f0 + NF - 1 of the smallest signed distance of Y's vertices to the face (A.3.4).
+  template <int NF>
+  static __device__ __forceinline__ void face_query(const float2 (&xw)[NF], const float2 (&xn)[NF], int f0, bool tri_x,
                                                     const float2 (&yw)[4], float& best, int& idx) {
     best = -INFINITY;
     idx = 0;
     // (vertex slot 3 of a triangle repeats vertex 0, which leaves the minimum over Y's vertices as it is;
     // the fourth "face" of a triangle X is computed and thrown away: no branch in the loops)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < NF; ++i) {
       float smin = INFINITY;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         float s = dot2(xn[i].x, xn[i].y, yw[k].x - xw[i].x, yw[k].y - xw[i].y);
         smin = (s < smin) ? s : smin;
       }
-      if ((i < 3 || !tri_x) && smin > best) { best = smin; idx = i; }
+      if ((f0 + i < 3 || !tri_x) && smin > best) { best = smin; idx = f0 + i; }
     }
   }
 
   // ---- A.3.4: polygon a, polygon b ----
-  // W = 1: one lane per pair.  W = 2: two neighbouring lanes, one asks a's faces, the other b's; the first is
-  // left with the result.
+  // W = 1: one lane per pair.  W = 2: two neighbouring lanes, one asks a's faces, the other b's; W = 4: two faces
+  // each.  The first lane is left with the result.  (Faces are compared with "strictly better", the earlier
+  // lane holding the earlier faces: the lowest face index wins ties.)
   template <int W>
   static __device__ __forceinline__ void manifold_pp(float* E, int h, int pa, bool tri_a, int pb, bool tri_b, float tie_eps,
                                                      Manifold& m) {
@@ -349,14 +360,27 @@ struct Step {
       float2 aw[4], bw[4], xn[4];
       load4(E, pa, 0, aw); load4(E, pb, 0, bw);
       load4(E, pa, 8, xn);
-      face_query(aw, xn, tri_a, bw, sa, ia);
+      face_query<4>(aw, xn, 0, tri_a, bw, sa, ia);
       load4(E, pb, 8, xn);
-      face_query(bw, xn, tri_b, aw, sb, ib);
+      face_query<4>(bw, xn, 0, tri_b, aw, sb, ib);
     } else {
-      const int px = h ? pb : pa, py = h ? pa : pb;
-      float2 xw[4], yw[4], xn[4];
-      load4(E, px, 0, xw); load4(E, py, 0, yw); load4(E, px, 8, xn);
-      face_query(xw, xn, h ? tri_b : tri_a, yw, sa, ia);
+      const int px = (h & 1) ? pb : pa, py = (h & 1) ? pa : pb;
+      const bool tri_x = (h & 1) ? tri_b : tri_a;
+      float2 yw[4];
+      load4(E, py, 0, yw);
+      if constexpr (W == 2) {
+        float2 xw[4], xn[4];
+        load4(E, px, 0, xw); load4(E, px, 8, xn);
+        face_query<4>(xw, xn, 0, tri_x, yw, sa, ia);
+      } else {
+        const int f0 = h & 2;
+        const float4 w = *reinterpret_cast<const float4*>(&wv(E, f0, px)), n = *reinterpret_cast<const float4*>(&wn(E, f0, px));
+        const float2 xw[2] = {make_float2(w.x, w.y), make_float2(w.z, w.w)}, xn[2] = {make_float2(n.x, n.y), make_float2(n.z, n.w)};
+        face_query<2>(xw, xn, f0, tri_x, yw, sa, ia);
+        const float s2 = K2D_DPPF(sa, kQuadXor2);
+        const int i2 = K2D_DPP(ia, kQuadXor2);
+        if (s2 > sa) { sa = s2; ia = i2; }   // (lanes 0 and 1 of the four: the others hold the later faces)
+      }
       sb = K2D_DPPF(sa, kQuadXor1);
       ib = K2D_DPP(ia, kQuadXor1);
     }
@@ -610,8 +634,13 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
   const int lane = threadIdx.x;
   const int g = lane / G, k = lane % G;
   // the bits of a ballot that belong to this lane's environment, and how many of them lie below this lane
-  auto group_bits = [&](unsigned long long bal) { return (unsigned)(bal >> (g * G)) & ((1u << G) - 1u); };
-  const unsigned below = (1u << k) - 1u;
+  using Bits = GroupBits<G>;
+  auto group_bits = [&](unsigned long long bal) {
+    if constexpr (G == 64) return (Bits)bal;
+    else if constexpr (G == 32) return (Bits)(bal >> (g * G));
+    else return (Bits)(bal >> (g * G)) & ((1u << G) - 1u);
+  };
+  const Bits below = ((Bits)1 << k) - 1;
   // which environment this lane works for: a launch may come with an ordering of the environments
   // (slot -> environment, -1 = none) that puts similar ones together; without one, slot s is environment s
   const int slot = blockIdx.x * K::EPW + g;
@@ -689,9 +718,9 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
         if (i < P) tri = f2i(word(L.n_verts + i)) == 3;
         else { c_radius[s] = word(L.radius + (i - P)); E[K::X_RAD + (i - P)] = c_radius[s]; }
       }
-      act_bits |= group_bits(__ballot(act)) << (s * G);
-      static_bits |= group_bits(__ballot(fixed)) << (s * G);
-      tri_bits |= group_bits(__ballot(tri)) << (s * G);
+      act_bits |= (unsigned)group_bits(__ballot(act)) << (s * G < 32 ? s * G : 0);
+      static_bits |= (unsigned)group_bits(__ballot(fixed)) << (s * G < 32 ? s * G : 0);
+      tri_bits |= (unsigned)group_bits(__ballot(tri)) << (s * G < 32 ? s * G : 0);
     }
     static_mask = static_bits;
     tri_mask = tri_bits;
@@ -789,9 +818,9 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
           ok = ((act_bits >> a) & 1u) && ((act_bits >> b) & 1u) && !((f2i(E[K::X_JOINED + a]) >> b) & 1) &&
                (S::prop4(E, a).x + S::prop4(E, b).x) > 0.f;
         }
-        const unsigned bits = group_bits(__ballot(ok));
-        if (ok) list[n_elig + __popc(bits & below)] = (unsigned char)(a | (b << 4));
-        n_elig += __popc(bits);
+        const Bits bits = group_bits(__ballot(ok));
+        if (ok) list[n_elig + popc(bits & below)] = (unsigned char)(a | (b << 4));
+        n_elig += popc(bits);
       }
       wave_sync();
       elig = 0u; pp_mask = 0u; pc_mask = 0u;
@@ -1014,14 +1043,14 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
         const bool act0 = lead && m.valid[0] && m.pen[0] > 0.f, act1 = lead && m.valid[1] && m.pen[1] > 0.f;
         const bool active = act0 || act1;
         set_changed |= lead && (((prev & 3) != 0) != active);
-        const unsigned bits = group_bits(__ballot(active));
-        const int idx = n_act + __popc(bits & below);
-        n_act += __popc(bits);
+        const Bits bits = group_bits(__ballot(active));
+        const int idx = n_act + popc(bits & below);
+        n_act += popc(bits);
         int now = 0;
         if (active) {
           const int ab = e & 255;
           const int w = ab | ((int)act0 << 8) | ((int)act1 << 9) | (prev << 10);
-          now = (int)act0 | ((int)act1 << 1) | ((idx < K::LAMN ? idx : kInRecord) << 2);
+          now = (int)act0 | ((int)act1 << 1) | ((idx < K::NREG ? idx : kInRecord) << 2);
           if (idx < K::NREG) {   // staged for the lane that keeps it
             float4* p = reinterpret_cast<float4*>(E + K::X_STAGE + idx * K::kManW);
             p[0] = make_float4(m.nx, m.ny, m.px[0], m.py[0]);
@@ -1076,12 +1105,16 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
           emit(have && k % W == 0, m, e, prev);
         }
       };
-      // polygon pairs: two lanes each while every environment's fit into one trip that way
-      if (!__any(n_pp > G / 2)) run_pp(std::integral_constant<int, 2>{});
-      else run_pp(std::integral_constant<int, 1>{});
-      // polygon-circle pairs: four lanes each while they fit into one trip, else two
-      if (!__any(n_pc > G / 4)) run_pc(std::integral_constant<int, 4>{});
-      else run_pc(std::integral_constant<int, 2>{});
+      // polygon pairs take as many lanes as let every environment's fit into one trip; polygon-circle pairs, whose four
+      // edges are a lane's work each, four lanes or two
+      using I1 = std::integral_constant<int, 1>;
+      using I2 = std::integral_constant<int, 2>;
+      using I4 = std::integral_constant<int, 4>;
+      if (G >= 32 && !__any(n_pp > G / 4)) run_pp(I4{});
+      else if (G == 64 || !__any(n_pp > G / 2)) run_pp(I2{});
+      else run_pp(I1{});
+      if (G >= 32 || !__any(n_pc > G / 4)) run_pc(I4{});
+      else run_pc(I2{});
       for (int base = 0; __any(base < n_cc); base += G) {
         Manifold m;
         const int c = base + k;
@@ -1144,30 +1177,44 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
       if (!levels_valid || !same_list || any_listed || __any(set_changed)) {
         auto movable = [&](int a, int b) { return ((1u << a) | (1u << b)) & ~static_mask; };
         int my_levels = 0;
-        if (!any_b) {
+        if (!any_b && !(G == 64 && __any(n_act > 32))) {
           // One pair per lane at most: every lane learns which of the environment's pairs come earlier and share
           // a movable shape with its own (a round's pairs are disjoint, so the order of the rounds decides), and a
           // pair can be placed once all of those are.
           const unsigned mine = oa.have ? (unsigned)S::round_of(oa.pa, oa.pb) << 16 | movable(oa.pa, oa.pb) : 0u;
           unsigned wait = 0u;
-          int most = 0;
+          if constexpr (G <= 16) {
+            int most = 0;
 #pragma unroll
-          for (int z = 1; z <= G; ++z)
-            if (__any(n_act >= z)) most = z;
-          auto meet = [&](auto z) {
-            constexpr int q = decltype(z)::value;
-            if (q < most) {
-              const unsigned o = group_bcast<G, q>(mine, g);
-              if ((o & mine & 0xffffu) != 0u && o < mine) wait |= 1u << q;
+            for (int z = 1; z <= G; ++z)
+              if (__any(n_act >= z)) most = z;
+            auto meet = [&](auto z) {
+              constexpr int q = decltype(z)::value;
+              if (q < most) {
+                const unsigned o = group_bcast<G, q>(mine, g);
+                if ((o & mine & 0xffffu) != 0u && o < mine) wait |= 1u << q;
+              }
+            };
+            meet(std::integral_constant<int, 0>{}); meet(std::integral_constant<int, 1>{}); meet(std::integral_constant<int, 2>{});
+            meet(std::integral_constant<int, 3>{}); meet(std::integral_constant<int, 4>{}); meet(std::integral_constant<int, 5>{});
+            meet(std::integral_constant<int, 6>{}); meet(std::integral_constant<int, 7>{});
+            if constexpr (G == 16) {
+              meet(std::integral_constant<int, 8>{}); meet(std::integral_constant<int, 9>{}); meet(std::integral_constant<int, 10>{});
+              meet(std::integral_constant<int, 11>{}); meet(std::integral_constant<int, 12>{}); meet(std::integral_constant<int, 13>{});
+              meet(std::integral_constant<int, 14>{}); meet(std::integral_constant<int, 15>{});
             }
-          };
-          meet(std::integral_constant<int, 0>{}); meet(std::integral_constant<int, 1>{}); meet(std::integral_constant<int, 2>{});
-          meet(std::integral_constant<int, 3>{}); meet(std::integral_constant<int, 4>{}); meet(std::integral_constant<int, 5>{});
-          meet(std::integral_constant<int, 6>{}); meet(std::integral_constant<int, 7>{});
-          if constexpr (G == 16) {
-            meet(std::integral_constant<int, 8>{}); meet(std::integral_constant<int, 9>{}); meet(std::integral_constant<int, 10>{});
-            meet(std::integral_constant<int, 11>{}); meet(std::integral_constant<int, 12>{}); meet(std::integral_constant<int, 13>{});
-            meet(std::integral_constant<int, 14>{}); meet(std::integral_constant<int, 15>{});
+          } else {   // (a larger group does not fit a DPP row: through LDS, four pairs at a time; the staging area is free)
+            unsigned* all = reinterpret_cast<unsigned*>(E + K::X_STAGE);
+            if (k < 32) all[k] = mine;
+            wave_sync();
+            for (int q = 0; __any(q < n_act); q += 4) {
+              const uint4 o = *reinterpret_cast<const uint4*>(all + q);
+              if ((o.x & mine & 0xffffu) != 0u && o.x < mine) wait |= 1u << q;
+              if ((o.y & mine & 0xffffu) != 0u && o.y < mine) wait |= 2u << q;
+              if ((o.z & mine & 0xffffu) != 0u && o.z < mine) wait |= 4u << q;
+              if ((o.w & mine & 0xffffu) != 0u && o.w < mine) wait |= 8u << q;
+            }
+            wave_sync();
           }
           int lv = oa.have ? -1 : 0;
           unsigned placed = 0u, busy = 0u;   // pairs placed so far; levels taken by the earlier pairs of the lane's shapes
@@ -1176,8 +1223,8 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
             if (now) lv = prm.lowest_free_level ? __ffs((int)~busy) - 1 : round;
             if (prm.lowest_free_level)
               for (int l = 0; l <= round; ++l)
-                if (wait & group_bits(__ballot(now && lv == l))) busy |= 1u << l;
-            placed |= group_bits(__ballot(now));
+                if (wait & (unsigned)group_bits(__ballot(now && lv == l))) busy |= 1u << l;
+            placed |= (unsigned)group_bits(__ballot(now));
           }
           if (oa.have) { oa.lv = lv; my_levels = lv + 1; }
         } else {
@@ -1576,18 +1623,19 @@ int launch_step(const StepLaunch& s) {
   }
   const int grid = (s.n_envs + K::EPW - 1) / K::EPW;
   bool ok = true;
-  if (s.order) {   // (a launch of a few steps is not worth the ordering pass)
+  int32_t* const order = K::EPW > 1 ? s.order : nullptr;   // (nothing to order where every environment has its own wavefront)
+  if (order) {   // (a launch of a few steps is not worth the ordering pass)
     // action rows that share a 128-byte line (rows of K::A floats; at least one environment per line)
     const int envs_per_line = K::A > 0 && 32 / K::A > 0 ? 32 / K::A : 1;
-    ok = order_environments(s.state, s.order, s.n_envs, grid, K::EPW, envs_per_line, K::REC_WORDS, K::L, K::J, s.stream);
+    ok = order_environments(s.state, order, s.n_envs, grid, K::EPW, envs_per_line, K::REC_WORDS, K::L, K::J, s.stream);
   }
 #ifdef K2D_PHASE_TIMERS
   K2D_LAUNCH(ok, (k2d_step_kernel<K, RESET, BATCHED>), dim3(grid), dim3(64), K::LDS_BYTES, s.stream, s.state, s.actions,
-             s.n_envs, s.n_steps, s.prm, s.levels, s.n_levels, s.reset_level, s.order,
+             s.n_envs, s.n_steps, s.prm, s.levels, s.n_levels, s.reset_level, order,
              grid <= s.phase_waves ? s.phase_clocks : nullptr);
 #else
   K2D_LAUNCH(ok, (k2d_step_kernel<K, RESET, BATCHED>), dim3(grid), dim3(64), K::LDS_BYTES, s.stream, s.state, s.actions,
-             s.n_envs, s.n_steps, s.prm, s.levels, s.n_levels, s.reset_level, s.order);
+             s.n_envs, s.n_steps, s.prm, s.levels, s.n_levels, s.reset_level, order);
 #endif
   return ok ? K2D_OK : K2D_E_HIP;
 }
@@ -1598,16 +1646,23 @@ int launch_step_as(const StepLaunch& s) {
   return s.batched ? launch_step<K, false, true>(s) : launch_step<K, false, false>(s);
 }
 
-// Lane mappings of a capacity class: 16 lanes per environment (four environments per wavefront) and 8 lanes
-// per environment (eight per wavefront: half the instructions per environment, but an LDS image twice as
-// large per wavefront).
+// Lane mappings of a capacity class.  64 lanes per environment: an environment has a wavefront to itself, waits
+// for nobody's levels but its own and spreads its shapes, pairs and manifolds over all lanes -- for batches that
+// leave wavefront slots empty.  32, 16: two or four environments to a wavefront, fewer instructions per
+// environment.  8: eight environments, half the instructions of 16 lanes again, but an LDS image twice as
+// large per wavefront.
 template <int P, int C, int J, int T>
 int launch_step_class(const StepLaunch& s) {
-  using K16 = Cfg<P, C, J, T, 16>;
-  using K8 = Cfg<P, C, J, T, 8>;
-  // the LDS images of a CU's resident wavefronts must fit its 160 KiB: eight (16 lanes) or four (8 lanes) per CU
-  static_assert(K16::LDS_BYTES * 8 <= 160 * 1024 && K8::LDS_BYTES * 4 <= 160 * 1024, "LDS image too large");
-  return s.lanes == 8 ? launch_step_as<K8>(s) : launch_step_as<K16>(s);
+  // the LDS images of a CU's resident wavefronts must fit its 160 KiB: eight (four with 8 lanes) per CU
+  static_assert(Cfg<P, C, J, T, 64>::LDS_BYTES * 8 <= 160 * 1024 && Cfg<P, C, J, T, 32>::LDS_BYTES * 8 <= 160 * 1024 &&
+                    Cfg<P, C, J, T, 16>::LDS_BYTES * 8 <= 160 * 1024 && Cfg<P, C, J, T, 8>::LDS_BYTES * 4 <= 160 * 1024,
+                "LDS image too large");
+  switch (s.lanes) {
+    case 8: return launch_step_as<Cfg<P, C, J, T, 8>>(s);
+    case 16: return launch_step_as<Cfg<P, C, J, T, 16>>(s);
+    case 32: return launch_step_as<Cfg<P, C, J, T, 32>>(s);
+    default: return launch_step_as<Cfg<P, C, J, T, 64>>(s);
+  }
 }
 
 }  // namespace k2d_impl

@@ -53,7 +53,7 @@ def main():
     if args.alone:
         return alone(L, k2d, torch, scenegen, caps, params, scene, scenegen.make_actions(args.config, n_steps, n_envs),
                      n_envs, n_steps, cfg)
-    n_waves = (n_envs + 3) // 4
+    n_waves = n_envs      # at most one wavefront per environment; the rows of wavefronts that do not exist stay zero
     slots = L.k2d_debug_set_phase_buffer(None, 0)
     buf = torch.zeros((n_waves, slots), dtype=torch.int64, device="cuda")
     L.k2d_debug_set_phase_buffer(buf.data_ptr(), n_waves)
@@ -67,6 +67,8 @@ def main():
         torch.cuda.synchronize()
     ms = e0.elapsed_time(e1)
     v = buf.cpu().numpy().astype(np.float64)
+    v = v[v[:, :len(PHASES)].any(1)]
+    n_waves = len(v)
     ph, lv = v[:, :len(PHASES)], v[:, len(PHASES):]
     tot = ph.sum(1)
     nsub = n_steps * params["n_substeps"]
@@ -103,6 +105,7 @@ def alone(L, k2d, torch, scenegen, caps, params, scene, act, n_envs, n_steps, cf
         buf = torch.zeros((len(envs), slots), dtype=torch.int64, device="cuda")
         L.k2d_debug_set_phase_buffer(buf.data_ptr(), len(envs))
         b = k2d.Batch(caps, len(order), params)
+        b.set_lanes_per_env(16)
         b.reset(words)
         b.step(a, n_steps)
         torch.cuda.synchronize()

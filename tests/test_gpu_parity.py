@@ -707,3 +707,34 @@ def test_device_sin_cos_tanh_against_libm_through_the_observation():
         worst = max(worst, np.abs(obs[:, base + 4] - np.sin(sc["thruster_angle"][:, t])).max(),
                     np.abs(obs[:, base + 5] - np.cos(sc["thruster_angle"][:, t])).max())
     assert 0.0 < worst < 1.5e-7, worst
+
+
+@pytest.mark.parametrize("n,lanes", [(3, 0), (2048, 0), (2049, 0), (4096, 0), (4097, 0), (35, 16), (35, 8)])
+@pytest.mark.parametrize("B,sweep_order", [(0, 0), (0, 1), (16, 0)])
+def test_lane_mappings_at_their_edges(n, lanes, B, sweep_order):
+    """The lane mapping that a launch takes depends on the number of environments (64 lanes per environment up to
+    2048, 32 up to 4096, then 16): both sides of every edge, a ragged last wavefront, and in each mapping three
+    environments with more colliding pairs than its registers hold (every shape dumped onto one spot) among
+    ordinary ones."""
+    caps = scenegen.CAPS["L"]
+    sb = SceneBuilder(caps, n_envs=3)
+    for e in range(3):
+        sb.box(6.0, 0.1, (0, 0), static=True, e=e)
+        for k in range(11):
+            sb.box(0.3 + 0.01 * k, 0.3, (0.01 * k + 0.01 * e, 0.35 + 0.01 * k), theta=0.05 * k, friction=0.4, e=e)
+        for k in range(4):
+            sb.circle(0.3, (0.02 * k, 0.4 + 0.02 * k), e=e)
+    piles = sb.scene()
+    _, _, sc = scenegen.make_scene(2, n_envs=n)
+    sc = {k: v.copy() for k, v in sc.items() if k in piles}
+    rows = [0, n // 2, n - 1]
+    for k in sc:
+        sc[k][rows] = np.asarray(piles[k]).reshape(3, *sc[k].shape[1:])
+    prm = mkparams(n_substeps=2, n_iters=6, alpha=0.5, beta=0.02, batch_size=B, sweep_order=sweep_order)
+    act = scenegen.make_actions(2, 3, n)
+    o = parity.run_oracle(caps, prm, sc, act)
+    b = parity.run_gpu(caps, prm, sc, act, lanes=lanes)
+    gs, os_ = b.state_dict(), o.state()
+    assert (os_["pair_count"] > 0).sum(1).max() > 62
+    for k in parity.FLOAT_KEYS + parity.INT_KEYS:
+        assert np.array_equal(gs[k], os_[k]), k
