@@ -64,7 +64,9 @@ struct Cfg {
   static constexpr int X_LVL = X_TAKEN + (N + 1) / 2;      // bytes [LISTED]: level of a pair not held in registers
   static constexpr int LCAP = 16;                          // a level holds at most one pair per movable shape
   static constexpr int X_SCHED = X_LVL + (LISTED + 3) / 4; // bytes [R][LCAP]: the pairs not held in registers, level by level
-  static_assert(X_SCHED + R * LCAP / 4 <= X_WV + WSTRIDE * P, "what shares the world polygons' LDS");
+  static constexpr int SEEN = NP < 64 ? NP : 64;
+  static constexpr int X_SEEN = X_SCHED + R * LCAP / 4;    // words [SEEN]: shapes met in a batch of A.8
+  static_assert(X_SEEN + SEEN <= X_WV + WSTRIDE * P, "what shares the world polygons' LDS");
   static constexpr int X_LIST = X_WV + WSTRIDE * P;        // 16-bit [NP]: candidate pairs, one shape-type mix after the other
   static constexpr int X_ELIG = X_LIST;                    // (episode set-up only) bytes [NP]: eligible pairs
   static constexpr int X_PSB = X_LIST;                     // (write-back only) bytes [NP]: pair states in lexicographic pair order
@@ -138,6 +140,15 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }
+// A number in a scalar register that the compiler cannot reason about: a comparison of it stays a scalar comparison where it
+// stands (hoisted out of a loop it would become a lane mask, and the branch on that mask waits for the vector unit).
+__device__ __forceinline__ int opaque(int n) {
+  asm volatile("" : "+s"(n));
+  return n;
+}
+// A number that is the same in all lanes, in a scalar register.
+__device__ __forceinline__ int scalar(int n) { return __builtin_amdgcn_readfirstlane(n); }
+
 // Stores of one lane to HBM that another lane of the wavefront is to read.
 __device__ __forceinline__ void hbm_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -182,6 +193,13 @@ constexpr int kInRecord = 63;
 using LdsF = __attribute__((address_space(3))) float*;
 using LdsCF = const __attribute__((address_space(3))) float*;
 __device__ __forceinline__ LdsF to_lds(float* p) { return (LdsF)p; }
+
+// A body of a register-held pair as a visit addresses it: LDS entry of its position; the velocities are a fixed
+// distance behind it.
+typedef float vec4 __attribute__((ext_vector_type(4)));
+typedef float vec2 __attribute__((ext_vector_type(2)));
+using BodyPtr = __attribute__((address_space(3))) vec4*;
+using PosPtr = __attribute__((address_space(3))) vec2*;
 
 template <class Ptr>
 __device__ __forceinline__ void rec_store(Ptr p, const PairRec& r) {
@@ -312,18 +330,16 @@ struct Step {
     };
     if constexpr (W >= 2) take(std::integral_constant<int, kQuadXor1>{});
     if constexpr (W == 4) take(std::integral_constant<int, kQuadXor2>{});
-    if (smax <= 0.f) {   // centre inside the polygon: the face of largest signed distance
-      m.nx = snx; m.ny = sny;
-      m.pen[0] = rb - smax;
-      m.px[0] = cx - smax * snx;
-      m.py[0] = cy - smax * sny;
-    } else {
-      float dist = sqrtf(best_d2);
-      float dqx = cx - qx, dqy = cy - qy;
-      m.nx = dqx / dist; m.ny = dqy / dist;
-      m.pen[0] = rb - dist;
-      m.px[0] = qx; m.py[0] = qy;
-    }
+    // centre inside the polygon: the face of largest signed distance; outside: the closest boundary point.  (Both are
+    // worked out and picked: a branch costs a wavefront more than the few instructions it could skip.)
+    const bool inside = smax <= 0.f;
+    const float dist = sqrtf(best_d2);
+    const float dqx = cx - qx, dqy = cy - qy;
+    m.nx = inside ? snx : dqx / dist;
+    m.ny = inside ? sny : dqy / dist;
+    m.pen[0] = rb - (inside ? smax : dist);
+    m.px[0] = inside ? cx - smax * snx : qx;
+    m.py[0] = inside ? cy - smax * sny : qy;
     m.valid[0] = true;
   }
 
@@ -384,7 +400,8 @@ struct Step {
       sb = K2D_DPPF(sa, kQuadXor1);
       ib = K2D_DPP(ia, kQuadXor1);
     }
-    if (fmaxf(sa, sb) >= 0.f) return;   // a separating axis exists
+    // (no branch from here on either: what a pair without contact computes is thrown away)
+    const bool apart = fmaxf(sa, sb) >= 0.f;   // a separating axis exists
     bool ref_b = sb > sa + tie_eps;
     int pr = ref_b ? pb : pa, ir = ref_b ? ib : ia;
     int pi = ref_b ? pa : pb;
@@ -407,22 +424,20 @@ struct Step {
     float u0 = dot2(tx, ty, v0.x - r1.x, v0.y - r1.y);
     float u1 = dot2(tx, ty, v1.x - r1.x, v1.y - r1.y);
     float len = dot2(tx, ty, r2.x - r1.x, r2.y - r1.y);
-    if ((u0 < 0.f && u1 < 0.f) || (u0 > len && u1 > len)) return;
+    const bool beside = (u0 < 0.f && u1 < 0.f) || (u0 > len && u1 > len);
     m.nx = ref_b ? -nref.x : nref.x;
     m.ny = ref_b ? -nref.y : nref.y;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       float uk = k ? u1 : u0;
       float uc = fminf(fmaxf(uk, 0.f), len);
-      float x = k ? v1.x : v0.x, y = k ? v1.y : v0.y;
-      if (uc != uk) {
-        float s = (uc - u0) / (u1 - u0);
-        x = v0.x + s * (v1.x - v0.x);
-        y = v0.y + s * (v1.y - v0.y);
-      }
+      const float s = (uc - u0) / (u1 - u0);
+      const bool clip = uc != uk;
+      const float x = clip ? v0.x + s * (v1.x - v0.x) : k ? v1.x : v0.x;
+      const float y = clip ? v0.y + s * (v1.y - v0.y) : k ? v1.y : v0.y;
       m.px[k] = x; m.py[k] = y;
       m.pen[k] = -dot2(nref.x, nref.y, x - r1.x, y - r1.y);
-      m.valid[k] = true;
+      m.valid[k] = !apart && !beside;
     }
   }
 
@@ -464,13 +479,13 @@ struct Step {
     solve_slot(rc, 0, ima, iia, imb, iib, va, vb);
     if (two) solve_slot(rc, 1, ima, iia, imb, iib, va, vb);
   }
-  // Batched schedule (A.8): slot q of a pair solved on private copies of the two bodies' velocities (the
-  // arithmetic of solve_slot); returns the normal impulse (jx, jy) and the friction impulse (fx, fy)
-  // that a receives, for the batch to apply afterwards, and the contact arms.  (With more than one batch
-  // the two points of a pair never share a batch, so one visit handles at most one of them: its
-  // constants are picked by q, which keeps the record in registers.)
+  // Batched schedule (A.8): slot q of a pair solved on the two bodies' velocities (the arithmetic of solve_slot);
+  // also returns the normal impulse (jx, jy) and the friction impulse (fx, fy) that a receives and the contact
+  // arms, for a batch that applies them afterwards.  (With more than one batch the two points of a pair never
+  // share a batch, so one visit handles at most one of them: its constants are picked by q, which keeps the
+  // record in registers.)
   static __device__ __forceinline__ void point_impulses(PairRec& rc, bool q, float ima, float iia, float imb, float iib,
-                                                        float4 va, float4 vb, float& jx, float& jy, float& fx,
+                                                        float4& va, float4& vb, float& jx, float& jy, float& fx,
                                                         float& fy, float& rax, float& ray, float& rbx, float& rby) {
     const float tx = -rc.ny, ty = rc.nx;
     rax = q ? rc.rax[1] : rc.rax[0]; ray = q ? rc.ray[1] : rc.ray[0];
@@ -494,8 +509,10 @@ struct Step {
     float lt = fminf(fmaxf(lam_t + dt_, -lim), lim);
     dt_ = lt - lam_t;
     fx = dt_ * tx; fy = dt_ * ty;
-    if (q) { rc.lam_n[1] = ln; rc.lam_t[1] = lt; }
-    else { rc.lam_n[0] = ln; rc.lam_t[0] = lt; }
+    apply_impulse(va, ima, iia, fx, fy, rax, ray);
+    apply_impulse(vb, imb, iib, -fx, -fy, rbx, rby);
+    rc.lam_n[0] = q ? rc.lam_n[0] : ln; rc.lam_t[0] = q ? rc.lam_t[0] : lt;
+    rc.lam_n[1] = q ? ln : rc.lam_n[1]; rc.lam_t[1] = q ? lt : rc.lam_t[1];
   }
   // Where the slots of a pair fall in the batched schedule: the manifold points, two per pair in tournament
   // order, are dealt in turn over n_b batches.  Returns batch | place<<8 of slot 0, the same <<16 of slot 1.
@@ -547,8 +564,9 @@ struct Step {
   struct Own {
     PairRec rc;
     float ima, iia, imb, iib;
-    int pa, pb;   // shape indices
-    int sa, sb;   // where results go back: the shape itself, or entry N if no impulse moves it
+    int pa, pb;               // shape indices
+    BodyPtr at_a, at_b;       // the shapes' LDS entries
+    BodyPtr to_a, to_b;       // where results go back: the shape's entry, or entry N if no impulse moves it
     bool have;
     int lv;       // dependency level of this substep, -1 = nothing held
   };
@@ -569,8 +587,6 @@ struct Step {
     const float2 pa = xy(E, a), pb = xy(E, b);
     const float4 va = vel4(E, a), vb = vel4(E, b);
     const float tx = -m.ny, ty = m.nx;
-    rc.rax[1] = rc.ray[1] = rc.rbx[1] = rc.rby[1] = rc.mass_n[1] = rc.mass_t[1] = rc.bias[1] = rc.rest[1] = 0.f;
-    rc.lam_n[1] = rc.lam_t[1] = 0.f;
     auto slot = [&](int q, float px, float py, float pen, bool had, float ln, float lt) {
       rc.rax[q] = px - pa.x; rc.ray[q] = py - pa.y;
       rc.rbx[q] = px - pb.x; rc.rby[q] = py - pb.y;
@@ -594,21 +610,27 @@ struct Step {
     const float pen0 = swapped ? m.pen[1] : m.pen[0];
     slot(0, swapped ? m.px[1] : m.px[0], swapped ? m.py[1] : m.py[0], pen0, (swapped ? prev >> 1 : prev) & 1u,
          swapped ? lam.z : lam.x, swapped ? lam.w : lam.y);
+    // (slot 1 of a pair that has one active point is worked out too, and never looked at)
+    slot(1, m.px[1], m.py[1], m.pen[1], two && (prev >> 1), lam.z, lam.w);
     float pen = fmaxf(0.f, pen0);
-    if (two) {
-      slot(1, m.px[1], m.py[1], m.pen[1], prev >> 1, lam.z, lam.w);
-      pen = fmaxf(pen, m.pen[1]);
-    }
+    pen = two ? fmaxf(pen, m.pen[1]) : pen;
     rc.corr = prm.beta * fmaxf(pen - prm.slop, 0.f) / (ima + imb);          // A.3.7
   }
+  static constexpr int kVel = (K::X_VEL - K::X_POS) / 4;   // from a body's position to its velocities, in 16-byte words
+  static __device__ __forceinline__ BodyPtr body(float* E, int i) { return (BodyPtr)(E + K::X_POS + 4 * i); }
+  static __device__ __forceinline__ float4 get_vel(BodyPtr p) {
+    const vec4 v = p[kVel];
+    return make_float4(v.x, v.y, v.z, v.w);
+  }
+  static __device__ __forceinline__ void put_vel(BodyPtr p, const float4& v) { p[kVel] = vec4{v.x, v.y, v.z, v.w}; }
   template <bool WARM>
-  static __device__ __forceinline__ void visit_own(float* E, Own& o) {
-    float4 va = vel4(E, o.pa), vb = vel4(E, o.pb);
+  static __device__ __forceinline__ void visit_own(Own& o) {
+    float4 va = get_vel(o.at_a), vb = get_vel(o.at_b);
     const bool two = o.rc.ab & kTwo;
     if (WARM) warm_points(o.rc, two, o.ima, o.iia, o.imb, o.iib, va, vb);
     else solve_points(o.rc, two, o.ima, o.iia, o.imb, o.iib, va, vb);
-    vel4(E, o.sa) = va;
-    vel4(E, o.sb) = vb;
+    put_vel(o.to_a, va);
+    put_vel(o.to_b, vb);
   }
 };
 
@@ -616,7 +638,7 @@ struct Step {
 // record l of `levels` (what k2d_reset does between launches, without leaving the kernel).
 // BATCHED: the collision constraints of a sweep are solved in the batches of A.8 instead of level by level.
 template <class K, bool RESET, bool BATCHED>
-__global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
+__global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
     k2d_step_kernel(float* __restrict__ state, const float* __restrict__ actions, int n_envs, int n_steps, Params prm,
                     const float* __restrict__ levels, int n_level_records, const int32_t* __restrict__ reset_level,
                     const int32_t* __restrict__ order
@@ -641,6 +663,15 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
     else return (Bits)(bal >> (g * G)) & ((1u << G) - 1u);
   };
   const Bits below = ((Bits)1 << k) - 1;
+  // Largest over the wavefront's environments of a value that is the same in all lanes of an environment, in a scalar
+  // register.  (A vote on a vector comparison makes the branch behind it wait some thirty clocks for the vector
+  // unit; comparing scalars does not.)
+  auto wave_max = [&](int v) {
+    int m = __builtin_amdgcn_readlane(v, 0);
+#pragma unroll
+    for (int e = 1; e < K::EPW; ++e) m = max(m, __builtin_amdgcn_readlane(v, e * G));
+    return m;
+  };
   // which environment this lane works for: a launch may come with an ordering of the environments
   // (slot -> environment, -1 = none) that puts similar ones together; without one, slot s is environment s
   const int slot = blockIdx.x * K::EPW + g;
@@ -849,17 +880,42 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
   }
   wave_sync();
   // levels and list lengths are per environment; the wavefront walks as many as its largest one has
-  int wave_levels = 0, cull_trips = 0;
-#pragma unroll
-  for (int lv = 1; lv <= J; ++lv)
-    if (__any(n_levels >= lv)) wave_levels = lv;
-#pragma unroll
-  for (int t = 0; t < ET; ++t)
-    if (__any(n_elig > t * G)) cull_trips = t + 1;
+  const int wave_levels = scalar(wave_max(n_levels)), cull_trips = scalar((wave_max(n_elig) + G - 1) / G);
   const bool any_motor = __any(j_live && j_motor && !j_fixed);
-  const bool any_angular = __any(j_live && (j_fixed || j_limited));
+  // which angular rows the wavefront's joints have: none, those of fixed joints, those of limited ones too
+  const int angular_rows = scalar(__any(j_live && j_limited) ? 2 : __any(j_live && j_fixed) ? 1 : 0);
+  // the joints level by level: the lanes of a level as a mask that is there already when the level comes up
+  const bool j_at0 = j_live && j_level == 0, j_at1 = j_live && j_level == 1, j_at2 = j_live && j_level == 2;
+  auto for_each_joint_level = [&](auto&& f) {
+    const int n = opaque(wave_levels);
+    if (n > 0) {
+      if (j_at0) f();
+      wave_sync();
+      if (J > 1 && n > 1) {
+        if (j_at1) f();
+        wave_sync();
+        if (J > 2 && n > 2) {
+          if (j_at2) f();
+          wave_sync();
+          for (int lv = 3; lv < n; ++lv) {
+            if (j_live && j_level == lv) f();
+            wave_sync();
+          }
+        }
+      }
+    }
+  };
+  // thrusters push their bodies one after the other (index order) where two of them sit on one body
+  bool thr_clash = false;
+#pragma unroll
+  for (int t = 1; t < T; ++t) {
+    const int other = __shfl_up(t_live ? t_body : -1 - t, t, G);
+    thr_clash |= k < T && k >= t && t_live && other == t_body;
+  }
+  const bool thr_serial = __any(thr_clash);
   // where a joint's results go: the shape, or the entry that swallows them if no impulse moves the shape
-  const int jsa = ja_fix ? N : ja, jsb = jb_fix ? N : jb;
+  const BodyPtr j_at_a = S::body(E, ja), j_at_b = S::body(E, jb);
+  const BodyPtr j_to_a = S::body(E, ja_fix ? N : ja), j_to_b = S::body(E, jb_fix ? N : jb);
   // Dependency levels of the collision constraints are kept from one substep to the next: they depend
   // only on which pairs collide and which lane keeps which pair, and both are the same in most consecutive
   // substeps.  Likewise the list of candidate pairs (it stays in LDS) while no lane's candidates change.
@@ -867,7 +923,9 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
   int lv_a = -1, lv_b = -1;   // levels of the lane's pairs
   bool levels_valid = false;  // false until the levels of the current set of colliding pairs are worked out
   unsigned prev_cand = 0u, kind_tot = 0u;
+  int most_pp = 0, most_pc = 0, most_cc = 0;   // candidates of each mix in the environment that has most of it
   bool list_valid = false;
+  bool in_record = true;      // some pair's accumulated impulses may be in the HBM record
 
   for (; step < n_steps; ++step) {
     float act_m = 0.f, act_t = 0.f;
@@ -921,7 +979,7 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
       // ---- joint constants of this substep; motor and thruster impulses from the same velocities ----
       float j_rax = 0.f, j_ray = 0.f, j_rbx = 0.f, j_rby = 0.f, j_k11 = 0.f, j_k12 = 0.f, j_k22 = 0.f;
       float j_idet = 0.f, j_bx = 0.f, j_by = 0.f, j_angb = 0.f, j_exc = 0.f, motor = 0.f;
-      if (k < J && j_live) {
+      if (j_live) {
         if (!prm.warm_start) { j_accx = 0.f; j_accy = 0.f; j_acca = 0.f; }
         const float4 fa = S::pos4(E, ja), fb = S::pos4(E, jb);
         const float4 va = S::vel4(E, ja), vb = S::vel4(E, jb);
@@ -948,7 +1006,7 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
         }
       }
       float t_ix = 0.f, t_iy = 0.f, t_rx = 0.f, t_ry = 0.f;
-      if (k < T && t_live) {   // A.6
+      if (t_live) {   // A.6
         const float4 f = S::pos4(E, t_body);
         const float dx = fmaf(f.z, t_dx, -(f.w * t_dy)), dy = fmaf(f.w, t_dx, f.z * t_dy);
         t_rx = fmaf(f.z, t_px, -(f.w * t_py)); t_ry = fmaf(f.w, t_px, f.z * t_py);
@@ -957,22 +1015,27 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
       }
       K2D_T(kT_JointConstants);
       wave_sync();
-      if (any_motor)
-        for (int lv = 0; lv < wave_levels; ++lv) {
-          if (k < J && j_live && j_level == lv && motor != 0.f) {
-            float *wa = E + K::X_VEL + 4 * ja + 2, *wb = E + K::X_VEL + 4 * jb + 2;
-            if (!ja_fix) *wa = *wa - j_iia * motor;
-            if (!jb_fix) *wb = *wb + j_iib * motor;
-          }
+      if (any_motor) {
+        const bool turns = motor != 0.f;
+        for_each_joint_level([&]() {
+          const float wa = ((LdsF)(j_at_a + S::kVel))[2], wb = ((LdsF)(j_at_b + S::kVel))[2];
+          ((LdsF)(j_to_a + S::kVel))[2] = turns ? wa - j_iia * motor : wa;
+          ((LdsF)(j_to_b + S::kVel))[2] = turns ? wb + j_iib * motor : wb;
+        });
+      }
+      auto push = [&]() {
+        float4 v = S::vel4(E, t_body);
+        apply_impulse(v, t_im, t_ii, t_ix, t_iy, t_rx, t_ry);
+        S::vel4(E, t_body) = v;
+      };
+      if (!thr_serial) {
+        if (t_live) push();
+        wave_sync();
+      } else {
+        for (int t = 0; t < T; ++t) {
+          if (k == t && t_live) push();
           wave_sync();
         }
-      for (int t = 0; t < T; ++t) {
-        if (k == t && t_live) {
-          float4 v = S::vel4(E, t_body);
-          apply_impulse(v, t_im, t_ii, t_ix, t_iy, t_rx, t_ry);
-          S::vel4(E, t_body) = v;
-        }
-        wave_sync();
       }
 
       K2D_T(kT_External);
@@ -1034,10 +1097,22 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
         put(m0, w0);
         put(m1, w1);
         put(m2, w2);
+        most_pp = wave_max(kind_tot & 255);
+        most_pc = wave_max((kind_tot >> 8) & 255);
+        most_cc = wave_max((kind_tot >> 16) & 255);
       }
       wave_sync();
       K2D_T(kT_Cull);
       int n_act = 0;   // active pairs of the environment so far
+      // the impulses a pair has accumulated (looked at only if one of its points was active in the previous substep)
+      auto stored_lam = [&](int prev, int a, int b) {
+        const int at = prev >> 2;
+        float4 lam = lam_store[at < K::NREG ? at : 0];
+        if (in_record) {
+          if ((prev & 3) && at == kInRecord) lam = *reinterpret_cast<const float4*>(Rg + L.lambda + 4 * S::pair_index(a, b));
+        }
+        return lam;
+      };
       // `lead`: this lane has the manifold m of candidate e (a pair that lanes share: the first of them)
       auto emit = [&](bool lead, const Manifold& m, unsigned e, int prev) {
         const bool act0 = lead && m.valid[0] && m.pen[0] > 0.f, act1 = lead && m.valid[1] && m.pen[1] > 0.f;
@@ -1058,11 +1133,7 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
             reinterpret_cast<int*>(p)[8] = w;
           } else if constexpr (K::LISTED > 0) {   // beyond the register-held pairs: a full record in the LDS pool or in HBM
             const int a = ab & 15, b = ab >> 4;
-            float4 lam = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (prm.warm_start && (prev & 3)) {
-              if ((prev >> 2) != kInRecord) lam = lam_store[prev >> 2];
-              else lam = *reinterpret_cast<const float4*>(Rg + L.lambda + 4 * S::pair_index(a, b));
-            }
+            const float4 lam = stored_lam(prev, a, b);
             PairRec rc;
             float ima, iia, imb, iib;
             S::presolve(E, prm, m, w, lam, rc, ima, iia, imb, iib);
@@ -1076,32 +1147,29 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
       const int n_pp = kind_tot & 255, n_pc = (kind_tot >> 8) & 255, n_cc = (kind_tot >> 16) & 255;
       auto run_pp = [&](auto width) {
         constexpr int W = decltype(width)::value;
-        for (int base = 0; __any(base < n_pp); base += G / W) {
+        for (int base = 0; base < most_pp; base += G / W) {
           Manifold m;
           const int c = base + k / W;
           const bool have = c < n_pp;
-          const unsigned e = have ? cand_list[c] : 0u;
-          const int prev = have ? (int)pst[e >> 8] : 0;
-          if (have) {
-            const int a = e & 15, b = (e >> 4) & 15;
-            S::template manifold_pp<W>(E, k % W, a, (tri_mask >> a) & 1u, b, (tri_mask >> b) & 1u, prm.tie_eps, m);
-          }
+          // (a lane without a candidate works on polygons 0 and 1, and nobody looks at what it finds)
+          const unsigned e = have ? cand_list[c] : 0x10u;
+          const int prev = pst[e >> 8];
+          const int a = e & 15, b = (e >> 4) & 15;
+          S::template manifold_pp<W>(E, k % W, a, (tri_mask >> a) & 1u, b, (tri_mask >> b) & 1u, prm.tie_eps, m);
           emit(have && k % W == 0, m, e, prev);
         }
       };
       auto run_pc = [&](auto width) {
         constexpr int W = decltype(width)::value;
-        for (int base = 0; __any(base < n_pc); base += G / W) {
+        for (int base = 0; base < most_pc; base += G / W) {
           Manifold m;
           const int c = base + k / W;
           const bool have = c < n_pc;
-          const unsigned e = have ? cand_list[n_pp + c] : 0u;
-          const int prev = have ? (int)pst[e >> 8] : 0;
-          if (have) {
-            const int a = e & 15, b = (e >> 4) & 15;
-            const float2 p = S::xy(E, b);
-            S::template manifold_pc<W>(E, k % W, a, (tri_mask >> a) & 1u, p.x, p.y, E[K::X_RAD + (b - P)], m);
-          }
+          const unsigned e = have ? cand_list[n_pp + c] : (unsigned)P << 4;
+          const int prev = pst[e >> 8];
+          const int a = e & 15, b = (e >> 4) & 15;
+          const float2 p = S::xy(E, b);
+          S::template manifold_pc<W>(E, k % W, a, (tri_mask >> a) & 1u, p.x, p.y, E[K::X_RAD + (b - P)], m);
           emit(have && k % W == 0, m, e, prev);
         }
       };
@@ -1110,22 +1178,20 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
       using I1 = std::integral_constant<int, 1>;
       using I2 = std::integral_constant<int, 2>;
       using I4 = std::integral_constant<int, 4>;
-      if (G >= 32 && !__any(n_pp > G / 4)) run_pp(I4{});
-      else if (G == 64 || !__any(n_pp > G / 2)) run_pp(I2{});
+      if (G >= 32 && most_pp <= G / 4) run_pp(I4{});
+      else if (G == 64 || most_pp <= G / 2) run_pp(I2{});
       else run_pp(I1{});
-      if (G >= 32 || !__any(n_pc > G / 4)) run_pc(I4{});
+      if (G >= 32 || most_pc <= G / 4) run_pc(I4{});
       else run_pc(I2{});
-      for (int base = 0; __any(base < n_cc); base += G) {
+      for (int base = 0; base < most_cc; base += G) {
         Manifold m;
         const int c = base + k;
         const bool have = c < n_cc;
-        const unsigned e = have ? cand_list[n_pp + n_pc + c] : 0u;
-        const int prev = have ? (int)pst[e >> 8] : 0;
-        if (have) {
-          const int a = e & 15, b = (e >> 4) & 15;
-          const float2 pa = S::xy(E, a), pb = S::xy(E, b);
-          S::manifold_cc(pa.x, pa.y, E[K::X_RAD + (a - P)], pb.x, pb.y, E[K::X_RAD + (b - P)], m);
-        }
+        const unsigned e = have ? cand_list[n_pp + n_pc + c] : (unsigned)(P | ((P + 1) << 4));
+        const int prev = pst[e >> 8];
+        const int a = e & 15, b = (e >> 4) & 15;
+        const float2 pa = S::xy(E, a), pb = S::xy(E, b);
+        S::manifold_cc(pa.x, pa.y, E[K::X_RAD + (a - P)], pb.x, pb.y, E[K::X_RAD + (b - P)], m);
         emit(have, m, e, prev);
       }
       wave_sync();
@@ -1142,25 +1208,22 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
         m.nx = p0.x; m.ny = p0.y; m.px[0] = p0.z; m.py[0] = p0.w;
         m.pen[0] = p1.x; m.px[1] = p1.y; m.py[1] = p1.z; m.pen[1] = p1.w;
         const int a = w & 15, b = (w >> 4) & 15, prev = w >> 10;
-        float4 lam = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (prm.warm_start && (prev & 3)) {   // the impulses it accumulated
-          if ((prev >> 2) != kInRecord) lam = lam_store[prev >> 2];
-          else lam = *reinterpret_cast<const float4*>(Rg + L.lambda + 4 * S::pair_index(a, b));
-        }
-        S::presolve(E, prm, m, w, lam, o.rc, o.ima, o.iia, o.imb, o.iib);
+        S::presolve(E, prm, m, w, stored_lam(prev, a, b), o.rc, o.ima, o.iia, o.imb, o.iib);
         o.pa = a; o.pb = b;
-        o.sa = ((static_mask >> a) & 1u) ? N : a;
-        o.sb = ((static_mask >> b) & 1u) ? N : b;
+        o.at_a = S::body(E, a); o.at_b = S::body(E, b);
+        o.to_a = S::body(E, ((static_mask >> a) & 1u) ? N : a);
+        o.to_b = S::body(E, ((static_mask >> b) & 1u) ? N : b);
         o.have = true;
       };
       if (k < n_act && k < K::NREG) take(k, oa);
-      bool any_b = false;   // a lane of the wavefront holds a second pair
+      const int most_act = wave_max(n_act);         // (scalar: every branch on it below is one on scalars)
+      const bool any_b = K::TWO && most_act > G;    // a lane of the wavefront holds a second pair
       if constexpr (K::TWO) {
-        any_b = __any(n_act > G);
         if (any_b && k + G < n_act && k + G < K::NREG) take(k + G, ob);
       }
       const int n_listed = max(n_act - K::NREG, 0);
-      const bool any_listed = K::LISTED > 0 && __any(n_listed > 0);
+      const bool any_listed = most_act > K::NREG;
+      in_record = any_listed;
       wave_sync();
       K2D_T(kT_Presolve);
       // Levels of the active pairs.  The colliding pairs are walked in tournament order (round by round).
@@ -1176,21 +1239,16 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
       unsigned long long level_cnt = 0ull;   // listed pairs per level, 4 bits each (a level holds fewer than 16)
       if (!levels_valid || !same_list || any_listed || __any(set_changed)) {
         auto movable = [&](int a, int b) { return ((1u << a) | (1u << b)) & ~static_mask; };
-        int my_levels = 0;
-        if (!any_b && !(G == 64 && __any(n_act > 32))) {
+        if (!any_b && most_act <= 32) {
           // One pair per lane at most: every lane learns which of the environment's pairs come earlier and share
           // a movable shape with its own (a round's pairs are disjoint, so the order of the rounds decides), and a
           // pair can be placed once all of those are.
           const unsigned mine = oa.have ? (unsigned)S::round_of(oa.pa, oa.pb) << 16 | movable(oa.pa, oa.pb) : 0u;
           unsigned wait = 0u;
           if constexpr (G <= 16) {
-            int most = 0;
-#pragma unroll
-            for (int z = 1; z <= G; ++z)
-              if (__any(n_act >= z)) most = z;
             auto meet = [&](auto z) {
               constexpr int q = decltype(z)::value;
-              if (q < most) {
+              if (q < most_act) {
                 const unsigned o = group_bcast<G, q>(mine, g);
                 if ((o & mine & 0xffffu) != 0u && o < mine) wait |= 1u << q;
               }
@@ -1207,7 +1265,7 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
             unsigned* all = reinterpret_cast<unsigned*>(E + K::X_STAGE);
             if (k < 32) all[k] = mine;
             wave_sync();
-            for (int q = 0; __any(q < n_act); q += 4) {
+            for (int q = 0; q < most_act; q += 4) {
               const uint4 o = *reinterpret_cast<const uint4*>(all + q);
               if ((o.x & mine & 0xffffu) != 0u && o.x < mine) wait |= 1u << q;
               if ((o.y & mine & 0xffffu) != 0u && o.y < mine) wait |= 2u << q;
@@ -1218,7 +1276,8 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
           }
           int lv = oa.have ? -1 : 0;
           unsigned placed = 0u, busy = 0u;   // pairs placed so far; levels taken by the earlier pairs of the lane's shapes
-          for (int round = 0; __any(lv < 0); ++round) {   // (at least the earliest unplaced pair is placed every time)
+          int round = 0;
+          for (; __any(lv < 0); ++round) {   // (at least the earliest unplaced pair is placed every time)
             const bool now = lv < 0 && (wait & ~placed) == 0u;
             if (now) lv = prm.lowest_free_level ? __ffs((int)~busy) - 1 : round;
             if (prm.lowest_free_level)
@@ -1226,11 +1285,15 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
                 if (wait & (unsigned)group_bits(__ballot(now && lv == l))) busy |= 1u << l;
             placed |= (unsigned)group_bits(__ballot(now));
           }
-          if (oa.have) { oa.lv = lv; my_levels = lv + 1; }
+          if (oa.have) oa.lv = lv;
+          wave_clevels = round;
+          if (prm.lowest_free_level)   // (a pair may find a lower level free than the number of pairs it waited for)
+            while (wave_clevels > 1 && !__any(oa.lv == wave_clevels - 1)) --wave_clevels;
         } else {
           // Some lane holds more than one pair: round by round, through the sets of levels taken at every shape
           // (16-bit words in LDS).  The pairs of a round touch disjoint shapes, so the lanes of a round read and
           // extend those sets without getting in each other's way, and the rounds follow one another.
+          int my_levels = 0;
           if (k < (N + 1) / 2) reinterpret_cast<unsigned*>(taken)[k] = 0u;
           if (G < (N + 1) / 2 && k + G < (N + 1) / 2) reinterpret_cast<unsigned*>(taken)[k + G] = 0u;
           wave_sync();
@@ -1252,10 +1315,10 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
                 if (q < n_listed && S::round_of(lt[q] & 15, lt[q] >> 4) == r) lvl[q] = (unsigned char)place(lt[q] & 15, lt[q] >> 4);
             wave_sync();
           }
+          wave_clevels = 0;
+          for (int lv = 1; lv <= R; ++lv)
+            if (__any(my_levels >= lv)) wave_clevels = lv;
         }
-        wave_clevels = 0;
-        for (int lv = 1; lv <= R; ++lv)
-          if (__any(my_levels >= lv)) wave_clevels = lv;
         levels_valid = true;
         lv_a = oa.lv; lv_b = ob.lv;
         // the pairs that are not held in registers are listed level by level (lane s mod G writes entry s)
@@ -1272,12 +1335,25 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
       }
       oa.lv = lv_a; ob.lv = lv_b;
       auto cnt_of = [&](int lv) { return (int)((level_cnt >> (4 * lv)) & 15ull); };
+      const bool at0 = oa.lv == 0, at1 = oa.lv == 1, at2 = oa.lv == 2;
       // one level at a time: the pairs held in registers (first and second of the lane), then the listed ones
       auto for_each_level = [&](auto&& f_own, auto&& f_listed) {
-        if (!any_b && !any_listed) {   // the common case, as a loop of its own: one pair per lane, all in registers
-          for (int lv = 0; lv < wave_clevels; ++lv) {
-            if (oa.lv == lv) f_own(oa);
+        if (!any_b && !any_listed) {   // the common case, unrolled: one pair per lane, all in registers
+          if (wave_clevels > 0) {
+            if (at0) f_own(oa);
             wave_sync();
+            if (wave_clevels > 1) {
+              if (at1) f_own(oa);
+              wave_sync();
+              if (wave_clevels > 2) {
+                if (at2) f_own(oa);
+                wave_sync();
+                for (int lv = 3; lv < wave_clevels; ++lv) {
+                  if (oa.lv == lv) f_own(oa);
+                  wave_sync();
+                }
+              }
+            }
           }
           return;
         }
@@ -1305,71 +1381,134 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
 #endif
       // ---- warm starting (Alg. 1, A.7): collisions level after level, then joints ----
       if (prm.warm_start) {
-        for_each_level([&](Own& o) { S::template visit_own<true>(E, o); },
+        for_each_level([&](Own& o) { S::template visit_own<true>(o); },
                        [&](int q) {
                          PairRec rc;
                          if (q < K::POOL) rec_load(to_lds(pool + q * kRecW), rc);
                          else rec_load(spill + (q - K::POOL) * kRecW, rc);
                          S::template visit_pair<true>(E, rc, static_mask);
                        });
-        for (int lv = 0; lv < wave_levels; ++lv) {
-          if (k < J && j_live && j_level == lv) {
-            float4 va = S::vel4(E, ja), vb = S::vel4(E, jb);
-            if (j_fixed) {
-              va.z = va.z + j_iia * j_acca;
-              vb.z = vb.z - j_iib * j_acca;
-            }
-            apply_impulse(va, j_ima, j_iia, j_accx, j_accy, j_rax, j_ray);
-            apply_impulse(vb, j_imb, j_iib, -j_accx, -j_accy, j_rbx, j_rby);
-            S::vel4(E, jsa) = va;
-            S::vel4(E, jsb) = vb;
-          }
-          wave_sync();
-        }
+        for_each_joint_level([&]() {
+          float4 va = S::get_vel(j_at_a), vb = S::get_vel(j_at_b);
+          va.z = j_fixed ? va.z + j_iia * j_acca : va.z;
+          vb.z = j_fixed ? vb.z - j_iib * j_acca : vb.z;
+          apply_impulse(va, j_ima, j_iia, j_accx, j_accy, j_rax, j_ray);
+          apply_impulse(vb, j_imb, j_iib, -j_accx, -j_accy, j_rbx, j_rby);
+          S::put_vel(j_to_a, va);
+          S::put_vel(j_to_b, vb);
+        });
       }
 
       K2D_T(kT_WarmStart);
       // ---- solver sweeps (Alg. 1): joints, then collisions ----
-      const int n_b = BATCHED ? prm.n_batches : 1;
-      int oa_bj = 0, ob_bj = 0;   // batched schedule: batch and place of the two slots of the held pairs
-      if constexpr (BATCHED) {
-        if (oa.have) oa_bj = S::batch_places(oa.rc.ab, n_b);
-        if (ob.have) ob_bj = S::batch_places(ob.rc.ab, n_b);
-      }
       const bool j_ang = j_fixed && j_angm > 0.f;                     // A.4.2: the joint has an angular row
       const bool j_lim = !j_fixed && j_exc != 0.f && j_angm > 0.f;    // A.4.3: it is beyond a limit
-      for (int it = 0; it < prm.n_iters; ++it) {
-        for (int lv = 0; lv < wave_levels; ++lv) {
-          if (k < J && j_live && j_level == lv) {
-            float4 va = S::vel4(E, ja), vb = S::vel4(E, jb);
-            if (any_angular) {
-              // (both kinds of angular row are worked out and picked by lane: a wavefront that has one pays for no branch)
-              const float w = va.z - vb.z;
+      // ROWS: 0 = no joint of the wavefront has an angular row, 1 = fixed joints have one (A.4.2), 2 = limited ones
+      // too (A.4.3).  (The row is worked out by all lanes and picked by those that have one.)
+      auto visit_joints = [&](auto rows) {
+        constexpr int ROWS = decltype(rows)::value;
+        for_each_joint_level([&]() {
+          float4 va = S::get_vel(j_at_a), vb = S::get_vel(j_at_b);
+          if constexpr (ROWS > 0) {
+            const float w = va.z - vb.z;
+            const float d = -(w + j_angb) * j_angm;
+            bool on = j_ang;
+            if constexpr (ROWS == 2) {
               const bool restoring = (j_exc > 0.f) ? (w < 0.f) : (w > 0.f);   // A.4.3: not while already coming back
-              const float d = -(w + j_angb) * j_angm;
-              const bool on = j_ang || (j_lim && !restoring);
-              va.z = on ? va.z + j_iia * d : va.z;
-              vb.z = on ? vb.z - j_iib * d : vb.z;
-              j_acca = j_ang ? j_acca + d : j_acca;                           // (limits are never accumulated)
+              on = j_ang || (j_lim && !restoring);
             }
-            float cx, cy;   // A.4.1: point constraint, 2x2 solve
-            S::rel_vel(va, j_rax, j_ray, vb, j_rbx, j_rby, cx, cy);
-            float rx = -(cx + j_bx), ry = -(cy + j_by);
-            float jx = (j_k22 * rx - j_k12 * ry) * j_idet, jy = (j_k11 * ry - j_k12 * rx) * j_idet;
-            apply_impulse(va, j_ima, j_iia, jx, jy, j_rax, j_ray);
-            apply_impulse(vb, j_imb, j_iib, -jx, -jy, j_rbx, j_rby);
-            j_accx = j_accx + jx; j_accy = j_accy + jy;
-            S::vel4(E, jsa) = va;
-            S::vel4(E, jsb) = vb;
+            const float wa = va.z + j_iia * d, wb = vb.z - j_iib * d, acc = j_acca + d;
+            va.z = on ? wa : va.z;
+            vb.z = on ? wb : vb.z;
+            j_acca = j_ang ? acc : j_acca;                                    // (limits are never accumulated)
+          }
+          float cx, cy;   // A.4.1: point constraint, 2x2 solve
+          S::rel_vel(va, j_rax, j_ray, vb, j_rbx, j_rby, cx, cy);
+          float rx = -(cx + j_bx), ry = -(cy + j_by);
+          float jx = (j_k22 * rx - j_k12 * ry) * j_idet, jy = (j_k11 * ry - j_k12 * rx) * j_idet;
+          apply_impulse(va, j_ima, j_iia, jx, jy, j_rax, j_ray);
+          apply_impulse(vb, j_imb, j_iib, -jx, -jy, j_rbx, j_rby);
+          j_accx = j_accx + jx; j_accy = j_accy + jy;
+          S::put_vel(j_to_a, va);
+          S::put_vel(j_to_b, vb);
+        });
+      };
+      auto sweep_joints = [&](auto rows) {
+        visit_joints(rows);
+        K2D_T(kT_SweepJoints);
+      };
+      using I0 = std::integral_constant<int, 0>;
+      using I3 = std::integral_constant<int, 3>;
+      if constexpr (BATCHED) {
+        // A.8: the points of batch b are solved from the velocities the batch starts with, and their impulses are
+        // applied in the order of their places in the batch.  Points of a batch that share no movable shape neither
+        // see nor disturb each other: each is solved and applied by its lane at once, one LDS round trip.  Only a
+        // batch in which two points meet at a movable shape stages its impulses by place; lane s then applies to
+        // shape s, in place order, those that touch it.
+        const int n_b = prm.n_batches;
+        const int oa_bj = oa.have ? S::batch_places(oa.rc.ab, n_b) : 0, ob_bj = ob.have ? S::batch_places(ob.rc.ab, n_b) : 0;
+        // batch of the two slots of the lane's pairs, -1 = none
+        const int a0 = oa.have ? oa_bj & 0xff : -1, a1 = (oa.rc.ab & kTwo) ? (oa_bj >> 16) & 0xff : -1;
+        const int b0 = ob.have ? ob_bj & 0xff : -1, b1 = (ob.rc.ab & kTwo) ? (ob_bj >> 16) & 0xff : -1;
+        // which batches hold points at all, and which of those stage their impulses (where there are more batches than the
+        // table has room for, each holds a point or a few, and all are staged)
+        unsigned long long used = ~0ull, staged = ~0ull;
+        const bool told = n_b <= K::SEEN && !any_listed;
+        if (told) {
+          unsigned* seen = reinterpret_cast<unsigned*>(E + K::X_SEEN);   // shapes met in a batch; bit 16: two points meet
+          for (int i = k; i < n_b; i += G) seen[i] = 0u;
+          wave_sync();
+          auto note = [&](int b, int pa, int pb) {
+            if (b < 0) return;
+            const unsigned m = ((1u << pa) | (1u << pb)) & ~static_mask;
+            const unsigned old = atomicOr(seen + b, m | (1u << 17));
+            if (old & m) atomicOr(seen + b, 1u << 16);
+          };
+          note(a0, oa.pa, oa.pb);
+          note(a1, oa.pa, oa.pb);
+          if constexpr (K::TWO) {
+            note(b0, ob.pa, ob.pb);
+            note(b1, ob.pa, ob.pb);
           }
           wave_sync();
+          used = 0ull; staged = 0ull;
+          for (int i0 = 0; i0 < n_b; i0 += G) {
+            const unsigned w = i0 + k < n_b ? seen[i0 + k] : 0u;
+            const unsigned long long u = __ballot((w >> 17) & 1u), st = __ballot((w >> 16) & 1u);
+#pragma unroll
+            for (int e = 0; e < K::EPW; ++e) {
+              constexpr unsigned long long mask = G == 64 ? ~0ull : (1ull << (G & 63)) - 1ull;
+              used |= ((u >> (e * G)) & mask) << i0;
+              staged |= ((st >> (e * G)) & mask) << i0;
+            }
+          }
         }
-        K2D_T(kT_SweepJoints);
-        if constexpr (BATCHED) {
-          // A.8: the points of batch b are solved from the velocities the batch starts with, their impulses
-          // staged by their place in the batch; then lane s applies to shape s, in place order, the
-          // impulses of the points that touch it (so every body sees them in point order).
+        for (int it = 0; it < prm.n_iters; ++it) {
+          sweep_joints(I2{});
           for (int b = 0; b < n_b; ++b) {
+            if (told) {   // (on to the next batch that holds points)
+              const unsigned long long rest = used >> b;
+              if (rest == 0ull) break;
+              b += __builtin_ctzll(rest);
+            }
+            if (told && !((staged >> b) & 1ull)) {
+              auto direct = [&](Own& o, int s0, int s1) {
+                const bool hit1 = s1 == b;
+                if (s0 == b || hit1) {
+                  float4 va = S::get_vel(o.at_a), vb = S::get_vel(o.at_b);
+                  float jx, jy, fx, fy, rax, ray, rbx, rby;
+                  S::point_impulses(o.rc, hit1, o.ima, o.iia, o.imb, o.iib, va, vb, jx, jy, fx, fy, rax, ray, rbx, rby);
+                  S::put_vel(o.to_a, va);
+                  S::put_vel(o.to_b, vb);
+                }
+              };
+              direct(oa, a0, a1);
+              if constexpr (K::TWO) {
+                if (any_b) direct(ob, b0, b1);
+              }
+              wave_sync();
+              continue;
+            }
             unsigned pm = 0u;   // places of the batch taken by this lane's points
             auto stage_point = [&](int j, int ab, float jx, float jy, float fx, float fy, float rax, float ray,
                                    float rbx, float rby) {
@@ -1379,19 +1518,18 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
               reinterpret_cast<int*>(p)[8] = ab & 0xffff;
               pm |= 1u << j;
             };
-            auto own_points = [&](Own& o, int bj) {
-              const bool hit0 = o.have && (bj & 0xff) == b;
-              const bool hit1 = (o.rc.ab & kTwo) && ((bj >> 16) & 0xff) == b;
-              if (hit0 || hit1) {
+            auto own_points = [&](Own& o, int bj, int s0, int s1) {
+              const bool hit1 = s1 == b;
+              if (s0 == b || hit1) {
+                float4 va = S::get_vel(o.at_a), vb = S::get_vel(o.at_b);
                 float jx, jy, fx, fy, rax, ray, rbx, rby;
-                S::point_impulses(o.rc, hit1, o.ima, o.iia, o.imb, o.iib, S::vel4(E, o.pa), S::vel4(E, o.pb), jx, jy, fx,
-                                  fy, rax, ray, rbx, rby);
+                S::point_impulses(o.rc, hit1, o.ima, o.iia, o.imb, o.iib, va, vb, jx, jy, fx, fy, rax, ray, rbx, rby);
                 stage_point((bj >> (hit1 ? 24 : 8)) & 0xff, o.rc.ab, jx, jy, fx, fy, rax, ray, rbx, rby);
               }
             };
-            own_points(oa, oa_bj);
+            own_points(oa, oa_bj, a0, a1);
             if constexpr (K::TWO) {
-              if (any_b) own_points(ob, ob_bj);
+              if (any_b) own_points(ob, ob_bj, b0, b1);
             }
             if constexpr (K::LISTED > 0) {
               if (any_listed) {
@@ -1404,9 +1542,9 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
                   if (hit0 || hit1) {
                     const int a = rc.ab & 0xff, bb = (rc.ab >> 8) & 0xff;
                     const float4 qa = S::prop4(E, a), qb = S::prop4(E, bb);
+                    float4 va = S::vel4(E, a), vb = S::vel4(E, bb);
                     float jx, jy, fx, fy, rax, ray, rbx, rby;
-                    S::point_impulses(rc, hit1, qa.x, qa.y, qb.x, qb.y, S::vel4(E, a), S::vel4(E, bb), jx, jy, fx, fy, rax,
-                                      ray, rbx, rby);
+                    S::point_impulses(rc, hit1, qa.x, qa.y, qb.x, qb.y, va, vb, jx, jy, fx, fy, rax, ray, rbx, rby);
                     stage_point((bj >> (hit1 ? 24 : 8)) & 0xff, rc.ab, jx, jy, fx, fy, rax, ray, rbx, rby);
                     if (hit1) { rp[15 + 8] = rc.lam_n[1]; rp[15 + 9] = rc.lam_t[1]; }
                     else { rp[5 + 8] = rc.lam_n[0]; rp[5 + 9] = rc.lam_t[0]; }
@@ -1446,8 +1584,48 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
               wave_sync();
             }
           }
-        } else
-          for_each_level([&](Own& o) { S::template visit_own<false>(E, o); },
+          K2D_T(kT_SweepPairs);
+        }
+      } else if (!any_b && !any_listed && angular_rows < 2) {
+        // The common case -- one pair per lane, all in registers, no joint limits -- as straight code for no, one, two, and
+        // three or more levels: a visit is 52 vector instructions per manifold point, and the branches of a loop over
+        // levels cost as much as half a point each.
+        const int n_lv = scalar(wave_clevels);
+        auto sweeps = [&](auto levels, auto rows) {
+          constexpr int NL = decltype(levels)::value;
+          for (int it = prm.n_iters; it > 0; --it) {
+            sweep_joints(rows);
+            if constexpr (NL > 0) {
+              if (at0) S::template visit_own<false>(oa);
+              wave_sync();
+            }
+            if constexpr (NL > 1) {
+              if (at1) S::template visit_own<false>(oa);
+              wave_sync();
+            }
+            if constexpr (NL > 2) {
+              if (at2) S::template visit_own<false>(oa);
+              wave_sync();
+              for (int lv = 3, n = opaque(n_lv); lv < n; ++lv) {
+                if (oa.lv == lv) S::template visit_own<false>(oa);
+                wave_sync();
+              }
+            }
+            K2D_T(kT_SweepPairs);
+          }
+        };
+        auto sweeps_of = [&](auto rows) {
+          if (n_lv == 0) sweeps(I0{}, rows);
+          else if (n_lv == 1) sweeps(I1{}, rows);
+          else if (n_lv == 2) sweeps(I2{}, rows);
+          else sweeps(I3{}, rows);
+        };
+        if (angular_rows == 0) sweeps_of(I0{});
+        else sweeps_of(I1{});
+      } else {
+        for (int it = 0; it < prm.n_iters; ++it) {
+          sweep_joints(I2{});
+          for_each_level([&](Own& o) { S::template visit_own<false>(o); },
                          [&](int q) {
                            // (the two branches keep LDS and HBM accesses apart: a merged pointer would turn
                            // every access into a slow flat one)
@@ -1466,7 +1644,8 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
                              for (int z = 0; z < 2; ++z) { rp[5 + 10 * z + 8] = rc.lam_n[z]; rp[5 + 10 * z + 9] = rc.lam_t[z]; }
                            }
                          });
-        K2D_T(kT_SweepPairs);
+          K2D_T(kT_SweepPairs);
+        }
       }
 
       // ---- Euler step of position and rotation (Alg. 1) ----
@@ -1501,7 +1680,13 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
         correct(a, b, ((static_mask >> a) & 1u) ? N : a, ((static_mask >> b) & 1u) ? N : b, S::prop4(E, a).x,
                 S::prop4(E, b).x, nx, ny, corr);
       };
-      for_each_level([&](Own& o) { correct(o.pa, o.pb, o.sa, o.sb, o.ima, o.imb, o.rc.nx, o.rc.ny, o.rc.corr); },
+      for_each_level([&](Own& o) {
+                       const float ca = o.ima * o.rc.corr, cb = o.imb * o.rc.corr;
+                       const vec2 p = *(PosPtr)o.at_a;
+                       *(PosPtr)o.to_a = vec2{p.x - ca * o.rc.nx, p.y - ca * o.rc.ny};
+                       const vec2 q = *(PosPtr)o.at_b;
+                       *(PosPtr)o.to_b = vec2{add_ordered(cb * o.rc.nx, q.x), add_ordered(cb * o.rc.ny, q.y)};
+                     },
                      [&](int q) {
                        if (q < K::POOL) {
                          LdsCF rp = to_lds(pool + q * kRecW);
@@ -1524,19 +1709,16 @@ __global__ void __launch_bounds__(64, K::EPW == 8 ? 1 : 2)
       }
       if (any_listed) hbm_sync();
       K2D_T(kT_CorrectPairs);
-      for (int lv = 0; lv < wave_levels; ++lv) {
-        if (k < J && j_live && j_level == lv) {
-          const float4 fa = S::pos4(E, ja), fb = S::pos4(E, jb);
-          const float xax = add_ordered(fmaf(fa.z, j_aax, -(fa.w * j_aay)), fa.x);
-          const float xay = add_ordered(fmaf(fa.w, j_aax, fa.z * j_aay), fa.y);
-          const float xbx = add_ordered(fmaf(fb.z, j_abx, -(fb.w * j_aby)), fb.x);
-          const float xby = add_ordered(fmaf(fb.w, j_abx, fb.z * j_aby), fb.y);
-          float cx = j_cf * (xax - xbx), cy = j_cf * (xay - xby);
-          *reinterpret_cast<float2*>(E + K::X_POS + 4 * jsa) = make_float2(fa.x - j_ima * cx, fa.y - j_ima * cy);
-          *reinterpret_cast<float2*>(E + K::X_POS + 4 * jsb) = make_float2(add_ordered(j_imb * cx, fb.x), add_ordered(j_imb * cy, fb.y));
-        }
-        wave_sync();
-      }
+      for_each_joint_level([&]() {
+        const float4 fa = S::pos4(E, ja), fb = S::pos4(E, jb);
+        const float xax = add_ordered(fmaf(fa.z, j_aax, -(fa.w * j_aay)), fa.x);
+        const float xay = add_ordered(fmaf(fa.w, j_aax, fa.z * j_aay), fa.y);
+        const float xbx = add_ordered(fmaf(fb.z, j_abx, -(fb.w * j_aby)), fb.x);
+        const float xby = add_ordered(fmaf(fb.w, j_abx, fb.z * j_aby), fb.y);
+        float cx = j_cf * (xax - xbx), cy = j_cf * (xay - xby);
+        *(PosPtr)j_to_a = vec2{fa.x - j_ima * cx, fa.y - j_ima * cy};
+        *(PosPtr)j_to_b = vec2{add_ordered(j_imb * cx, fb.x), add_ordered(j_imb * cy, fb.y)};
+      });
       K2D_T(kT_CorrectJoints);
     }
     if (RESET) {   // new episodes (wave-uniform branch: the wavefront leaves the step loop together)
