@@ -128,8 +128,8 @@ int k2d_alloc_batch(const k2d_caps* caps, const k2d_params* params, int n_envs, 
 /* How the step kernel maps environments onto the 64 lanes of a wavefront: `lanes` = 16 (four environments
  * per wavefront), 8 (eight per wavefront: half the instructions per environment, twice the on-chip memory
  * per wavefront), or 0 = chosen per launch (the default: 64 lanes, a wavefront per environment, for batches of
- * up to 2048 environments, 32 lanes up to 4096, 8 lanes for Small environments in batches of more than 8192,
- * 16 otherwise).  The mapping changes no result (the pairs of a level of
+ * up to 2048 environments, 32 lanes up to 4096, 8 lanes for Small environments in batches of more than 8192
+ * and Medium ones in batches of more than 8704, 16 otherwise).  The mapping changes no result (the pairs of a level of
  * the sweep touch disjoint movable shapes, A.8, whichever lanes hold them).  With 8 lanes the batched
  * schedule takes batch sizes up to 16 (the paper's).  K2D_E_ARG otherwise. */
 int k2d_set_lanes_per_env(k2d_batch* batch, int lanes);

@@ -511,8 +511,6 @@ unsigned long long* g_phase_clocks = nullptr;   // caller-owned device buffer, k
 long g_phase_waves = 0;
 bool g_phase_keep_order = false;                // launches take the environments as they are numbered
 #endif
-// environments beyond which the 8-lane mapping is chosen: what the 16-lane mapping keeps resident at once
-constexpr int kResidentEnvs16 = 256 * 8 * 4;
 // wavefronts of the step kernel that are resident at once: two on every SIMD (registers and LDS allow no more)
 constexpr int kWaveSlots = 256 * 8;
 
@@ -569,13 +567,15 @@ static Params device_params(const k2d_params& p) {
 // Lanes per environment where the batch does not say: as many as leave no environment waiting for a wavefront slot
 // (measured on MI355X, 64 steps, ms with 64 / 32 / 16 / 8 lanes: Large 2048 environments 2.72 / 2.99 / 3.29 / 3.93,
 // 4096: 5.07 / 2.88 / 3.29 / 4.15, 8192: 8.52 / 4.75 / 3.16 / 4.14; Medium 1024: 1.26 / 1.62 / 1.76 / 2.07; Small
-// 256: 0.46 / 0.48 / 0.61 / 0.66, 8192: 1.73 / 1.05 / 0.69 / 0.74).  Beyond what 16 lanes keep resident Small
-// environments take 8 lanes (16384: 1.27 with 16, 0.78 with 8); Medium and Large ones stay at 16, since their
-// 8-lane images leave room for one wavefront per SIMD, whose dependent instructions have nothing to overlap with.
+// 256: 0.46 / 0.48 / 0.61 / 0.66, 8192: 1.73 / 1.05 / 0.69 / 0.74).  Beyond what 16 lanes keep resident Small and
+// Medium environments take 8 lanes (16 / 8 lanes: Small 8193: 0.75 / 0.68, 65536: 4.40 / 2.71; Medium 8193: 1.52 /
+// 1.91, 10000: 2.36 / 2.12, 65536: 10.0 / 6.5); Large ones stay at 16 (32768: 8.7 / 11.1), since eight of their
+// images leave room for one wavefront per SIMD, whose dependent instructions have nothing to overlap with.
 static int lanes_for(int cls, int n_envs, int batch_size) {
   if (n_envs <= kWaveSlots) return 64;
   if (n_envs <= 2 * kWaveSlots) return 32;
-  return (cls == 0 && n_envs > kResidentEnvs16 && batch_size <= 16) ? 8 : 16;
+  const int most16 = 4 * kWaveSlots + (cls == 1 ? kWaveSlots / 4 : 0);
+  return (cls < 2 && n_envs > most16 && batch_size <= 16) ? 8 : 16;
 }
 
 static int step_launch(k2d_batch* b, const float* actions_dev, int n_envs, int n_steps, const float* lv, int n_levels,

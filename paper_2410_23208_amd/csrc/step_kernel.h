@@ -79,10 +79,10 @@ struct Cfg {
   static constexpr int STAGE_N = NREG < BATCH_MOST ? BATCH_MOST : NREG;
   static constexpr int X_STAGE = X_LAM + 4 * NREG;
   static constexpr int X_POOL = X_STAGE + STAGE_N * kManW;
-  // LDS budget of one environment: a CU's 160 KiB shared by eight wavefronts (four of those with eight
-  // environments).  The stride is an odd multiple of G words, so that the same word of different environments
+  // LDS budget of one environment: a CU's 160 KiB shared by eight wavefronts (four, where eight environments with
+  // their images would not fit otherwise).  The stride is an odd multiple of G words, so that the same word of different environments
   // falls into different banks.
-  static constexpr int MAX_STRIDE = (G == 8 ? 159 : 79) * G;
+  static constexpr int MAX_STRIDE = (X_POOL > 79 * G ? 159 : 79) * G;
   static constexpr int POOL_WANT = LISTED < 8 ? LISTED : 8;
   static constexpr int POOL_FIT = MAX_STRIDE > X_POOL ? (MAX_STRIDE - X_POOL) / kRecW : 0;
   static constexpr int POOL = POOL_WANT < POOL_FIT ? POOL_WANT : POOL_FIT;
