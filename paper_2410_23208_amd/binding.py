@@ -234,6 +234,9 @@ class Batch:
         nbytes = state_bytes(self.caps, self.n_envs)
         if nbytes == 0:
             raise ValueError("unsupported capacities %r" % (self.caps,))
+        self._index = torch.cuda.current_device() if self.device.index is None else self.device.index
+        self._raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+            lambda index: torch.cuda.current_stream(index).cuda_stream)
         self.state = torch.zeros(nbytes // 4, dtype=torch.float32, device=self.device)
         self._h = ctypes.c_void_p()
         c, p = make_caps(self.caps), make_params(params)
@@ -250,7 +253,8 @@ class Batch:
             self._h = None
 
     def _stream(self):
-        return self.torch.cuda.current_stream(self.device).cuda_stream
+        # (torch.cuda.current_stream wraps the same handle in a Stream object: 3.3 us a call against 0.1)
+        return self._raw_stream(self._index)
 
     def reset(self, scene_words, env_ids=None):
         """scene_words: host uint32 [n, scene_words] (pack_scenes) or a device int32/float32 tensor."""

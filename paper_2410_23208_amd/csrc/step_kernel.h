@@ -727,153 +727,196 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
   // ---- episode set-up ----
   if (fresh) {
     const bool first = src == Rg;
-    auto word = [&](int w) { return env_ok ? src[w] : 0.f; };   // (padding environments: everything inactive)
-    unsigned act_bits = 0u, static_bits = 0u, tri_bits = 0u;
-    sh_act = 0u; sh_fall = 0u;
+    // Everything is read before anything is looked at: one round trip to memory, not one for every kind of entity.
+    // (A lane without an entity reads its neighbour's; padding environments have everything inactive.)
+    auto word = [&](int w) { return src[w]; };
+    float s_px[NS], s_py[NS], s_th[NS], s_vx[NS], s_vy[NS], s_w[NS], s_im[NS], s_ii[NS], s_fr[NS], s_re[NS];
+    int s_fl[NS], s_nv[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const int i = min(k + s * G, N - 1);
+      s_px[s] = word(L.pos_x + i); s_py[s] = word(L.pos_y + i); s_th[s] = word(L.theta + i);
+      s_vx[s] = word(L.vel_x + i); s_vy[s] = word(L.vel_y + i); s_w[s] = word(L.omega + i);
+      s_im[s] = word(L.inv_mass + i); s_ii[s] = word(L.inv_inertia + i);
+      s_fr[s] = word(L.friction + i); s_re[s] = word(L.restitution + i);
+      s_fl[s] = f2i(word(L.shape_flags + i));
+      s_nv[s] = f2i(word(i < P ? L.n_verts + i : L.radius + (i - P)));   // vertices of a polygon, radius of a circle
+    }
+    float v0x[QT], v0y[QT];
+#pragma unroll
+    for (int q = 0; q < QT; ++q) {
+      const int p = min(q * (G / 4) + k / 4, P - 1), v = k & 3;
+      lx[q] = word(L.verts + (2 * v) * P + p); ly[q] = word(L.verts + (2 * v + 1) * P + p);
+      v0x[q] = word(L.verts + p); v0y[q] = word(L.verts + P + p);
+    }
+    const int jk = min(k, J - 1), tk = min(k, T - 1);
+    const int j_fl = f2i(word(L.joint_flags + jk)), j_a = f2i(word(L.joint_a + jk)), j_b = f2i(word(L.joint_b + jk));
+    j_aax = word(L.anchor_a_x + jk); j_aay = word(L.anchor_a_y + jk);
+    j_abx = word(L.anchor_b_x + jk); j_aby = word(L.anchor_b_y + jk);
+    j_thf = word(L.theta_f + jk); j_speed = word(L.motor_speed + jk); j_power = word(L.motor_power + jk);
+    j_lo = word(L.limit_lo + jk); j_hi = word(L.limit_hi + jk);
+    j_accx = word(L.acc_x + jk); j_accy = word(L.acc_y + jk); j_acca = word(L.acc_ang + jk);
+    const int t_fl = f2i(word(L.thr_flags + tk)), t_b = f2i(word(L.thr_body + tk));
+    t_px = word(L.thr_pos_x + tk); t_py = word(L.thr_pos_y + tk); t_power = word(L.thr_power + tk);
+    const float t_angle = word(L.thr_angle + tk);
+    constexpr int PSW = (K::NP + 3) / 4, PSL = (PSW + G - 1) / G;
+    unsigned ps_words[PSL];
+#pragma unroll
+    for (int i = 0; i < PSL; ++i)
+      ps_words[i] = first ? reinterpret_cast<const unsigned*>(Rg + L.pair_state)[min(k + i * G, PSW - 1)] : 0u;
+    unsigned* ps_copy = reinterpret_cast<unsigned*>(E + K::X_STAGE);
+#pragma unroll
+    for (int i = 0; i < PSL; ++i)
+      if (k + i * G < PSW) ps_copy[k + i * G] = ps_words[i];
+
+    unsigned act_bits = 0u, pos_bits = 0u;
+    bool odd_mass = false;   // a mass that is neither zero nor positive
+    sh_act = 0u; sh_fall = 0u; static_mask = 0u; tri_mask = 0u;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       const int i = k + s * G;
-      bool act = false, fixed = true, tri = false;
+      const bool in = env_ok && i < N, act = in && (s_fl[s] & 1);
+      const bool fixed = !act || (s_im[s] == 0.f && s_ii[s] == 0.f);
+      if (act) sh_act |= 1u << s;
+      if (act && s_im[s] > 0.f) sh_fall |= 1u << s;
+      odd_mass |= act && !(s_im[s] >= 0.f);
+      float sn, cs;
+      k2d_sincos(s_th[s], sn, cs);
       if (i < N) {
-        const float im = word(L.inv_mass + i), ii = word(L.inv_inertia + i), th = word(L.theta + i);
-        act = f2i(word(L.shape_flags + i)) & 1;
-        fixed = !act || (im == 0.f && ii == 0.f);
-        if (act) sh_act |= 1u << s;
-        if (act && im > 0.f) sh_fall |= 1u << s;
-        float sn, cs;
-        k2d_sincos(th, sn, cs);
-        S::pos4(E, i) = make_float4(word(L.pos_x + i), word(L.pos_y + i), cs, sn);
-        S::vel4(E, i) = make_float4(word(L.vel_x + i), word(L.vel_y + i), word(L.omega + i), th);
-        S::prop4(E, i) = make_float4(im, ii, word(L.friction + i), word(L.restitution + i));
+        S::pos4(E, i) = make_float4(s_px[s], s_py[s], cs, sn);
+        S::vel4(E, i) = make_float4(s_vx[s], s_vy[s], s_w[s], s_th[s]);
+        S::prop4(E, i) = make_float4(s_im[s], s_ii[s], s_fr[s], s_re[s]);
         E[K::X_JOINED + i] = i2f(0);
-        if (i < P) tri = f2i(word(L.n_verts + i)) == 3;
-        else { c_radius[s] = word(L.radius + (i - P)); E[K::X_RAD + (i - P)] = c_radius[s]; }
+        if (i >= P) { c_radius[s] = i2f(s_nv[s]); E[K::X_RAD + (i - P)] = c_radius[s]; }
       }
-      act_bits |= (unsigned)group_bits(__ballot(act)) << (s * G < 32 ? s * G : 0);
-      static_bits |= (unsigned)group_bits(__ballot(fixed)) << (s * G < 32 ? s * G : 0);
-      tri_bits |= (unsigned)group_bits(__ballot(tri)) << (s * G < 32 ? s * G : 0);
+      auto bits = [&](bool b) { return (unsigned)group_bits(__ballot(b)) << (s * G < 32 ? s * G : 0); };
+      act_bits |= bits(act);
+      static_mask |= bits(fixed);
+      tri_mask |= bits(i < P && s_nv[s] == 3);
+      pos_bits |= bits(act && s_im[s] > 0.f);
     }
-    static_mask = static_bits;
-    tri_mask = tri_bits;
 #pragma unroll
-    for (int q = 0; q < QT; ++q) {
-      const int p = q * (G / 4) + k / 4, v = k & 3;
-      if (p < P) {
-        const int vv = (v == 3 && ((tri_bits >> p) & 1u)) ? 0 : v;   // a triangle's spare slot repeats vertex 0: the manifold
-        lx[q] = word(L.verts + (2 * vv) * P + p);                    // code can then run over four vertices
-        ly[q] = word(L.verts + (2 * vv + 1) * P + p);
-      }
+    for (int q = 0; q < QT; ++q) {   // a triangle's spare slot repeats vertex 0: the manifold code can then run over four vertices
+      const int p = q * (G / 4) + k / 4;
+      const bool spare = (k & 3) == 3 && ((tri_mask >> (p & 31)) & 1u);
+      lx[q] = spare ? v0x[q] : lx[q];
+      ly[q] = spare ? v0y[q] : ly[q];
     }
-    // joints: lane j of the group owns joint j for the whole episode
-    j_live = false;
-    ja = 0; jb = 0;
     wave_sync();
-    if (k < J) {
-      const int fl = f2i(word(L.joint_flags + k));
-      ja = f2i(word(L.joint_a + k));
-      jb = f2i(word(L.joint_b + k));
-      const bool idx_ok = ja >= 0 && ja < N && jb >= 0 && jb < N && ja != jb;
-      if (!idx_ok) { ja = 0; jb = 0; }
+    // joints: lane j of the group owns joint j for the whole episode
+    {
+      const bool idx_ok = j_a >= 0 && j_a < N && j_b >= 0 && j_b < N && j_a != j_b;
+      ja = idx_ok ? j_a : 0;
+      jb = idx_ok ? j_b : 0;
       const float4 qa = S::prop4(E, ja), qb = S::prop4(E, jb);
       j_ima = qa.x; j_iia = qa.y; j_imb = qb.x; j_iib = qb.y;
-      j_fixed = (fl >> 1) & 1;
-      j_motor = (fl >> 2) & 1;
-      j_limited = ((fl >> 4) & 1) && !j_fixed;
-      j_live = (fl & 1) && idx_ok && ((act_bits >> ja) & 1u) && ((act_bits >> jb) & 1u) && (j_ima + j_imb) > 0.f;
-      j_aax = word(L.anchor_a_x + k); j_aay = word(L.anchor_a_y + k);
-      j_abx = word(L.anchor_b_x + k); j_aby = word(L.anchor_b_y + k);
-      j_thf = word(L.theta_f + k); j_speed = word(L.motor_speed + k); j_power = word(L.motor_power + k);
-      j_lo = word(L.limit_lo + k); j_hi = word(L.limit_hi + k);
-      j_accx = j_accy = j_acca = 0.f;
-      if (first) {
-        j_accx = word(L.acc_x + k); j_accy = word(L.acc_y + k); j_acca = word(L.acc_ang + k);
-        if (!j_live) { j_accx = 0.f; j_accy = 0.f; j_acca = 0.f; }
-        if (!j_fixed) j_acca = 0.f;
-      }
+      j_fixed = (j_fl >> 1) & 1;
+      j_motor = (j_fl >> 2) & 1;
+      j_limited = ((j_fl >> 4) & 1) && !j_fixed;
+      j_live = env_ok && k < J && (j_fl & 1) && idx_ok && ((act_bits >> ja) & 1u) && ((act_bits >> jb) & 1u) && (j_ima + j_imb) > 0.f;
+      if (!first || !j_live) { j_accx = 0.f; j_accy = 0.f; j_acca = 0.f; }
+      if (!j_fixed) j_acca = 0.f;
       const float is = j_iia + j_iib;
       j_angm = (is > 0.f) ? 1.f / is : 0.f;
       j_cf = prm.joint_beta / (j_ima + j_imb);
+      ja_fix = (static_mask >> ja) & 1u;
+      jb_fix = (static_mask >> jb) & 1u;
       if (j_live) {   // A.4: joined shapes do not collide
         atomicOr(reinterpret_cast<unsigned*>(E + K::X_JOINED + ja), 1u << jb);
         atomicOr(reinterpret_cast<unsigned*>(E + K::X_JOINED + jb), 1u << ja);
       }
-      E[K::X_JINFO + k] = i2f(ja | (jb << 8) | (j_live ? 1 << 16 : 0));
-    }
-    ja_fix = (static_mask >> ja) & 1u;
-    jb_fix = (static_mask >> jb) & 1u;
-    wave_sync();
-    // dependency levels of the joints: a joint runs one level after the last earlier joint that shares a
-    // movable shape with it, so joints sharing a shape keep their index order, the others run side by side
-    j_level = 0; n_levels = 0;
-    {
-      unsigned long long last = 0ull;   // 4 bits per shape: next free level
+      // dependency levels of the joints: a joint runs one level after the last earlier joint that shares a
+      // movable shape with it, so joints sharing a shape keep their index order, the others run side by side
+      const unsigned shapes = j_live ? ((1u << ja) | (1u << jb)) & ~static_mask : 0u;
+      if (k < J) reinterpret_cast<unsigned*>(E + K::X_JINFO)[k] = shapes;
+      wave_sync();
+      unsigned wait = 0u, placed = 0u;
 #pragma unroll
-      for (int q = 0; q < J; ++q) {
-        const int info = f2i(E[K::X_JINFO + q]);
-        if (info & (1 << 16)) {
-          const int a = info & 255, b = (info >> 8) & 255;
-          const bool da = !((static_mask >> a) & 1u), db = !((static_mask >> b) & 1u);
-          const int la = da ? (int)((last >> (4 * a)) & 15ull) : 0, lb = db ? (int)((last >> (4 * b)) & 15ull) : 0;
-          const int lv = max(la, lb);
-          if (q == k) j_level = lv;
-          n_levels = max(n_levels, lv + 1);
-          if (da) last = (last & ~(15ull << (4 * a))) | ((unsigned long long)(lv + 1) << (4 * a));
-          if (db) last = (last & ~(15ull << (4 * b))) | ((unsigned long long)(lv + 1) << (4 * b));
+      for (int q = 0; q < J; ++q)
+        if (q < k && (reinterpret_cast<const unsigned*>(E + K::X_JINFO)[q] & shapes)) wait |= 1u << q;
+      j_level = -1;
+      n_levels = 0;
+      for (int lv = 0; lv < J; ++lv) {   // (the earliest joint without a level gets one every time)
+        const bool now = j_live && j_level < 0 && (wait & ~placed) == 0u;
+        if (now) j_level = lv;
+        const unsigned bits = (unsigned)group_bits(__ballot(now));
+        placed |= bits;
+        if (bits) n_levels = lv + 1;
+      }
+      // a row per shape: the shapes it can collide with (both active, not joined, not both of infinite mass)
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const int i = k + s * G;
+        if (i < N) {
+          unsigned row = ((act_bits >> i) & 1u) ? act_bits & ~(unsigned)f2i(E[K::X_JOINED + i]) & ~(1u << i) : 0u;
+          if (!((pos_bits >> i) & 1u)) row &= pos_bits;
+          E[K::X_JOINED + i] = i2f((int)row);
         }
       }
+      wave_sync();
     }
     // thrusters: lane t of the group owns thruster t
-    t_live = false;
-    if (k < T) {
-      const int fl = f2i(word(L.thr_flags + k));
-      t_body = f2i(word(L.thr_body + k));
-      const bool idx_ok = t_body >= 0 && t_body < N;
-      if (!idx_ok) t_body = 0;
-      t_live = (fl & 1) && idx_ok && ((act_bits >> t_body) & 1u);
-      t_px = word(L.thr_pos_x + k); t_py = word(L.thr_pos_y + k);
-      k2d_sincos(word(L.thr_angle + k), t_dy, t_dx);
-      t_power = word(L.thr_power + k);
+    {
+      const bool idx_ok = t_b >= 0 && t_b < N;
+      t_body = idx_ok ? t_b : 0;
+      t_live = env_ok && k < T && (t_fl & 1) && idx_ok && ((act_bits >> t_body) & 1u);
+      k2d_sincos(t_angle, t_dy, t_dx);
       const float4 q = S::prop4(E, t_body);
       t_im = q.x; t_ii = q.y;
     }
-    // The eligible pairs (both shapes active, not joined, not both of infinite mass) are listed in tournament
-    // order and dealt over the lanes: a pair that can never collide costs the cull nothing.
+    // The eligible pairs are listed in tournament order and dealt over the lanes: a pair that can never collide
+    // costs the cull nothing.
     {
       unsigned char* list = reinterpret_cast<unsigned char*>(E + K::X_ELIG);
+      constexpr int CHUNKS = (R * K::PPR + G - 1) / G;
+      const bool exact = __any(odd_mass);   // (masses that are not numbers or negative: the sum itself decides)
+      unsigned ab_of[(CHUNKS + 3) / 4];
+      unsigned ok_bits = 0u;
+#pragma unroll
+      for (int c = 0; c < (CHUNKS + 3) / 4; ++c) ab_of[c] = 0u;
+#pragma unroll
+      for (int c = 0; c < CHUNKS; ++c) {
+        const int q = c * G + k;
+        int a, b;
+        const bool real = S::sched_pair(q / K::PPR, q % K::PPR, a, b) && q < R * K::PPR;
+        a = real ? a : 0;
+        b = real ? b : 1;
+        bool ok = real && ((f2i(E[K::X_JOINED + a]) >> b) & 1);
+        if (exact) ok = ok && (S::prop4(E, a).x + S::prop4(E, b).x) > 0.f;
+        if (ok) ok_bits |= 1u << c;
+        ab_of[c >> 2] |= (unsigned)(a | (b << 4)) << (8 * (c & 3));
+      }
       n_elig = 0;
-      for (int q0 = 0; q0 < R * K::PPR; q0 += G) {
-        const int q = q0 + k;
-        int a = 0, b = 0;
-        bool ok = q < R * K::PPR && S::sched_pair(q / K::PPR, q % K::PPR, a, b);
-        if (ok) {
-          ok = ((act_bits >> a) & 1u) && ((act_bits >> b) & 1u) && !((f2i(E[K::X_JOINED + a]) >> b) & 1) &&
-               (S::prop4(E, a).x + S::prop4(E, b).x) > 0.f;
-        }
+#pragma unroll
+      for (int c = 0; c < CHUNKS; ++c) {
+        const bool ok = (ok_bits >> c) & 1u;
         const Bits bits = group_bits(__ballot(ok));
-        if (ok) list[n_elig + popc(bits & below)] = (unsigned char)(a | (b << 4));
+        if (ok) list[n_elig + popc(bits & below)] = (unsigned char)(ab_of[c >> 2] >> (8 * (c & 3)));
         n_elig += popc(bits);
       }
       wave_sync();
       elig = 0u; pp_mask = 0u; pc_mask = 0u;
 #pragma unroll
       for (int i = 0; i < (ET + 3) / 4; ++i) my_ab[i] = 0u;
+      const unsigned char* ps_of = reinterpret_cast<const unsigned char*>(ps_copy);
+      unsigned ps_mine[TSP / 4];
 #pragma unroll
       for (int t = 0; t < TSP; ++t) {
-        unsigned char ps = 0;
+        if ((t & 3) == 0) ps_mine[t >> 2] = 0u;
         const int e = t * G + k;
-        if (t < ET && e < n_elig) {
-          const int ab = list[e], a = ab & 15, b = ab >> 4;
-          my_ab[t >> 2] |= (unsigned)ab << (8 * (t & 3));
-          elig |= 1u << t;
-          if (b < P) pp_mask |= 1u << t;
-          else if (a < P) pc_mask |= 1u << t;
-          if (first) {
-            ps = reinterpret_cast<const unsigned char*>(Rg + L.pair_state)[S::pair_index(a, b)] & 3;
-            if (ps) ps |= kInRecord << 2;
-          }
+        if (t < ET) {
+          const bool mine = e < n_elig;
+          const int ab = mine ? list[e] : 0x10, a = ab & 15, b = ab >> 4;
+          const unsigned ps = mine ? ps_of[S::pair_index(a, b)] & 3u : 0u;
+          my_ab[t >> 2] |= mine ? (unsigned)ab << (8 * (t & 3)) : 0u;
+          elig |= mine ? 1u << t : 0u;
+          pp_mask |= mine && b < P ? 1u << t : 0u;
+          pc_mask |= mine && b >= P && a < P ? 1u << t : 0u;
+          ps_mine[t >> 2] |= (ps ? ps | (kInRecord << 2) : 0u) << (8 * (t & 3));
         }
-        pst[k * TSP + t] = ps;
       }
+#pragma unroll
+      for (int i = 0; i < TSP / 4; ++i) reinterpret_cast<unsigned*>(pst)[k * (TSP / 4) + i] = ps_mine[i];
     }
     held_a = -1; held_b = -1;
     fresh = false;
