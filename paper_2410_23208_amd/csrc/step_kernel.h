@@ -167,6 +167,18 @@ __device__ __forceinline__ float add_ordered(float a, float b) {
   asm("v_add_f32_e32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
   return d;
 }
+// Minimum and maximum as the bare instruction: operands that come from a neighbouring lane would first be quieted (an
+// instruction each) in case they are signalling NaNs, which no result of an fp32 operation is.
+__device__ __forceinline__ float min_raw(float a, float b) {
+  float d;
+  asm("v_min_f32_e32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+__device__ __forceinline__ float max_raw(float a, float b) {
+  float d;
+  asm("v_max_f32_e32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
 // an impulse (jx, jy) at offset (rx, ry) from the centre of mass (A.2); v = (vx, vy, omega, -)
 __device__ __forceinline__ void apply_impulse(float4& v, float im, float ii, float jx, float jy, float rx, float ry) {
   v.x = fmaf(im, jx, v.x);
@@ -357,7 +369,7 @@ struct Step {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         float s = dot2(xn[i].x, xn[i].y, yw[k].x - xw[i].x, yw[k].y - xw[i].y);
-        smin = (s < smin) ? s : smin;
+        smin = fminf(s, smin);
       }
       if ((f0 + i < 3 || !tri_x) && smin > best) { best = smin; idx = f0 + i; }
     }
@@ -689,6 +701,12 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
   unsigned char* sched = reinterpret_cast<unsigned char*>(E + K::X_SCHED);
   float4* lam_store = reinterpret_cast<float4*>(E + K::X_LAM);
   const float h = prm.h;
+  // the lane's polygon q; where a class has fewer polygons than the lanes could take, the last one is worked out (and stored)
+  // several times over
+  auto polygon_of = [&](int q) {
+    const int p = q * (G / 4) + k / 4;
+    return QT * (G / 4) == P ? p : min(p, P - 1);
+  };
 
 #ifdef K2D_PHASE_TIMERS
   long long t_acc[kT_Count] = {};
@@ -745,7 +763,7 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
     float v0x[QT], v0y[QT];
 #pragma unroll
     for (int q = 0; q < QT; ++q) {
-      const int p = min(q * (G / 4) + k / 4, P - 1), v = k & 3;
+      const int p = polygon_of(q), v = k & 3;
       lx[q] = word(L.verts + (2 * v) * P + p); ly[q] = word(L.verts + (2 * v + 1) * P + p);
       v0x[q] = word(L.verts + p); v0y[q] = word(L.verts + P + p);
     }
@@ -797,8 +815,7 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
     }
 #pragma unroll
     for (int q = 0; q < QT; ++q) {   // a triangle's spare slot repeats vertex 0: the manifold code can then run over four vertices
-      const int p = q * (G / 4) + k / 4;
-      const bool spare = (k & 3) == 3 && ((tri_mask >> (p & 31)) & 1u);
+      const bool spare = (k & 3) == 3 && ((tri_mask >> polygon_of(q)) & 1u);
       lx[q] = spare ? v0x[q] : lx[q];
       ly[q] = spare ? v0y[q] : ly[q];
     }
@@ -924,7 +941,7 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
   wave_sync();
   // levels and list lengths are per environment; the wavefront walks as many as its largest one has
   const int wave_levels = scalar(wave_max(n_levels)), cull_trips = scalar((wave_max(n_elig) + G - 1) / G);
-  const bool any_motor = __any(j_live && j_motor && !j_fixed);
+  const int any_motor = scalar(__any(j_live && j_motor && !j_fixed));
   // which angular rows the wavefront's joints have: none, those of fixed joints, those of limited ones too
   const int angular_rows = scalar(__any(j_live && j_limited) ? 2 : __any(j_live && j_fixed) ? 1 : 0);
   // the joints level by level: the lanes of a level as a mask that is there already when the level comes up
@@ -998,22 +1015,36 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
         }
       }
       // ---- world-frame polygons: four neighbouring lanes share one, each has a vertex and the edge behind it ----
+      // (all of a lane's polygons side by side, with no branch in between: one after the other, the chain from the vertex
+      // to the normal of each -- a root and two divisions -- waited for itself: 2717 -> 2381 clocks, three polygons a lane)
+      {
+        float wx[QT], wy[QT], ex[QT], ey[QT];
 #pragma unroll
-      for (int q = 0; q < QT; ++q) {
-        const int p = q * (G / 4) + k / 4, v = k & 3;
-        if (p < P) {
-          const float4 f = S::pos4(E, p);   // x, y, cos, sin
-          const float wx = f.x + fmaf(f.z, lx[q], -(f.w * ly[q]));
-          const float wy = f.y + fmaf(f.w, lx[q], f.z * ly[q]);
-          const float ex = K2D_DPPF(wx, kQuadNext) - wx, ey = K2D_DPPF(wy, kQuadNext) - wy;
-          const float len = sqrtf(dot2(ex, ey, ex, ey));
-          S::wv(E, v, p) = make_float2(wx, wy);
-          S::wn(E, v, p) = make_float2(ey / len, -ex / len);
-          float x0 = fminf(wx, K2D_DPPF(wx, kQuadXor1)), x1 = fmaxf(wx, K2D_DPPF(wx, kQuadXor1));
-          float y0 = fminf(wy, K2D_DPPF(wy, kQuadXor1)), y1 = fmaxf(wy, K2D_DPPF(wy, kQuadXor1));
-          x0 = fminf(x0, K2D_DPPF(x0, kQuadXor2)); x1 = fmaxf(x1, K2D_DPPF(x1, kQuadXor2));
-          y0 = fminf(y0, K2D_DPPF(y0, kQuadXor2)); y1 = fmaxf(y1, K2D_DPPF(y1, kQuadXor2));
-          if (v == 0) S::box4(E, p) = make_float4(x0 - kCullMargin, y0 - kCullMargin, x1 + kCullMargin, y1 + kCullMargin);
+        for (int q = 0; q < QT; ++q) {
+          const float4 f = S::pos4(E, polygon_of(q));   // x, y, cos, sin
+          wx[q] = f.x + fmaf(f.z, lx[q], -(f.w * ly[q]));
+          wy[q] = f.y + fmaf(f.w, lx[q], f.z * ly[q]);
+          ex[q] = K2D_DPPF(wx[q], kQuadNext) - wx[q];
+          ey[q] = K2D_DPPF(wy[q], kQuadNext) - wy[q];
+        }
+        float4 box[QT];
+#pragma unroll
+        for (int q = 0; q < QT; ++q) {
+          const int p = polygon_of(q), v = k & 3;
+          const float len = sqrtf(dot2(ex[q], ey[q], ex[q], ey[q]));
+          S::wv(E, v, p) = make_float2(wx[q], wy[q]);
+          S::wn(E, v, p) = make_float2(ey[q] / len, -ex[q] / len);
+          const float nx = K2D_DPPF(wx[q], kQuadXor1), ny = K2D_DPPF(wy[q], kQuadXor1);
+          box[q] = make_float4(min_raw(wx[q], nx), min_raw(wy[q], ny), max_raw(wx[q], nx), max_raw(wy[q], ny));
+          box[q].x = min_raw(box[q].x, K2D_DPPF(box[q].x, kQuadXor2));
+          box[q].y = min_raw(box[q].y, K2D_DPPF(box[q].y, kQuadXor2));
+          box[q].z = max_raw(box[q].z, K2D_DPPF(box[q].z, kQuadXor2));
+          box[q].w = max_raw(box[q].w, K2D_DPPF(box[q].w, kQuadXor2));
+        }
+        if ((k & 3) == 0) {
+#pragma unroll
+          for (int q = 0; q < QT; ++q)
+            S::box4(E, polygon_of(q)) = make_float4(box[q].x - kCullMargin, box[q].y - kCullMargin, box[q].z + kCullMargin, box[q].w + kCullMargin);
         }
       }
       wave_sync();
@@ -1059,11 +1090,13 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
       K2D_T(kT_JointConstants);
       wave_sync();
       if (any_motor) {
+        // (a joint without a motor impulse changes nothing: w - 0 and w + -0 are w, whatever w is)
         const bool turns = motor != 0.f;
+        const float da = turns ? j_iia * motor : 0.f, db = turns ? j_iib * motor : -0.f;
         for_each_joint_level([&]() {
           const float wa = ((LdsF)(j_at_a + S::kVel))[2], wb = ((LdsF)(j_at_b + S::kVel))[2];
-          ((LdsF)(j_to_a + S::kVel))[2] = turns ? wa - j_iia * motor : wa;
-          ((LdsF)(j_to_b + S::kVel))[2] = turns ? wb + j_iib * motor : wb;
+          ((LdsF)(j_to_a + S::kVel))[2] = wa - da;
+          ((LdsF)(j_to_b + S::kVel))[2] = wb + db;
         });
       }
       auto push = [&]() {
@@ -1093,12 +1126,23 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
       //    registers for the rest of the substep (pairs beyond two per lane become records in LDS / HBM).
       unsigned cand = 0u;
       bool set_changed = false;   // a pair of this lane collides now and did not one substep ago, or the reverse
+      // (four pairs at a time and all of both boxes: one round trip to LDS, and no branch on a comparison.  This phase with
+      // the list, clocks a wavefront and substep: Large 2591 -> 1595, piles 3472 -> 2226.)
 #pragma unroll
-      for (int t = 0; t < ET; ++t)
-        if (t < cull_trips) {
-          const unsigned ab = my_ab[t >> 2] >> (8 * (t & 3));
-          const float4 ba = S::box4(E, ab & 15), bb = S::box4(E, (ab >> 4) & 15);
-          if (ba.x <= bb.z && bb.x <= ba.z && ba.y <= bb.w && bb.y <= ba.w) cand |= 1u << t;
+      for (int t0 = 0; t0 < ET; t0 += 4)
+        if (t0 == 0 || t0 < cull_trips) {
+          float4 ba[4], bb[4];
+#pragma unroll
+          for (int t = t0; t < t0 + 4 && t < ET; ++t) {
+            const unsigned ab = my_ab[t0 >> 2] >> (8 * (t & 3));
+            ba[t - t0] = S::box4(E, ab & 15); bb[t - t0] = S::box4(E, (ab >> 4) & 15);
+          }
+#pragma unroll
+          for (int t = t0; t < t0 + 4 && t < ET; ++t) {
+            const float4 a = ba[t - t0], b = bb[t - t0];
+            const bool meet = (a.x <= b.z) & (b.x <= a.z) & (a.y <= b.w) & (b.y <= a.w);
+            cand |= meet ? 1u << t : 0u;
+          }
         }
       cand &= elig;
       {   // pairs that were colliding and are not even candidates now: their points are no longer active
