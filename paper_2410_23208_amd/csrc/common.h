@@ -154,10 +154,10 @@ struct StepLaunch {
 K2D_HIDDEN int launch_step_small(const StepLaunch&);
 K2D_HIDDEN int launch_step_medium(const StepLaunch&);
 K2D_HIDDEN int launch_step_large(const StepLaunch&);
-// Orders the environments of a launch (k2d.hip): order[slot] = environment, keys behind it.
-K2D_HIDDEN bool order_environments(const float* state, int32_t* order, int n_envs, int n_waves, int envs_per_wave,
-                                   int envs_per_line, int rec_words, const k2d_layout& layout, int n_joints,
-                                   hipStream_t stream);
+// Orders the environments of a launch (k2d.hip): order[slot] = environment, keys behind it.  1 << wave_shift
+// environments share a wavefront, the action rows of 1 << line_shift neighbours a 128-byte line.
+K2D_HIDDEN bool order_environments(const float* state, int32_t* order, int n_envs, int n_waves, int wave_shift, int line_shift,
+                                   int rec_words, const k2d_layout& layout, hipStream_t stream);
 
 // Words of one environment record in HBM: the state words, then room for the pair records that neither
 // registers nor LDS hold (sized for the lane mapping that holds fewest, so that every mapping of a class

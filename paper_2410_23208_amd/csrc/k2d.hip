@@ -357,35 +357,57 @@ __global__ void k2d_contacts_kernel(const float* state, uint8_t* pair_count, uin
 // the depth of the joints' dependency levels), busiest first, so that a wavefront steps similar ones instead
 // of paying for the most pairs, the most shapes and the deepest joint chain of a random few.  The result of
 // the step does not depend on the ordering.
-// Two kernels: the keys (one lane per environment), then a counting sort over the key values in one workgroup.
+// Two kernels: the keys (one lane per environment), then a counting sort over the key values.  Both are bound by
+// latency.  The keys' loads depend on nothing, so they are all in flight at once (lengths are known at compile time).
 constexpr int kOrderKeys = 1024;
-__global__ void k2d_order_keys_kernel(const float* state, int32_t* keys, int n_envs, int rec_words, k2d_layout L,
-                                      int n_joints) {
-  const int env = blockIdx.x * blockDim.x + threadIdx.x;
+template <int P, int C, int J, int T>
+__global__ void __launch_bounds__(64) k2d_order_keys_kernel(const float* state, int32_t* keys, int n_envs, int rec_words) {
+  constexpr k2d_layout L = make_layout(P, C, J, T);
+  constexpr int N = P + C, PSW = (L.n_pairs + 3) / 4;
+  const int env = blockIdx.x * 64 + threadIdx.x;
   if (env >= n_envs) return;
   const float* S = state + (size_t)env * rec_words;
-  const unsigned* ps = reinterpret_cast<const unsigned*>(S + L.pair_state);
-  const int N = L.n_shapes;
-  int pairs = 0, movable = 0;
-  for (int w = 0; w < (L.n_pairs + 3) / 4; ++w) {   // four pair-state bytes per word (the padding bytes are zero)
-    const unsigned v = ps[w] & 0x03030303u;
-    pairs += ((v & 0xffu) != 0) + ((v & 0xff00u) != 0) + ((v & 0xff0000u) != 0) + ((v & 0xff000000u) != 0);
-  }
-  unsigned active = 0u, moves = 0u;
+  unsigned ps[PSW];
+  int fl[N], ja[J], jb[J], jf[J];
+  float im[N], ii[N];
+#pragma unroll
+  for (int w = 0; w < PSW; ++w) ps[w] = reinterpret_cast<const unsigned*>(S + L.pair_state)[w];
+#pragma unroll
   for (int i = 0; i < N; ++i) {
-    const bool on = __float_as_int(S[L.shape_flags + i]) & 1;
-    const bool mv = on && (S[L.inv_mass + i] != 0.f || S[L.inv_inertia + i] != 0.f);
+    fl[i] = __float_as_int(S[L.shape_flags + i]);
+    im[i] = S[L.inv_mass + i];
+    ii[i] = S[L.inv_inertia + i];
+  }
+#pragma unroll
+  for (int q = 0; q < J; ++q) {
+    ja[q] = __float_as_int(S[L.joint_a + q]);
+    jb[q] = __float_as_int(S[L.joint_b + q]);
+    jf[q] = __float_as_int(S[L.joint_flags + q]);
+  }
+  int pairs = 0, movable = 0;
+#pragma unroll
+  for (int w = 0; w < PSW; ++w) {   // four pair-state bytes per word (the padding bytes are zero)
+    const unsigned v = ps[w] & 0x03030303u;
+    pairs += __popc((v | (v >> 1)) & 0x01010101u);
+  }
+  unsigned active = 0u, moves = 0u, has_mass = 0u;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const bool on = fl[i] & 1;
+    const bool mv = on && (im[i] != 0.f || ii[i] != 0.f);
     active |= (unsigned)on << i;
     moves |= (unsigned)mv << i;
+    has_mass |= (unsigned)(im[i] > 0.f) << i;
     movable += mv;
   }
   // joints that share a movable shape run one after the other (the step kernel's rule): depth of that chain
   unsigned long long next = 0ull;   // 4 bits per shape
   int depth = 0;
-  for (int q = 0; q < n_joints; ++q) {
-    const int a = __float_as_int(S[L.joint_a + q]), b = __float_as_int(S[L.joint_b + q]);
-    if (!(__float_as_int(S[L.joint_flags + q]) & 1) || a < 0 || a >= N || b < 0 || b >= N || a == b) continue;
-    if (!((active >> a) & (active >> b) & 1u) || !(S[L.inv_mass + a] + S[L.inv_mass + b] > 0.f)) continue;
+#pragma unroll
+  for (int q = 0; q < J; ++q) {
+    const int a = ja[q], b = jb[q];
+    if (!(jf[q] & 1) || a < 0 || a >= N || b < 0 || b >= N || a == b) continue;
+    if (!((active >> a) & (active >> b) & 1u) || !(((has_mass >> a) | (has_mass >> b)) & 1u)) continue;
     const bool da = (moves >> a) & 1u, db = (moves >> b) & 1u;
     const int lv = max(da ? (int)((next >> (4 * a)) & 15ull) : 0, db ? (int)((next >> (4 * b)) & 15ull) : 0);
     if (da) next = (next & ~(15ull << (4 * a))) | ((unsigned long long)(lv + 1) << (4 * a));
@@ -395,72 +417,105 @@ __global__ void k2d_order_keys_kernel(const float* state, int32_t* keys, int n_e
   static_assert(14 * 68 + 16 * 4 + 3 < kOrderKeys, "key range");
   keys[env] = kOrderKeys - 1 - (min(pairs, 14) * 68 + min(movable, 16) * 4 + min(depth, 3));   // busiest first
 }
-// The counting sort.  Slots are handed out in key order (slot s belongs to wavefront s / envs_per_wave), so the
+// The counting sort.  Slots are handed out in key order (slot s belongs to wavefront s >> wave_shift), so the
 // environments of a wavefront have the same or neighbouring keys.  Inside a key the environments are free to
 // trade places, and that freedom is used for the L2: wavefront w of the step kernel runs on XCD w % 8
 // (workgroups go to the eight XCDs in turn) and every XCD has an L2 of its own, so the environments whose action
-// rows share a 128-byte line (`envs_per_line` neighbours; class c = (env / envs_per_line) % 8) look for a slot
+// rows share a 128-byte line (1 << line_shift neighbours; class c = (env >> line_shift) % 8) look for a slot
 // on XCD c among the slots of their key: the line that one of them fetches is then in the L2 that the others
 // ask.  The environments of a key that find the slots of their class taken (the classes of a key are not equally
 // large) take what the other classes of the key leave free.
-constexpr int kOrderClasses = 8;
-__global__ void __launch_bounds__(1024) k2d_order_kernel(int32_t* keys, int32_t* order, int n_envs, int n_waves,
-                                                         int envs_per_wave, int envs_per_line) {
-  __shared__ int count[kOrderKeys * kOrderClasses];   // histogram over (key, class); then ranks
-  __shared__ int part[1024];
-  const int t = threadIdx.x;
-  auto class_of = [&](int env) { return (env / envs_per_line) % kOrderClasses; };
-  for (int q = t; q < kOrderKeys * kOrderClasses; q += blockDim.x) count[q] = 0;
+// A workgroup places kOrderChunk environments.  It needs every bin's size and how many environments of its bins come
+// before its own; rather than hand a table from kernel to kernel it counts all keys itself -- one pass of LDS atomics,
+// with its own chunk between the ones before and the ones after it, so that the atomics of the chunk return the places
+// -- and only the placing is shared out.  (One workgroup that counted, drew ranks and placed all of them in turn, with a
+// division for every class and slot: 30 us for 8192 environments, 10 now; with the keys 48 -> 15 us.  65536 Small
+// ones: 64 us for both kernels, 76 us off the launch.)
+constexpr int kOrderClasses = 8, kOrderChunk = 2048, kOrderThreads = 1024;
+__global__ void __launch_bounds__(kOrderThreads) k2d_order_kernel(const int32_t* keys, int32_t* order, int n_envs, int n_waves,
+                                                                  int wave_shift, int line_shift) {
+  static_assert(kOrderKeys == kOrderThreads, "one thread per key");
+  __shared__ int count[kOrderClasses][kOrderKeys];   // size of a bin (class, key); then its first rank
+  __shared__ int part[kOrderThreads / 64];
+  constexpr int PER = kOrderChunk / kOrderThreads, AHEAD = 8;
+  const int t = threadIdx.x, chunk0 = blockIdx.x * kOrderChunk;
+  auto class_of = [&](int env) { return (env >> line_shift) % kOrderClasses; };
+#pragma unroll
+  for (int c = 0; c < kOrderClasses; ++c) count[c][t] = 0;
   __syncthreads();
-  for (int env = t; env < n_envs; env += blockDim.x) atomicAdd(&count[keys[env] * kOrderClasses + class_of(env)], 1);
-  __syncthreads();
-  // exclusive prefix sum over the bins: thread t owns the bins of key t
-  static_assert(kOrderKeys == 1024, "one thread per key");
-  int mine = 0;
-  for (int c = 0; c < kOrderClasses; ++c) mine += count[t * kOrderClasses + c];
-  part[t] = mine;
-  __syncthreads();
-  for (int d = 1; d < 1024; d <<= 1) {
-    const int v = t >= d ? part[t - d] : 0;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
-  }
-  int acc = part[t] - mine;
-  for (int c = 0; c < kOrderClasses; ++c) { const int n = count[t * kOrderClasses + c]; count[t * kOrderClasses + c] = acc; acc += n; }
-  for (int sl = t; sl < n_waves * envs_per_wave; sl += blockDim.x) order[sl] = -1;
-  __syncthreads();
-  // every environment draws its rank (key-major, class-minor); the rank is kept beside the key
-  for (int env = t; env < n_envs; env += blockDim.x) {
-    const int key = keys[env];
-    const int r = atomicAdd(&count[key * kOrderClasses + class_of(env)], 1);
-    keys[env] = key | (r << 10);
-  }
-  __syncthreads();
-  // now count[x] is the first rank of bin x + 1: the bins' boundaries can be read off again
-  auto first_rank = [&](int x) { return x > 0 ? count[x - 1] : 0; };
-  const int wave_slots = envs_per_wave, period = kOrderClasses * envs_per_wave;
-  // slots below s that lie on XCD c, and the j-th slot of XCD c
-  auto slots_before = [&](int c, int s) {
-    const int full = s / period, rem = s % period;
-    return full * wave_slots + min(max(rem - c * wave_slots, 0), wave_slots);
+  auto count_range = [&](int from, int to) {
+    for (int base = from; base < to; base += AHEAD * kOrderThreads) {
+      int key[AHEAD];
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) key[u] = keys[min(base + u * kOrderThreads + t, n_envs - 1)];
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) {
+        const int env = base + u * kOrderThreads + t;
+        if (env < to) atomicAdd(&count[class_of(env)][key[u]], 1);
+      }
+    }
   };
-  auto slot_of = [&](int c, int j) { return ((j / wave_slots) * kOrderClasses + c) * wave_slots + j % wave_slots; };
-  for (int env = t; env < n_envs; env += blockDim.x) {
-    const int key = keys[env] & 1023, r = keys[env] >> 10, c = class_of(env);
-    const int r0 = first_rank(key * kOrderClasses), r1 = count[key * kOrderClasses + kOrderClasses - 1];   // the key's slots
-    const int i = r - first_rank(key * kOrderClasses + c);                                               // place within (key, class)
+  int key[PER], place[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) key[u] = keys[min(chunk0 + u * kOrderThreads + t, n_envs - 1)];
+  count_range(0, chunk0);
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int env = chunk0 + u * kOrderThreads + t;
+    place[u] = env < n_envs ? atomicAdd(&count[class_of(env)][key[u]], 1) : 0;
+  }
+  __syncthreads();
+  count_range(chunk0 + kOrderChunk, n_envs);
+  __syncthreads();
+  // exclusive prefix sum over the bins, key-major: thread t owns the bins of key t
+  int size[kOrderClasses], mine = 0;
+#pragma unroll
+  for (int c = 0; c < kOrderClasses; ++c) { size[c] = count[c][t]; mine += size[c]; }
+  int sum = mine;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int v = __shfl_up(sum, d, 64);
+    sum += (t & 63) >= d ? v : 0;
+  }
+  if ((t & 63) == 63) part[t >> 6] = sum;
+  __syncthreads();
+  int first = sum - mine;
+#pragma unroll
+  for (int w = 0; w < kOrderThreads / 64; ++w) first += w < (t >> 6) ? part[w] : 0;
+#pragma unroll
+  for (int c = 0; c < kOrderClasses; ++c) { count[c][t] = first; first += size[c]; }
+  // (every slot below n_envs is some environment's; the ones behind are the last wavefront's spare ones)
+  const int spare = n_envs + t;
+  if (blockIdx.x == 0 && spare < (n_waves << wave_shift)) order[spare] = -1;
+  __syncthreads();
+  auto first_rank = [&](int key, int c) {
+    return c < kOrderClasses ? count[c][key] : key + 1 < kOrderKeys ? count[0][key + 1] : n_envs;
+  };
+  // slots below s that lie on XCD c, and the j-th slot of XCD c
+  const int wave_slots = 1 << wave_shift;
+  auto slots_before = [&](int c, int s) {
+    const int full = (s >> wave_shift) / kOrderClasses, rem = s - ((full * kOrderClasses) << wave_shift);
+    return (full << wave_shift) + min(max(rem - (c << wave_shift), 0), wave_slots);
+  };
+  auto slot_of = [&](int c, int j) { return ((((j >> wave_shift) * kOrderClasses) + c) << wave_shift) + (j & (wave_slots - 1)); };
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int env = chunk0 + u * kOrderThreads + t;
+    if (env >= n_envs) break;
+    const int q = key[u], c = class_of(env), i = place[u];
+    const int r0 = first_rank(q, 0), r1 = first_rank(q, kOrderClasses);   // the key's slots
     const int have = slots_before(c, r1) - slots_before(c, r0);
     if (i < have) {
       order[slot_of(c, slots_before(c, r0) + i)] = env;
     } else {   // the o-th environment of the key without a slot on its XCD takes the o-th slot the key has left
       int o = i - have;
       for (int c2 = 0; c2 < c; ++c2) {
-        const int n2 = count[key * kOrderClasses + c2] - first_rank(key * kOrderClasses + c2);
+        const int n2 = first_rank(q, c2 + 1) - first_rank(q, c2);
         o += max(0, n2 - (slots_before(c2, r1) - slots_before(c2, r0)));
       }
       for (int c2 = 0; c2 < kOrderClasses; ++c2) {
-        const int n2 = count[key * kOrderClasses + c2] - first_rank(key * kOrderClasses + c2);
+        const int n2 = first_rank(q, c2 + 1) - first_rank(q, c2);
         const int fre = max(0, (slots_before(c2, r1) - slots_before(c2, r0)) - n2);
         if (o < fre) { order[slot_of(c2, slots_before(c2, r0) + n2 + o)] = env; break; }
         o -= fre;
@@ -598,15 +653,22 @@ constexpr int kWaveSlots = 256 * 8;
 
 }  // namespace
 
-bool k2d_impl::order_environments(const float* state, int32_t* order, int n_envs, int n_waves, int envs_per_wave,
-                                  int envs_per_line, int rec_words, const k2d_layout& layout, int n_joints,
-                                  hipStream_t stream) {
-  int32_t* keys = order + n_waves * envs_per_wave;
+bool k2d_impl::order_environments(const float* state, int32_t* order, int n_envs, int n_waves, int wave_shift, int line_shift,
+                                  int rec_words, const k2d_layout& layout, hipStream_t stream) {
+  int32_t* keys = order + (n_waves << wave_shift);
   bool ok = true;
-  K2D_LAUNCH(ok, k2d_order_keys_kernel, dim3((n_envs + 255) / 256), dim3(256), 0, stream, state, keys, n_envs, rec_words,
-             layout, n_joints);
-  K2D_LAUNCH(ok, k2d_order_kernel, dim3(1), dim3(1024), 0, stream, keys, order, n_envs, n_waves, envs_per_wave,
-             envs_per_line);
+  const dim3 grid((n_envs + 63) / 64), block(64);
+  switch (layout.n_shapes) {   // (one capacity class each)
+#define K2D_ORDER_KEYS(P, C, J, T)                                                                                     \
+  case P + C: K2D_LAUNCH(ok, (k2d_order_keys_kernel<P, C, J, T>), grid, block, 0, stream, state, keys, n_envs, rec_words); break;
+    K2D_ORDER_KEYS(5, 2, 1, 1)
+    K2D_ORDER_KEYS(6, 3, 2, 2)
+    K2D_ORDER_KEYS(12, 4, 6, 2)
+#undef K2D_ORDER_KEYS
+    default: return false;
+  }
+  K2D_LAUNCH(ok, k2d_order_kernel, dim3((n_envs + kOrderChunk - 1) / kOrderChunk), dim3(kOrderThreads), 0, stream, keys, order,
+             n_envs, n_waves, wave_shift, line_shift);
   return ok;
 }
 
@@ -624,7 +686,7 @@ struct k2d_batch {
 
 // launches of fewer steps than this keep the identity ordering (the ordering pass would cost more than it could save)
 constexpr int kOrderMinSteps = 8;
-// the counting sort keeps an environment's rank in 21 bits beside its key
+// (every workgroup of the ordering reads all keys: larger batches keep the identity ordering too)
 constexpr int kOrderMaxEnvs = 1 << 21;
 static size_t records_bytes(int cls, int n_envs) {
   return ((size_t)n_envs * rec_words_of(cls) * sizeof(float) + 255) / 256 * 256;

@@ -1894,9 +1894,11 @@ int launch_step(const StepLaunch& s) {
   bool ok = true;
   int32_t* const order = K::EPW > 1 ? s.order : nullptr;   // (nothing to order where every environment has its own wavefront)
   if (order) {   // (a launch of a few steps is not worth the ordering pass)
-    // action rows that share a 128-byte line (rows of K::A floats; at least one environment per line)
-    const int envs_per_line = K::A > 0 && 32 / K::A > 0 ? 32 / K::A : 1;
-    ok = order_environments(s.state, order, s.n_envs, grid, K::EPW, envs_per_line, K::REC_WORDS, K::L, K::J, s.stream);
+    // environments whose action rows (K::A floats) lie in one 128-byte line, at least one: as a power of two
+    constexpr int line_shift = K::A <= 2 ? 4 : K::A <= 4 ? 3 : K::A <= 8 ? 2 : K::A <= 16 ? 1 : 0;
+    constexpr int wave_shift = K::EPW == 2 ? 1 : K::EPW == 4 ? 2 : 3;
+    static_assert(K::EPW == 1 || K::EPW == 1 << wave_shift, "environments of a wavefront");
+    ok = order_environments(s.state, order, s.n_envs, grid, wave_shift, line_shift, K::REC_WORDS, K::L, s.stream);
   }
 #ifdef K2D_PHASE_TIMERS
   K2D_LAUNCH(ok, (k2d_step_kernel<K, RESET, BATCHED>), dim3(grid), dim3(64), K::LDS_BYTES, s.stream, s.state, s.actions,

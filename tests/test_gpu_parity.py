@@ -738,3 +738,17 @@ def test_lane_mappings_at_their_edges(n, lanes, B, sweep_order):
     assert (os_["pair_count"] > 0).sum(1).max() > 62
     for k in parity.FLOAT_KEYS + parity.INT_KEYS:
         assert np.array_equal(gs[k], os_[k]), k
+
+
+@pytest.mark.parametrize("cfg,lanes", [(0, 8), (0, 16), (1, 8), (1, 16), (2, 0)])
+@pytest.mark.parametrize("n", [2047, 2048, 2049, 6145])
+def test_ordered_launch_over_several_workgroups(cfg, lanes, n):
+    """The ordering shares the environments out over workgroups of 2048: around the edge of one, and a ragged last
+    one of several.  The second launch is ordered by the pairs that collide then (many different keys)."""
+    caps, prm, sc = scenegen.make_scene(cfg, n_envs=n)
+    act = scenegen.make_actions(cfg, 32, n)
+    o = parity.run_oracle(caps, prm, sc, act)
+    b = parity.run_gpu(caps, prm, sc, act, chunk=16, lanes=lanes)
+    gs, os_ = b.state_dict(), o.state()
+    for k in parity.FLOAT_KEYS + parity.INT_KEYS:
+        assert np.array_equal(gs[k], os_[k]), k
