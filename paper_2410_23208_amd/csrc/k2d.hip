@@ -12,10 +12,9 @@
 //     synchronisation point a wavefront-scope fence and lets the hardware place wavefronts on CUs freely.
 //   * The whole scene of an environment lives in LDS for the entire launch (all steps, substeps and
 //     solver sweeps).  HBM is touched when the launch begins (one coalesced read of the record), once per
-//     step for the actions, when it ends -- and in between only for the accumulated impulses (A.7) of
-//     pairs that change lanes because the set of colliding pairs changed, for the pair records of piles
-//     deeper than registers and LDS hold, and for the new scenes of restarted episodes.  Lanes of a group
-//     exchange body velocities through LDS.
+//     step for the actions, when it ends -- and in between only for the pair records of piles deeper than
+//     registers and LDS hold and for the new scenes of restarted episodes.  Lanes of a group exchange body
+//     velocities through LDS.
 //   * The sweep order of the collision constraints (A.8 leaves it to the engine) is built from a
 //     round-robin tournament over the shapes, whose rounds touch disjoint shapes.  Walking the colliding
 //     pairs in that order, a pair is placed on a level that none of the earlier colliding pairs sharing a
@@ -28,8 +27,7 @@
 //   * Active manifolds of a substep become records that live in registers: lane k of the environment
 //     keeps active pairs k and G + k for the whole substep (warm start, all sweeps, corrections), so a
 //     visit costs one LDS round trip for the two bodies' velocities and nothing else; the accumulated
-//     impulses of pair k stay in the lane's registers from substep to substep while the set of colliding
-//     pairs is unchanged.  Pairs beyond 2G stay in a small LDS pool, the rare excess beyond that spills
+//     impulses wait in LDS from substep to substep.  Pairs beyond 2G stay in a small LDS pool, the rare excess beyond that spills
 //     to the environment's HBM record.
 //   * Joints are solved in index order per shape (A.8: sequential); joints that share no shape are
 //     independent, so they are grouped into dependency levels once per episode and lane j solves joint j.
@@ -429,29 +427,41 @@ __global__ void __launch_bounds__(64) k2d_order_keys_kernel(const float* state, 
 // before its own; rather than hand a table from kernel to kernel it counts all keys itself -- one pass of LDS atomics,
 // with its own chunk between the ones before and the ones after it, so that the atomics of the chunk return the places
 // -- and only the placing is shared out.  (One workgroup that counted, drew ranks and placed all of them in turn, with a
-// division for every class and slot: 30 us for 8192 environments, 10 now; with the keys 48 -> 15 us.  65536 Small
-// ones: 64 us for both kernels, 76 us off the launch.)
+// division for every class and slot: 30 us for 8192 environments, 11 now; with the keys 48 -> 16 us.  65536 Small
+// ones, all of one key when their episodes begin: 23 us, 57 with an atomic for every environment counted.)
 constexpr int kOrderClasses = 8, kOrderChunk = 2048, kOrderThreads = 1024;
 __global__ void __launch_bounds__(kOrderThreads) k2d_order_kernel(const int32_t* keys, int32_t* order, int n_envs, int n_waves,
                                                                   int wave_shift, int line_shift) {
   static_assert(kOrderKeys == kOrderThreads, "one thread per key");
   __shared__ int count[kOrderClasses][kOrderKeys];   // size of a bin (class, key); then its first rank
   __shared__ int part[kOrderThreads / 64];
-  constexpr int PER = kOrderChunk / kOrderThreads, AHEAD = 8;
+  constexpr int PER = kOrderChunk / kOrderThreads, AHEAD = 4;
   const int t = threadIdx.x, chunk0 = blockIdx.x * kOrderChunk;
   auto class_of = [&](int env) { return (env >> line_shift) % kOrderClasses; };
 #pragma unroll
   for (int c = 0; c < kOrderClasses; ++c) count[c][t] = 0;
   __syncthreads();
+  // (four neighbours a thread: their class is the same, and where their keys are too -- all scenes are alike when
+  // episodes begin -- one atomic counts them, with fewer lanes of a wavefront at one address)
   auto count_range = [&](int from, int to) {
-    for (int base = from; base < to; base += AHEAD * kOrderThreads) {
-      int key[AHEAD];
+    for (int base = from; base < to; base += 4 * AHEAD * kOrderThreads) {
+      int key[AHEAD][4];
 #pragma unroll
-      for (int u = 0; u < AHEAD; ++u) key[u] = keys[min(base + u * kOrderThreads + t, n_envs - 1)];
+      for (int u = 0; u < AHEAD; ++u)
+#pragma unroll
+        for (int z = 0; z < 4; ++z) {
+          const int env = base + 4 * (u * kOrderThreads + t) + z, k = keys[min(env, n_envs - 1)];
+          key[u][z] = env < to ? k : -1;
+        }
 #pragma unroll
       for (int u = 0; u < AHEAD; ++u) {
-        const int env = base + u * kOrderThreads + t;
-        if (env < to) atomicAdd(&count[class_of(env)][key[u]], 1);
+        const int (&k)[4] = key[u];
+        const int c = class_of(base + 4 * (u * kOrderThreads + t));
+        auto add = [&](bool first, int k0, int n) { if (first && k0 >= 0) atomicAdd(&count[c][k0], n); };
+        add(true, k[0], 1 + (k[1] == k[0]) + (k[2] == k[0]) + (k[3] == k[0]));
+        add(k[1] != k[0], k[1], 1 + (k[2] == k[1]) + (k[3] == k[1]));
+        add(k[2] != k[0] && k[2] != k[1], k[2], 1 + (k[3] == k[2]));
+        add(k[3] != k[0] && k[3] != k[1] && k[3] != k[2], k[3], 1);
       }
     }
   };

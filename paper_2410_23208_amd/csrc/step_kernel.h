@@ -1894,8 +1894,9 @@ int launch_step(const StepLaunch& s) {
   bool ok = true;
   int32_t* const order = K::EPW > 1 ? s.order : nullptr;   // (nothing to order where every environment has its own wavefront)
   if (order) {   // (a launch of a few steps is not worth the ordering pass)
-    // environments whose action rows (K::A floats) lie in one 128-byte line, at least one: as a power of two
-    constexpr int line_shift = K::A <= 2 ? 4 : K::A <= 4 ? 3 : K::A <= 8 ? 2 : K::A <= 16 ? 1 : 0;
+    // environments whose action rows (K::A floats) lie in one 128-byte line, as a power of two
+    static_assert(K::A <= 8, "the ordering counts four neighbours at once");
+    constexpr int line_shift = K::A <= 2 ? 4 : K::A <= 4 ? 3 : 2;
     constexpr int wave_shift = K::EPW == 2 ? 1 : K::EPW == 4 ? 2 : 3;
     static_assert(K::EPW == 1 || K::EPW == 1 << wave_shift, "environments of a wavefront");
     ok = order_environments(s.state, order, s.n_envs, grid, wave_shift, line_shift, K::REC_WORDS, K::L, s.stream);
