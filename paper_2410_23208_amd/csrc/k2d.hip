@@ -677,6 +677,7 @@ bool k2d_impl::order_environments(const float* state, int32_t* order, int n_envs
 #undef K2D_ORDER_KEYS
     default: return false;
   }
+  if (!ok) return false;   // (keys that nobody wrote must not become indices of the bins)
   K2D_LAUNCH(ok, k2d_order_kernel, dim3((n_envs + kOrderChunk - 1) / kOrderChunk), dim3(kOrderThreads), 0, stream, keys, order,
              n_envs, n_waves, wave_shift, line_shift);
   return ok;

@@ -1899,7 +1899,9 @@ int launch_step(const StepLaunch& s) {
     constexpr int line_shift = K::A <= 2 ? 4 : K::A <= 4 ? 3 : 2;
     constexpr int wave_shift = K::EPW == 2 ? 1 : K::EPW == 4 ? 2 : 3;
     static_assert(K::EPW == 1 || K::EPW == 1 << wave_shift, "environments of a wavefront");
-    ok = order_environments(s.state, order, s.n_envs, grid, wave_shift, line_shift, K::REC_WORDS, K::L, s.stream);
+    // (an ordering that did not start leaves entries that the step kernel must not take for records)
+    if (!order_environments(s.state, order, s.n_envs, grid, wave_shift, line_shift, K::REC_WORDS, K::L, s.stream))
+      return K2D_E_HIP;
   }
 #ifdef K2D_PHASE_TIMERS
   K2D_LAUNCH(ok, (k2d_step_kernel<K, RESET, BATCHED>), dim3(grid), dim3(64), K::LDS_BYTES, s.stream, s.state, s.actions,
