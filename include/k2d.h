@@ -224,7 +224,7 @@ int k2d_decode_actions(const k2d_caps* caps, const int32_t* discrete_dev, float*
  * environment ends with reward +1 if an active green shape is in active collision (a manifold point with
  * penetration > 0 at the last substep) with an active blue shape, else with reward -1 if it is with a red
  * shape; to this the dense term kappa * (d_t - d_{t+1}) is added, d = smallest centre distance over the
- * active (green, blue) pairs.  A shape's role is the integer in bits 8.. of its shape_flags.
+ * active (green, blue) pairs.  A shape's role is the (signed) integer in bits 8.. of its shape_flags.
  * dist_dev: float [n_envs], in: d_t (negative = no previous step, dense term 0), out: d_{t+1} (0 if the
  * environment has no green or no blue shape; the dense term is then 0 too);
  * reward_dev: float [n_envs]; done_dev: uint8 [n_envs] (1 = episode ended).  Device memory, caller-owned. */

@@ -542,7 +542,7 @@ __global__ void __launch_bounds__(kOrderThreads) k2d_order_kernel(const int32_t*
 __global__ void __launch_bounds__(64) k2d_outcome_kernel(const float* state, float* dist, float* reward,
                                                          uint8_t* done, int n_envs, int rec_words, k2d_layout L,
                                                          float kappa, int green, int blue, int red) {
-  __shared__ float4 shape[4][16];      // x, y, role
+  __shared__ float4 shape[4][16];      // x, y, role, active
   __shared__ unsigned pairs[4][32];    // pair-state bytes
   const int lane = threadIdx.x, i = lane & 15, g = lane >> 4;
   const int env = blockIdx.x * 4 + g;
@@ -555,19 +555,21 @@ __global__ void __launch_bounds__(64) k2d_outcome_kernel(const float* state, flo
   const float px = S[L.pos_x + is], py = S[L.pos_y + is];
   const unsigned w0 = ps_words[min(i, psw - 1)], w1 = ps_words[min(i + 16, psw - 1)];
   const float d_prev = dist[ok ? env : 0];
-  const int role = (ok && i < N && (fl & 1)) ? (fl >> 8) : -1;
-  shape[g][i] = make_float4(px, py, __int_as_float(role), 0.f);
+  // (any integer is a role, so being an active shape is kept apart from it: lanes i >= N and inactive shapes play none)
+  const bool on = ok && i < N && (fl & 1);
+  const int role = fl >> 8;
+  shape[g][i] = make_float4(px, py, __int_as_float(role), on ? 1.f : 0.f);
   if (i < psw) pairs[g][i] = w0;
   if (i + 16 < psw) pairs[g][i + 16] = w1;
   __syncthreads();
   const unsigned char* ps = reinterpret_cast<const unsigned char*>(pairs[g]);
   bool goal = false, bad = false;
   float best = INFINITY;
-  if (role == green) {
+  if (on && role == green) {
     for (int j = 0; j < N; ++j) {
       const float4 q = shape[g][j];
       const int rj = __float_as_int(q.z);
-      if (j != i && rj >= 0 && (rj == blue || rj == red)) {
+      if (j != i && q.w != 0.f && (rj == blue || rj == red)) {
         const int a = min(i, j), b = max(i, j);
         const bool touching = (ps[a * (2 * N - a - 1) / 2 + (b - a - 1)] & 3) != 0;
         if (rj == blue) {

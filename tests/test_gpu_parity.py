@@ -340,6 +340,37 @@ def test_reward_and_termination(cfg, n, steps):
     assert n_done > 0 and n_dense > n
 
 
+@pytest.mark.parametrize("cfg", [0, 1, 2])
+@pytest.mark.parametrize("green,blue,red", [(-1, 2, 3), (1, -1, 3), (-1, -2, -3), (77, 2, 3), (1, 2, 2)])
+def test_outcome_with_roles_that_no_shape_or_only_some_play(cfg, green, blue, red):
+    """Role parameters outside the roles of the scenes (-1 as "none"), roles below zero that shapes do carry, and one
+    integer for blue and red: only active shapes play, whatever integer is asked for.  Inactive shapes, and the lanes
+    of an environment that stand for no shape (9, 7 and 0 of 16), are nobody's green."""
+    import torch
+    import paper_2410_23208_amd as k2d
+    from oracle import k2d_env
+    n = 67
+    caps, prm, sc = scenegen.make_scene(cfg, n_envs=n)
+    N = caps[0] + caps[1]
+    rng = np.random.default_rng(7)
+    if (green, blue, red) == (-1, -2, -3):
+        sc["role"][:] = rng.integers(-3, 1, sc["role"].shape)
+    sc["active"][:, 1:][rng.random((n, N - 1)) < 0.2] = 0
+    act = scenegen.make_actions(cfg, 40, n)
+    o = parity.run_oracle(caps, prm, sc, act)
+    b = parity.run_gpu(caps, prm, sc, act)
+    d0 = rng.random(n).astype(np.float32)
+    d_gpu = torch.from_numpy(d0).cuda()
+    st = o.state()
+    r_ref, done_ref, d_ref = k2d_env.outcome(st["pos"].reshape(n, N, 2), sc["role"], sc["active"], st["pair_count"], d0, 0.25,
+                                             green, blue, red)
+    r, done = b.read_outcome(d_gpu, 0.25, green, blue, red)
+    assert np.array_equal(done.cpu().numpy(), done_ref)
+    assert np.array_equal(r.cpu().numpy(), r_ref)
+    assert np.array_equal(d_gpu.cpu().numpy(), d_ref)
+    assert (d_ref != 0).any() == ((green, blue, red) in ((-1, -2, -3), (1, 2, 2)))
+
+
 @pytest.mark.parametrize("cfg,n,steps", [(4, 131, 30), (1, 67, 20), (3, 67, 10)])
 def test_entity_observation_and_masks(cfg, n, steps):
     """k2d_read_entities against the numpy oracle built on the engine oracle's flat observation: exact."""
