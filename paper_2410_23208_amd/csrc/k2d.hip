@@ -122,11 +122,13 @@ __device__ __forceinline__ void copy_words(Word* dst, const Word* src, int n, in
     }
   }
 }
+// words of a record that the entity observation reads: scene words and pair states
+__host__ __device__ constexpr int entity_words_in(const k2d_layout& L) { return L.scene_words + (L.n_pairs + 3) / 4; }
 // the scene words of environments env0 .. env0 + ne - 1, and their pair states behind them, into LDS (stride `in`)
 __device__ __forceinline__ void load_records(float* lds, int in, const float* state, int env0, int ne, int rec_words,
                                              const k2d_layout& L, int t) {
   float v[kObsEnvs][2];
-  static_assert(2 * kObsThreads >= 512, "a record in two lines per wavefront");
+  static_assert(entity_words_in(make_layout(12, 4, 6, 2)) <= 2 * kObsThreads, "two words a thread hold the largest class's record");
 #pragma unroll
   for (int e = 0; e < kObsEnvs; ++e)
 #pragma unroll
@@ -208,8 +210,7 @@ struct EntityArrays {
   int32_t *joint_idx, *thruster_idx;
   uint32_t* masks;
 };
-// words an environment takes in LDS: scene words and pair states, then the arrays as they leave
-__host__ __device__ constexpr int entity_words_in(const k2d_layout& L) { return L.scene_words + (L.n_pairs + 3) / 4; }
+// words an environment takes in LDS behind the record's, for the arrays as they leave
 __host__ __device__ constexpr int entity_words_out(int N, int J, int T) { return 30 * N + 26 * J + 7 * T + 4 * N; }
 __global__ void __launch_bounds__(kObsThreads) k2d_entities_kernel(const float* state, EntityArrays to, int n_envs,
                                                                    int rec_words, k2d_layout L, int P, int C, int J, int T) {

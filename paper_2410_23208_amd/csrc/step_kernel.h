@@ -35,6 +35,7 @@ struct Cfg {
   static constexpr int NS = (N + G - 1) / G, QT = (4 * P + G - 1) / G, ET = (NP + G - 1) / G;
   static constexpr int TSP = ET <= 4 ? 4 : ET <= 8 ? 8 : 16;   // bytes of a lane's pair states
   static_assert(ET <= 16, "pair states of a lane");
+  static_assert(G * TSP <= 256, "a candidate's 16 bits: shapes in the low byte, the place of its state byte in the high one");
   // Active pairs are numbered 0, 1, ... as the narrowphase finds them.  Pairs below NREG live in
   // registers (lane k holds pairs k and G + k): the lane that found the manifold leaves it in an LDS
   // staging slot, the lane that keeps the pair derives the substep constants from it.  Pairs beyond them
