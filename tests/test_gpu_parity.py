@@ -16,6 +16,9 @@ from helpers import SceneBuilder, params as mkparams
 pytestmark = pytest.mark.gpu
 
 SMALL = {0: 67, 1: 131, 2: 259, 3: 131, 4: 195}     # several wavefronts and a ragged tail each
+# Lane mappings: lanes=0 (the library's choice) is a wavefront per environment up to 2048 environments, two environments
+# to a wavefront from TWO_EACH on (up to 4096); lanes=16 and 8 put four and eight environments into a wavefront.
+TWO_EACH = 2049
 
 
 def _both(cfg, n, steps, chunk=None):
@@ -96,7 +99,8 @@ def test_eight_lanes_dense_pile_and_pool_overflow():
 
 
 @pytest.mark.parametrize("cfg,n,steps,lanes", [(0, 67, 120, 0), (1, 131, 64, 0), (2, 259, 64, 0), (3, 131, 96, 0),
-                                               (4, 195, 64, 0), (3, 131, 48, 8), (0, 131, 64, 8)])
+                                               (4, 195, 64, 0), (3, 131, 48, 8), (0, 131, 64, 8), (3, 131, 96, 16),
+                                               (1, 131, 64, 16), (2, TWO_EACH, 48, 0)])
 def test_level_order_of_the_sweep_bit_identical(cfg, n, steps, lanes):
     """k2d_params.sweep_order = K2D_SWEEP_LEVELS (the colliding pairs visited level after level, each on the
     lowest level free at its movable shapes) against the oracle sweeping in the same order -- and the result
@@ -114,30 +118,33 @@ def test_level_order_of_the_sweep_bit_identical(cfg, n, steps, lanes):
         assert not np.array_equal(other["vel"], os_["vel"])
 
 
+@pytest.mark.parametrize("lanes", [0, 16, 8])
 @pytest.mark.parametrize("sweep_order", [0, 1])
-def test_stacking_workload_bit_identical(sweep_order):
+def test_stacking_workload_bit_identical(sweep_order, lanes):
     """Towers of up to nine boxes: chains of contacts, which the tournament order walks in as many dependent
     steps as a tower is high and the level order in three."""
     caps, prm, sc = scenegen.make_stack_scene(n_envs=131)
     prm = dict(prm, sweep_order=sweep_order)
     act = np.zeros((96, 131, caps[2] + caps[3]), dtype=np.float32)
     o = parity.run_oracle(caps, prm, sc, act)
-    b = parity.run_gpu(caps, prm, sc, act)
+    b = parity.run_gpu(caps, prm, sc, act, lanes=lanes)
     gs, os_ = b.state_dict(), o.state()
     for k in parity.FLOAT_KEYS + parity.INT_KEYS:
         assert np.array_equal(gs[k], os_[k]), k
     assert ((os_["pair_count"] > 0).sum(1) == 13).all()
 
 
+@pytest.mark.parametrize("lanes", [0, 16])
 @pytest.mark.parametrize("sweep_order", [0, 1])
-def test_dense_pile_workload_bit_identical(sweep_order):
-    """Workload 3's heap in a narrow pen: many environments keep more colliding pairs than one per lane, so the
-    second register-held pair of a lane is exercised over several wavefronts."""
+def test_dense_pile_workload_bit_identical(sweep_order, lanes):
+    """Workload 3's heap in a narrow pen: many environments keep more than 16 colliding pairs.  With 16 lanes that is
+    the second register-held pair of a lane, over several wavefronts; with a wavefront per environment every pair has
+    a lane of its own."""
     caps, prm, sc = scenegen.make_dense_scene(n_envs=195)
     prm = dict(prm, sweep_order=sweep_order)
     act = scenegen.make_actions(3, 96, 195)
     o = parity.run_oracle(caps, prm, sc, act)
-    b = parity.run_gpu(caps, prm, sc, act)
+    b = parity.run_gpu(caps, prm, sc, act, lanes=lanes)
     gs, os_ = b.state_dict(), o.state()
     for k in parity.FLOAT_KEYS + parity.INT_KEYS:
         assert np.array_equal(gs[k], os_[k]), k
@@ -147,29 +154,32 @@ def test_dense_pile_workload_bit_identical(sweep_order):
 
 @pytest.mark.parametrize("cfg,B,n,steps", [(0, 16, 67, 120), (0, 1, 67, 60), (0, 32, 131, 60), (1, 16, 131, 64),
                                            (1, 5, 67, 48), (2, 16, 259, 64), (2, 1, 131, 32), (2, 32, 131, 48),
-                                           (3, 16, 131, 64), (3, 7, 67, 48), (4, 16, 195, 48)])
-def test_batched_schedule_bit_identical(cfg, B, n, steps):
+                                           (3, 16, 131, 64), (3, 7, 67, 48), (4, 16, 195, 48), (0, 5, TWO_EACH, 60),
+                                           (1, 16, TWO_EACH, 60), (2, 32, TWO_EACH, 48)])
+@pytest.mark.parametrize("lanes", [0, 16])
+def test_batched_schedule_bit_identical(cfg, B, n, steps, lanes):
     """The batched impulse resolution of A.8 (16 is the paper's batch size; 1 is a sequential sweep in the plain
     tournament order, 32 the largest the library takes), odd and even numbers of shapes, against the oracle running the same schedule."""
     caps, prm, sc = scenegen.make_scene(cfg, n_envs=n)
     prm = dict(prm, batch_size=B)
     act = scenegen.make_actions(cfg, steps, n)
     o = parity.run_oracle(caps, prm, sc, act)
-    b = parity.run_gpu(caps, prm, sc, act)
+    b = parity.run_gpu(caps, prm, sc, act, lanes=lanes)
     gs, os_ = b.state_dict(), o.state()
     for k in parity.FLOAT_KEYS + parity.INT_KEYS:
         assert np.array_equal(gs[k], os_[k]), k
     assert (os_["pair_count"] > 0).sum() > n
 
 
-def test_batched_schedule_on_the_towers_and_with_restarts():
+@pytest.mark.parametrize("lanes", [0, 16, 8])
+def test_batched_schedule_on_the_towers_and_with_restarts(lanes):
     import torch
     import paper_2410_23208_amd as k2d
     caps, prm, sc = scenegen.make_stack_scene(n_envs=131)
     prm = dict(prm, batch_size=16)
     act = np.zeros((96, 131, caps[2] + caps[3]), dtype=np.float32)
     o = parity.run_oracle(caps, prm, sc, act)
-    b = parity.run_gpu(caps, prm, sc, act)
+    b = parity.run_gpu(caps, prm, sc, act, lanes=lanes)
     gs, os_ = b.state_dict(), o.state()
     for k in parity.FLOAT_KEYS + parity.INT_KEYS:
         assert np.array_equal(gs[k], os_[k]), k
@@ -180,6 +190,8 @@ def test_batched_schedule_on_the_towers_and_with_restarts():
     act = torch.from_numpy(scenegen.make_actions(2, 24, 67)).cuda()
     words = k2d.pack_scenes(caps, sc)
     x, y = k2d.Batch(caps, 67, prm), k2d.Batch(caps, 67, prm)
+    x.set_lanes_per_env(lanes)
+    y.set_lanes_per_env(lanes)
     x.reset(words)
     y.reset(words)
     x.step(act)
@@ -259,17 +271,29 @@ def test_heterogeneous_batch_with_resets():
         assert np.array_equal(gs[k], os_[k]), k
 
 
-@pytest.mark.parametrize("cfg,n,steps,sweep_order", [(4, 195, 24, 0), (1, 131, 30, 0), (0, 67, 20, 0), (4, 195, 24, 1),
-                                                     (3, 131, 20, 1)])
-def test_resets_inside_one_launch(cfg, n, steps, sweep_order):
-    """k2d_step_reset: the protocol of the heterogeneous workload (a seeded 5 % of the environments restart
+@pytest.mark.parametrize("cfg,n,steps,sweep_order,lanes,B,limits", [
+    # a wavefront per environment
+    (4, 195, 24, 0, 0, 0, False), (1, 131, 30, 0, 0, 0, False), (0, 67, 20, 0, 0, 0, False), (4, 195, 24, 1, 0, 0, False),
+    (3, 131, 20, 1, 0, 0, False),
+    # two, four and eight environments to a wavefront: some of them restart while their neighbours go on
+    (0, TWO_EACH, 48, 0, 0, 0, False), (1, TWO_EACH, 40, 0, 0, 0, False), (3, TWO_EACH, 16, 0, 0, 0, False),
+    (1, TWO_EACH + 402, 40, 1, 0, 16, False),
+    (0, 67, 20, 0, 16, 0, False), (1, 131, 30, 0, 16, 0, False), (3, 131, 20, 1, 16, 0, False), (4, 195, 24, 0, 16, 0, False),
+    (0, 67, 20, 0, 8, 0, False), (1, 131, 30, 1, 8, 0, False), (4, 195, 24, 0, 8, 0, False), (3, 131, 20, 0, 8, 0, False),
+    # ... with batches of A.8, and with limited joints
+    (3, 131, 16, 0, 16, 16, False), (3, 67, 16, 0, 16, 32, False), (1, 131, 20, 0, 8, 16, False), (0, 67, 20, 0, 8, 5, False),
+    (4, 195, 24, 0, 16, 0, True), (4, 195, 24, 0, 8, 0, True), (1, TWO_EACH, 40, 0, 0, 0, True)])
+def test_resets_inside_one_launch(cfg, n, steps, sweep_order, lanes, B, limits):
+    """k2d_step_reset: the protocol of the heterogeneous workload (a seeded share of the environments restarts
     from new scenes after every step) in ONE launch, against the oracle stepped and reloaded from the host,
-    and against the GPU path that alternates k2d_step(1) and k2d_reset."""
+    and against the GPU path that alternates k2d_step(1) and k2d_reset (under the library's own lane mapping)."""
     import torch
     import paper_2410_23208_amd as k2d
     from oracle.k2d_oracle import Oracle
+    limited = scenegen.add_joint_limits if limits else (lambda scene: scene)
     caps, prm, sc = scenegen.make_scene(cfg, n_envs=n)
-    prm = dict(prm, sweep_order=sweep_order)
+    sc = limited(sc)
+    prm = dict(prm, sweep_order=sweep_order, batch_size=B)
     act = scenegen.make_actions(cfg, steps, n)
     o = Oracle(caps, n, prm, "f32")
     o.load_scene(sc)
@@ -280,16 +304,18 @@ def test_resets_inside_one_launch(cfg, n, steps, sweep_order):
     for s in range(steps):
         o.step(act[s:s + 1])
         alt.step(act_d[s:s + 1].contiguous())
-        ids = scenegen.reset_ids(cfg, s, n, frac=0.08)
+        ids = scenegen.reset_ids(cfg, s, n, frac=0.08 if n < TWO_EACH else 0.03)
         if len(ids):
             _, _, fresh = scenegen.make_scene(cfg, env_ids=ids, episode=s + 1)
+            fresh = limited(fresh)
             o.load_scene(fresh, env_ids=ids)
             alt.reset(k2d.pack_scenes(caps, fresh), env_ids=ids)
             words = k2d.pack_scenes(caps, fresh)
             sched[s, ids] = np.arange(len(levels), len(levels) + len(ids))
             levels.extend(list(words))
-    assert len(levels) > steps
+    assert len(levels) > steps and (o.state()["pair_count"] > 0).any()
     one = k2d.Batch(caps, n, prm)
+    one.set_lanes_per_env(lanes)
     one.reset(k2d.pack_scenes(caps, sc))
     lv = torch.from_numpy(np.stack(levels).view(np.int32)).cuda()
     one.step_reset(act_d, lv, torch.from_numpy(sched).cuda())
@@ -414,11 +440,12 @@ def _hand_scene_parity(sb, prm, steps, n_envs=1):
     return gs, os_
 
 
-@pytest.mark.parametrize("cfg,lanes", [(2, 0), (0, 8), (1, 0)])
+@pytest.mark.parametrize("cfg,lanes", [(2, 16), (2, 8), (0, 16), (0, 8), (1, 16), (1, 8), (2, 0), (1, 0)])
 def test_ordered_launch_of_small_ragged_batches(cfg, lanes):
     """Launches long enough to be ordered (8 steps and more), with so few environments that the classes of the
     ordering (environments sharing an action line, one class per XCD) do not fill their wavefronts evenly: every
-    environment must still be stepped exactly once."""
+    environment must still be stepped exactly once.  (lanes=0: a wavefront per environment, where there is nothing
+    to order.)"""
     for n in (2, 3, 5, 9, 17, 31, 33, 47, 65):
         caps, prm, sc = scenegen.make_scene(cfg, n_envs=n)
         act = scenegen.make_actions(cfg, 10, n)
@@ -443,7 +470,8 @@ def test_single_environment_and_empty_scene():
 
 
 @pytest.mark.parametrize("B,lanes,sweep_order", [(0, 0, 0), (16, 0, 0), (32, 0, 0), (3, 0, 0), (0, 8, 0), (16, 8, 0),
-                                                 (0, 0, 1), (16, 0, 1), (0, 8, 1)])
+                                                 (0, 0, 1), (16, 0, 1), (0, 8, 1), (0, 16, 0), (16, 16, 0), (32, 16, 0),
+                                                 (3, 16, 0), (0, 16, 1), (16, 16, 1)])
 def test_pile_deeper_than_the_lds_pool(B, lanes, sweep_order):
     """All 16 shapes of an L scene dumped onto one spot: far more active pairs than the per-environment
     LDS pool holds, so the overflow path through the HBM record is exercised (under both schedules)."""
@@ -482,38 +510,44 @@ def test_triangles_circles_inside_polygons_and_static_joints():
     _hand_scene_parity(sb, mkparams(n_substeps=2, n_iters=8), 40)
 
 
-def test_joint_limits_hand_scene():
-    """A.4.3: a bar hinged to a static block drops against its limit; a motorised limited hinge in free space."""
+@pytest.mark.parametrize("lanes", [0, 16, 8])
+def test_joint_limits_hand_scene(lanes):
+    """A.4.3: a bar hinged to a static block drops against its limit; a motorised limited hinge in free space.  Five
+    copies, only the first and the fourth limited: with 16 and 8 lanes they share wavefronts with the others."""
     caps = scenegen.CAPS["M"]
-    sb = SceneBuilder(caps)
-    top = sb.box(0.2, 0.2, (0.0, 2.0), static=True)
-    bar = sb.box(0.5, 0.05, (0.5, 2.0))
-    a = sb.box(0.4, 0.3, (3.0, 3.0), omega=2.0)
-    b = sb.box(0.3, 0.2, (3.3, 3.0))
-    sb.box(5.0, 0.1, (0, 0), static=True)
-    sb.joint(top, bar, (0.0, 2.0), limits=(-0.1, 0.6))
-    sb.joint(a, b, (3.2, 3.0), motor_on=True, speed=2.0, power=0.3, limits=(-0.3, 0.2))
+    sb = SceneBuilder(caps, n_envs=5)
+    for e in range(5):
+        top = sb.box(0.2, 0.2, (0.0, 2.0), static=True, e=e)
+        bar = sb.box(0.5, 0.05, (0.5, 2.0), e=e)
+        a = sb.box(0.4, 0.3, (3.0, 3.0), omega=2.0, e=e)
+        b = sb.box(0.3, 0.2, (3.3, 3.0), e=e)
+        sb.box(5.0, 0.1, (0, 0), static=True, e=e)
+        sb.joint(top, bar, (0.0, 2.0), limits=(-0.1, 0.6) if e in (0, 3) else None, e=e)
+        sb.joint(a, b, (3.2, 3.0), motor_on=True, speed=2.0, power=0.3, limits=(-0.3, 0.2) if e in (0, 3) else None, e=e)
     prm = mkparams(n_substeps=2, n_iters=8)
     sc = sb.scene()
-    act = scenegen.make_actions(1, 90, 1)
+    act = np.repeat(scenegen.make_actions(1, 90, 1), 5, axis=1)
     o = parity.run_oracle(caps, prm, sc, act)
-    b_ = parity.run_gpu(caps, prm, sc, act)
+    b_ = parity.run_gpu(caps, prm, sc, act, lanes=lanes)
     gs, os_ = b_.state_dict(), o.state()
     for k in parity.FLOAT_KEYS + parity.INT_KEYS:
         assert np.array_equal(gs[k], os_[k]), k
-    th = os_["theta"][0]
-    assert -0.15 < th[top] - th[bar] < 0.65               # the bar stays within its range
+    th = os_["theta"]
+    assert -0.15 < th[0][top] - th[0][bar] < 0.65         # the bar stays within its range
+    assert th[1][top] - th[1][bar] > 0.65                 # and without a limit does not
 
 
-@pytest.mark.parametrize("cfg,steps", [(2, 48), (4, 64)])
-def test_joint_limits_generated_scenes(cfg, steps):
+@pytest.mark.parametrize("cfg,steps,n,lanes", [(2, 48, SMALL[2], 0), (4, 64, SMALL[4], 0), (2, 48, SMALL[2], 16),
+                                               (4, 64, SMALL[4], 16), (2, 48, SMALL[2], 8), (4, 64, SMALL[4], 8),
+                                               (1, 48, SMALL[1], 16), (1, 48, SMALL[1], 8), (2, 32, TWO_EACH, 0),
+                                               (1, 32, TWO_EACH, 0)])
+def test_joint_limits_generated_scenes(cfg, steps, n, lanes):
     """The generated workloads with every revolute joint limited: bit-identical, and the limits matter."""
-    n = SMALL[cfg]
     caps, prm, sc0 = scenegen.make_scene(cfg, n_envs=n)
     sc = scenegen.add_joint_limits(sc0)
     act = scenegen.make_actions(cfg, steps, n)
     o = parity.run_oracle(caps, prm, sc, act)
-    b = parity.run_gpu(caps, prm, sc, act)
+    b = parity.run_gpu(caps, prm, sc, act, lanes=lanes)
     gs, os_ = b.state_dict(), o.state()
     for k in parity.FLOAT_KEYS + parity.INT_KEYS:
         assert np.array_equal(gs[k], os_[k]), k
@@ -668,7 +702,8 @@ def test_health_check_flags_the_environments_with_non_finite_state():
 # --------------------------------------------------------------------------------- degenerate input
 @pytest.mark.parametrize("kind", ["coincident_circles", "zero_length_edge", "joint_on_itself", "indices_out_of_range",
                                   "infinite_inverse_mass"])
-def test_degenerate_scenes_have_the_oracles_defined_result(kind):
+@pytest.mark.parametrize("copies,lanes", [(1, 0), (683, 0), (1, 16), (1, 8)])
+def test_degenerate_scenes_have_the_oracles_defined_result(kind, copies, lanes):
     """Through k2d_reset and k2d_step: coincident circle centres, a polygon edge without length, a joint with
     both ends on one shape, shape indices outside the arrays, an infinite inverse mass.  The state and the
     observation equal the oracle's bit for bit, and k2d_read_health flags exactly the environments whose
@@ -676,28 +711,31 @@ def test_degenerate_scenes_have_the_oracles_defined_result(kind):
     from helpers import degenerate_scene, same_bits_or_both_nan
     from oracle import k2d_env
     caps, prm, sc, twin, steps = degenerate_scene(kind)
-    # three environments: the degenerate one between two copies of a sound scene
+    # three environments: the degenerate one between two copies of a sound scene -- each in a wavefront of its own, in
+    # wavefronts of two (683 such triples), and all three in one wavefront
     _, _, sound, _, _ = degenerate_scene("coincident_circles") if twin is None else (caps, prm, twin, None, steps)
-    batch = {k: np.concatenate([sound[k], sc[k], sound[k]], 0) for k in sc}
-    act = np.zeros((steps, 3, caps[2] + caps[3]), dtype=np.float32)
+    batch = {k: np.concatenate([sound[k], sc[k], sound[k]] * copies, 0) for k in sc}
+    n = 3 * copies
+    act = np.zeros((steps, n, caps[2] + caps[3]), dtype=np.float32)
     o = parity.run_oracle(caps, prm, batch, act)
-    b = parity.run_gpu(caps, prm, batch, act)
+    b = parity.run_gpu(caps, prm, batch, act, lanes=lanes)
     gs, os_ = b.state_dict(), o.state()
     # an environment that has blown up holds no meaningful numbers: there the two sides must agree that it
     # has (next assertion block), not on which of its entries are NaN and which infinite (the kernel never
     # writes to shapes that no impulse can move, the oracle multiplies their zero inverse mass by the
     # non-finite impulse); everywhere else every bit must agree
-    rows = [0, 2] if kind == "infinite_inverse_mass" else [0, 1, 2]
+    ids = np.arange(n)
+    rows = ids[ids % 3 != 1] if kind == "infinite_inverse_mass" else ids
     for k in parity.FLOAT_KEYS + parity.INT_KEYS:
         assert same_bits_or_both_nan(gs[k][rows], os_[k][rows]), k
     assert same_bits_or_both_nan(b.read_obs().cpu().numpy().astype(np.float64)[rows], o.obs()[rows])
     N = caps[0] + caps[1]
-    want, n_want = k2d_env.health(os_["pos"].reshape(3, N, 2), os_["theta"], os_["vel"].reshape(3, N, 2),
+    want, n_want = k2d_env.health(os_["pos"].reshape(n, N, 2), os_["theta"], os_["vel"].reshape(n, N, 2),
                                   os_["omega"], batch["active"])
     bad, count = b.read_health()
     assert np.array_equal(bad.cpu().numpy(), want) and int(count.item()) == n_want
-    assert n_want == (1 if kind == "infinite_inverse_mass" else 0)
-    assert np.isfinite(gs["pos"][[0, 2]]).all()               # the neighbours of a blown-up environment are untouched
+    assert n_want == (copies if kind == "infinite_inverse_mass" else 0)
+    assert np.isfinite(gs["pos"][ids % 3 != 1]).all()         # the neighbours of a blown-up environment are untouched
 
 
 def test_device_sin_cos_tanh_against_libm_through_the_observation():
@@ -740,39 +778,43 @@ def test_device_sin_cos_tanh_against_libm_through_the_observation():
     assert 0.0 < worst < 1.5e-7, worst
 
 
-@pytest.mark.parametrize("n,lanes", [(3, 0), (2048, 0), (2049, 0), (4096, 0), (4097, 0), (35, 16), (35, 8)])
+@pytest.mark.parametrize("cfg,n,lanes", [(2, 3, 0), (2, 2048, 0), (2, 2049, 0), (2, 4096, 0), (2, 4097, 0), (2, 35, 16), (2, 35, 8),
+                                         (0, 2048, 0), (0, 2049, 0), (0, 4096, 0), (0, 4097, 0), (0, 8192, 0), (0, 8193, 0),
+                                         (1, 2048, 0), (1, 2049, 0), (1, 4096, 0), (1, 4097, 0), (1, 8704, 0), (1, 8705, 0)])
 @pytest.mark.parametrize("B,sweep_order", [(0, 0), (0, 1), (16, 0)])
-def test_lane_mappings_at_their_edges(n, lanes, B, sweep_order):
+def test_lane_mappings_at_their_edges(cfg, n, lanes, B, sweep_order):
     """The lane mapping that a launch takes depends on the number of environments (64 lanes per environment up to
-    2048, 32 up to 4096, then 16): both sides of every edge, a ragged last wavefront, and in each mapping three
-    environments with more colliding pairs than its registers hold (every shape dumped onto one spot) among
-    ordinary ones."""
-    caps = scenegen.CAPS["L"]
-    sb = SceneBuilder(caps, n_envs=3)
+    2048, 32 up to 4096, then 16, and 8 for Small ones beyond 8192 and Medium ones beyond 8704): both sides of every
+    edge, a ragged last wavefront, and in each mapping three environments with nearly all their pairs colliding
+    (every shape dumped onto one spot: for Large more than any mapping's registers hold, for Medium more than 32 lanes)
+    among ordinary ones."""
+    P, C = scenegen.CAPS["SML"[cfg]][:2]
+    sb = SceneBuilder(scenegen.CAPS["SML"[cfg]], n_envs=3)
     for e in range(3):
         sb.box(6.0, 0.1, (0, 0), static=True, e=e)
-        for k in range(11):
+        for k in range(P - 1):
             sb.box(0.3 + 0.01 * k, 0.3, (0.01 * k + 0.01 * e, 0.35 + 0.01 * k), theta=0.05 * k, friction=0.4, e=e)
-        for k in range(4):
-            sb.circle(0.3, (0.02 * k, 0.4 + 0.02 * k), e=e)
+        for k in range(C):
+            sb.circle(0.3, (0.02 * k, 0.37 + 0.02 * k), e=e)
     piles = sb.scene()
-    _, _, sc = scenegen.make_scene(2, n_envs=n)
+    _, _, sc = scenegen.make_scene(cfg, n_envs=n)
     sc = {k: v.copy() for k, v in sc.items() if k in piles}
     rows = [0, n // 2, n - 1]
     for k in sc:
         sc[k][rows] = np.asarray(piles[k]).reshape(3, *sc[k].shape[1:])
     prm = mkparams(n_substeps=2, n_iters=6, alpha=0.5, beta=0.02, batch_size=B, sweep_order=sweep_order)
-    act = scenegen.make_actions(2, 3, n)
-    o = parity.run_oracle(caps, prm, sc, act)
-    b = parity.run_gpu(caps, prm, sc, act, lanes=lanes)
+    act = scenegen.make_actions(cfg, 3, n)
+    o = parity.run_oracle(sb.caps, prm, sc, act)
+    b = parity.run_gpu(sb.caps, prm, sc, act, lanes=lanes)
     gs, os_ = b.state_dict(), o.state()
-    assert (os_["pair_count"] > 0).sum(1).max() > 62
+    assert (os_["pair_count"] > 0).sum(1).max() > (16, 32, 62)[cfg]
     for k in parity.FLOAT_KEYS + parity.INT_KEYS:
         assert np.array_equal(gs[k], os_[k]), k
 
 
-@pytest.mark.parametrize("cfg,lanes", [(0, 8), (0, 16), (1, 8), (1, 16), (2, 0)])
-@pytest.mark.parametrize("n", [2047, 2048, 2049, 6145])
+@pytest.mark.parametrize("cfg,lanes,n", [(cfg, lanes, n) for cfg, lanes in [(0, 8), (0, 16), (1, 8), (1, 16), (2, 16)]
+                                         for n in (2047, 2048, 2049, 6145)] +
+                         [(cfg, 0, n) for cfg in (0, 1, 2) for n in (2049, 4095)])
 def test_ordered_launch_over_several_workgroups(cfg, lanes, n):
     """The ordering shares the environments out over workgroups of 2048: around the edge of one, and a ragged last
     one of several.  The second launch is ordered by the pairs that collide then (many different keys)."""

@@ -36,7 +36,8 @@ def test_noalloc_step_equals_step_twice_second_smaller():
 
 
 def test_noalloc_step_other_capacity_class_after_it():
-    for cfg, n in ((1, 8323), (2, 131)):
+    # (two, four and eight environments to a wavefront; the last batch has a wavefront per environment and no ordering)
+    for cfg, n in ((1, 8323), (1, 8739), (2, 4227), (1, 2179), (2, 131)):
         want = _records(cfg, n, 16, noalloc=False)
         got = _records(cfg, n, 16, noalloc=True)
         assert np.array_equal(want, got)
