@@ -25,14 +25,15 @@
 //     to a sequential Gauss-Seidel sweep (the sequential end of the speed/stability trade-off of A.8,
 //     reached without the paper's batch-of-16 compromise).
 //   * Active manifolds of a substep become records that live in registers: lane k of the environment
-//     keeps active pairs k and G + k for the whole substep (warm start, all sweeps, corrections), so a
-//     visit costs one LDS round trip for the two bodies' velocities and nothing else; the accumulated
-//     impulses wait in LDS from substep to substep.  Pairs beyond 2G stay in a small LDS pool, the rare excess beyond that spills
-//     to the environment's HBM record.
+//     keeps active pair k, and with up to 32 lanes per environment pair G + k too (62 pairs at most, what a
+//     state byte can name), for the whole substep (warm start, all sweeps, corrections), so a visit costs
+//     one LDS round trip for the two bodies' velocities and nothing else; the accumulated impulses wait in
+//     LDS from substep to substep.  Pairs beyond those stay in a small LDS pool, the rare excess beyond
+//     that spills to the environment's HBM record.
 //   * Joints are solved in index order per shape (A.8: sequential); joints that share no shape are
 //     independent, so they are grouped into dependency levels once per episode and lane j solves joint j.
-//   * A launch of many steps first sorts the environments by expected work, so that the environments
-//     of a wavefront are alike: what a wavefront skips when none of its environments changed its set of
+//   * Where environments share wavefronts, a launch of many steps first sorts them by expected work, so
+//     that those of a wavefront are alike: what a wavefront skips when none of its environments changed its set of
 //     colliding pairs (candidate list, dependency levels) it then skips more often.
 //
 // Nothing here is a dense contraction: no MFMA.  Arithmetic is fp32; the kernel is compiled without
@@ -661,7 +662,8 @@ unsigned long long* g_phase_clocks = nullptr;   // caller-owned device buffer, k
 long g_phase_waves = 0;
 bool g_phase_keep_order = false;                // launches take the environments as they are numbered
 #endif
-// wavefronts of the step kernel that are resident at once: two on every SIMD (registers and LDS allow no more)
+// wavefronts of the step kernel that are resident at once: two on every SIMD of the 256 CUs (registers allow no more; the
+// LDS images of 8 Large environments allow one)
 constexpr int kWaveSlots = 256 * 8;
 
 }  // namespace
@@ -695,7 +697,7 @@ struct k2d_batch {
   int rec_words;
   float* state;
   int32_t* order;   // behind the records in the caller's buffer: slot -> environment for one launch
-  int lanes;        // lanes per environment of the step kernel: 8, 16, or 0 = chosen by the batch size
+  int lanes;        // lanes per environment of the step kernel: 8, 16, or 0 = chosen by the number of environments
 };
 
 // launches of fewer steps than this keep the identity ordering (the ordering pass would cost more than it could save)
@@ -722,13 +724,24 @@ static Params device_params(const k2d_params& p) {
   return prm;
 }
 
-// Lanes per environment where the batch does not say: as many as leave no environment waiting for a wavefront slot
-// (measured on MI355X, 64 steps, ms with 64 / 32 / 16 / 8 lanes: Large 2048 environments 2.72 / 2.99 / 3.29 / 3.93,
-// 4096: 5.07 / 2.88 / 3.29 / 4.15, 8192: 8.52 / 4.75 / 3.16 / 4.14; Medium 1024: 1.26 / 1.62 / 1.76 / 2.07; Small
-// 256: 0.46 / 0.48 / 0.61 / 0.66, 8192: 1.73 / 1.05 / 0.69 / 0.74).  Beyond what 16 lanes keep resident Small and
-// Medium environments take 8 lanes (16 / 8 lanes: Small 8193: 0.75 / 0.68, 65536: 4.40 / 2.71; Medium 8193: 1.52 /
-// 1.91, 10000: 2.36 / 2.12, 65536: 10.0 / 6.5); Large ones stay at 16 (32768: 8.7 / 11.1), since eight of their
-// images leave room for one wavefront per SIMD, whose dependent instructions have nothing to overlap with.
+// Lanes per environment where the batch does not say: as many as leave no environment waiting for a wavefront slot.
+// Measured on MI355X, 64 steps from new episodes, ms with 64 / 32 / 16 / 8 lanes:
+//   environments    Small                       Medium                      Large
+//     256     0.40 / 0.45 / 0.52 / 0.58   0.97 / 1.08 / 1.38 / 1.70   1.84 / 2.07 / 2.32 / 3.21
+//    2048     0.48 / 0.49 / 0.53 / 0.55   1.27 / 1.31 / 1.42 / 1.68   2.23 / 2.33 / 2.49 / 3.19
+//    2049     0.60 / 0.50 / 0.54 / 0.61   1.47 / 1.27 / 1.39 / 1.81   2.23 / 2.28 / 2.46 / 3.18
+//    3072     0.81 / 0.53 / 0.55 / 0.62   1.96 / 1.33 / 1.48 / 1.73   3.40 / 2.35 / 2.56 / 3.44
+//    4096     0.87 / 0.56 / 0.55 / 0.62   2.22 / 1.33 / 1.45 / 1.78   4.14 / 2.31 / 2.57 / 3.40
+//    4097     0.90 / 0.65 / 0.55 / 0.67   2.26 / 1.32 / 1.45 / 1.74   4.12 / 2.26 / 2.56 / 3.44
+//    6144     1.28 / 0.88 / 0.60 / 0.64   3.20 / 2.12 / 1.41 / 1.93   5.64 / 3.73 / 2.51 / 3.47
+//    8192     1.67 / 0.97 / 0.60 / 0.63   4.06 / 2.31 / 1.57 / 1.83   7.04 / 3.88 / 2.55 / 3.40
+//    8193     1.68 / 1.02 / 0.74 / 0.64                               7.01 / 4.01 / 2.57 / 3.40
+//    8704                                 4.36 / 2.78 / 2.09 / 1.82
+//   16384     3.15 / 1.81 / 1.13 / 0.71   7.52 / 4.31 / 2.64 / 1.93
+// (Just past a line the wider mapping can still be the faster one, Medium and Large at 4097; Medium's last line is a
+// little late, at 8704 it is faster with 8 lanes already.)  Beyond what 16 lanes keep resident Small and Medium environments take 8
+// lanes; Large ones stay at 16 (32768: 8.7 with 16, 11.1 with 8), since eight of their images leave room for one
+// wavefront per SIMD, whose dependent instructions have nothing to overlap with.
 static int lanes_for(int cls, int n_envs, int batch_size) {
   if (n_envs <= kWaveSlots) return 64;
   if (n_envs <= 2 * kWaveSlots) return 32;
@@ -748,9 +761,11 @@ static int step_launch(k2d_batch* b, const float* actions_dev, int n_envs, int n
     s.prm.n_batches = (2 * b->layout.n_pairs + b->params.batch_size - 1) / b->params.batch_size;
     if (s.prm.n_batches < 2) return K2D_E_ARG;   // (the kernel relies on the two points of a pair being in different batches)
   }
-  // A launch of many steps takes its environments in the order of their expected work: the four of a
+  // A launch of many steps takes its environments in the order of their expected work: those that share a
   // wavefront are then alike, and what a wavefront skips when none of its environments changed (candidate
-  // list, dependency levels) it skips more often (7 % of the launch time on the Large workload).
+  // list, dependency levels) it skips more often.  Ordered against numbered, ms: 16384 heterogeneous environments
+  // x 256 steps 31.0 / 38.1, 32768 contact-heavy ones x 128 32.9 / 37.7, 16384 Medium ones x 64 1.94 / 2.13, 65536
+  // Small ones x 64 2.57 / 2.58; no difference (16.4) where all are resident and the slowest decides (Large 8192 x 256).
   s.order = (n_steps >= kOrderMinSteps && n_envs < kOrderMaxEnvs) ? order_buf : nullptr;
 #ifdef K2D_PHASE_TIMERS
   if (g_phase_keep_order) s.order = nullptr;

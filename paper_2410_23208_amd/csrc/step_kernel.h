@@ -37,7 +37,7 @@ struct Cfg {
   static_assert(ET <= 16, "pair states of a lane");
   static_assert(G * TSP <= 256, "a candidate's 16 bits: shapes in the low byte, the place of its state byte in the high one");
   // Active pairs are numbered 0, 1, ... as the narrowphase finds them.  Pairs below NREG live in
-  // registers (lane k holds pairs k and G + k): the lane that found the manifold leaves it in an LDS
+  // registers (lane k holds pair k and, where NREG > G, pair G + k): the lane that found the manifold leaves it in an LDS
   // staging slot, the lane that keeps the pair derives the substep constants from it.  Pairs beyond them
   // live as full records in a small LDS pool (POOL records, as many as the LDS budget of the class has
   // room for, eight at most) or, past that, in the HBM record.
@@ -161,8 +161,9 @@ __device__ __forceinline__ void hbm_sync() {
 __device__ __forceinline__ float dot2(float ax, float ay, float bx, float by) { return fmaf(ax, bx, ay * by); }
 __device__ __forceinline__ float cross2(float ax, float ay, float bx, float by) { return fmaf(ax, by, -(ay * bx)); }
 // a + b with `a` as the first operand of the instruction.  For numbers the order is nothing; where both are NaN (an
-// environment that blew up) the first one's sign survives, and the records of such an environment should not
-// depend on how a compiler happens to arrange a commutative addition.
+// environment that blew up) the first one's sign survives.  This keeps poses from depending on how a compiler arranges
+// these additions, and is no promise: the sweeps are compiled several times over, the neighbours of a wavefront decide
+// which of them runs, and the bits of the NaNs in an environment that blew up may differ from launch to launch.
 __device__ __forceinline__ float add_ordered(float a, float b) {
   float d;
   asm("v_add_f32_e32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
@@ -1124,7 +1125,7 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
       //    after the other, so that the group's lanes share them evenly and a wavefront runs one kind
       //    of manifold code per trip;
       // 3. the manifold of every active pair is staged in LDS for the lane that keeps the pair in
-      //    registers for the rest of the substep (pairs beyond two per lane become records in LDS / HBM).
+      //    registers for the rest of the substep (pairs from NREG on become records in LDS / HBM).
       unsigned cand = 0u;
       bool set_changed = false;   // a pair of this lane collides now and did not one substep ago, or the reverse
       // (four pairs at a time and all of both boxes: one round trip to LDS, and no branch on a comparison.  This phase with
@@ -1284,7 +1285,7 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
       }
       wave_sync();
       K2D_T(kT_Manifolds);
-      // lane k keeps active pairs k and G + k of its environment in registers
+      // lane k keeps active pairs k and, where NREG > G, G + k of its environment in registers
       Own oa, ob;
       oa.have = false; ob.have = false; oa.lv = -1; ob.lv = -1;
       oa.rc.ab = 0; ob.rc.ab = 0;
