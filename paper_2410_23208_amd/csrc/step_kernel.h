@@ -65,9 +65,9 @@ struct Cfg {
   static constexpr int X_LVL = X_TAKEN + (N + 1) / 2;      // bytes [LISTED]: level of a pair not held in registers
   static constexpr int LCAP = 16;                          // a level holds at most one pair per movable shape
   static constexpr int X_SCHED = X_LVL + (LISTED + 3) / 4; // bytes [R][LCAP]: the pairs not held in registers, level by level
-  static constexpr int SEEN = NP < 64 ? NP : 64;
-  static constexpr int X_SEEN = X_SCHED + R * LCAP / 4;    // words [SEEN]: shapes met in a batch of A.8
-  static_assert(X_SEEN + SEEN <= X_WV + WSTRIDE * P, "what shares the world polygons' LDS");
+  static_assert(X_SCHED + R * LCAP / 4 <= X_WV + WSTRIDE * P, "what shares the world polygons' LDS");
+  static constexpr int X_SEEN = X_WV;                      // (no pairs outside the registers) words [2 NP]: shapes met in a batch of A.8
+  static_assert(2 * NP <= WSTRIDE * P, "a word for every batch there can be");
   static constexpr int X_LIST = X_WV + WSTRIDE * P;        // 16-bit [NP]: candidate pairs, one shape-type mix after the other
   static constexpr int X_ELIG = X_LIST;                    // (episode set-up only) bytes [NP]: eligible pairs
   static constexpr int X_PSB = X_LIST;                     // (write-back only) bytes [NP]: pair states in lexicographic pair order
@@ -1539,11 +1539,15 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
         // batch of the two slots of the lane's pairs, -1 = none
         const int a0 = oa.have ? oa_bj & 0xff : -1, a1 = (oa.rc.ab & kTwo) ? (oa_bj >> 16) & 0xff : -1;
         const int b0 = ob.have ? ob_bj & 0xff : -1, b1 = (ob.rc.ab & kTwo) ? (ob_bj >> 16) & 0xff : -1;
-        // which batches hold points at all, and which of those stage their impulses (where there are more batches than the
-        // table has room for, each holds a point or a few, and all are staged)
-        unsigned long long used = ~0ull, staged = ~0ull;
-        const bool told = n_b <= K::SEEN && !any_listed;
-        if (told) {
+        // which batches hold points at all, and which of those stage their impulses, a bit each.  (Where pairs live outside
+        // the registers every batch is looked at, and staged.  The table has a word for every batch there can be: where it
+        // held 64, batches of one to three points, of which Large has 240 to 80, were all walked and staged.  5000 Large
+        // environments x 24 steps with 1 / 2 / 3 points to a batch, ms: 32.1 / 16.7 / 11.7 then, 1.5 / 1.3 / 1.2 now; in the
+        // dense pile 41.8 / 25.1 / 19.4, 7.7 / 7.1 / 7.2.)
+        // Lane w keeps the bits of batches 32 w, ..., 32 w + 31 (scalar registers for all of them would have to be spilled).
+        const int mine = n_b - 32 * lane;
+        unsigned used = mine >= 32 ? ~0u : mine > 0 ? (1u << mine) - 1u : 0u, staged = ~0u;
+        if (!any_listed) {
           unsigned* seen = reinterpret_cast<unsigned*>(E + K::X_SEEN);   // shapes met in a batch; bit 16: two points meet
           for (int i = k; i < n_b; i += G) seen[i] = 0u;
           wave_sync();
@@ -1560,117 +1564,123 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
             note(b1, ob.pa, ob.pb);
           }
           wave_sync();
-          used = 0ull; staged = 0ull;
-          for (int i0 = 0; i0 < n_b; i0 += G) {
-            const unsigned w = i0 + k < n_b ? seen[i0 + k] : 0u;
-            const unsigned long long u = __ballot((w >> 17) & 1u), st = __ballot((w >> 16) & 1u);
+          for (int w = 0; 32 * w < n_b; ++w) {
+            constexpr int CHUNK = G < 32 ? G : 32;
+            unsigned u = 0u, st = 0u;
+            for (int i0 = 0; i0 < min(n_b - 32 * w, 32); i0 += CHUNK) {
+              const int i = 32 * w + i0 + k;
+              const unsigned m = k < CHUNK && i < n_b ? seen[i] : 0u;
+              const unsigned long long um = __ballot((m >> 17) & 1u), sm = __ballot((m >> 16) & 1u);
 #pragma unroll
-            for (int e = 0; e < K::EPW; ++e) {
-              constexpr unsigned long long mask = G == 64 ? ~0ull : (1ull << (G & 63)) - 1ull;
-              used |= ((u >> (e * G)) & mask) << i0;
-              staged |= ((st >> (e * G)) & mask) << i0;
+              for (int e = 0; e < K::EPW; ++e) {
+                constexpr unsigned mask = CHUNK == 32 ? ~0u : (1u << (CHUNK & 31)) - 1u;
+                u |= ((unsigned)(um >> (e * G)) & mask) << i0;
+                st |= ((unsigned)(sm >> (e * G)) & mask) << i0;
+              }
             }
+            used = lane == w ? u : used;
+            staged = lane == w ? st : staged;
           }
         }
         for (int it = 0; it < prm.n_iters; ++it) {
           sweep_joints(I2{});
-          for (int b = 0; b < n_b; ++b) {
-            if (told) {   // (on to the next batch that holds points)
-              const unsigned long long rest = used >> b;
-              if (rest == 0ull) break;
-              b += __builtin_ctzll(rest);
-            }
-            if (told && !((staged >> b) & 1ull)) {
-              auto direct = [&](Own& o, int s0, int s1) {
+          for (int w = 0; 32 * w < n_b; ++w) {
+            const unsigned stages = (unsigned)__builtin_amdgcn_readlane((int)staged, w);
+            // (from one batch that holds points to the next)
+            for (unsigned rest = (unsigned)__builtin_amdgcn_readlane((int)used, w); rest != 0u; rest &= rest - 1u) {
+              const int bit = __builtin_ctz(rest), b = 32 * w + bit;
+              if (!((stages >> bit) & 1u)) {
+                auto direct = [&](Own& o, int s0, int s1) {
+                  const bool hit1 = s1 == b;
+                  if (s0 == b || hit1) {
+                    float4 va = S::get_vel(o.at_a), vb = S::get_vel(o.at_b);
+                    float jx, jy, fx, fy, rax, ray, rbx, rby;
+                    S::point_impulses(o.rc, hit1, o.ima, o.iia, o.imb, o.iib, va, vb, jx, jy, fx, fy, rax, ray, rbx, rby);
+                    S::put_vel(o.to_a, va);
+                    S::put_vel(o.to_b, vb);
+                  }
+                };
+                direct(oa, a0, a1);
+                if constexpr (K::TWO) {
+                  if (any_b) direct(ob, b0, b1);
+                }
+                wave_sync();
+                continue;
+              }
+              unsigned pm = 0u;   // places of the batch taken by this lane's points
+              auto stage_point = [&](int j, int ab, float jx, float jy, float fx, float fy, float rax, float ray,
+                                     float rbx, float rby) {
+                float4* p = reinterpret_cast<float4*>(E + K::X_STAGE + j * K::kManW);
+                p[0] = make_float4(jx, jy, fx, fy);
+                p[1] = make_float4(rax, ray, rbx, rby);
+                reinterpret_cast<int*>(p)[8] = ab & 0xffff;
+                pm |= 1u << j;
+              };
+              auto own_points = [&](Own& o, int bj, int s0, int s1) {
                 const bool hit1 = s1 == b;
                 if (s0 == b || hit1) {
                   float4 va = S::get_vel(o.at_a), vb = S::get_vel(o.at_b);
                   float jx, jy, fx, fy, rax, ray, rbx, rby;
                   S::point_impulses(o.rc, hit1, o.ima, o.iia, o.imb, o.iib, va, vb, jx, jy, fx, fy, rax, ray, rbx, rby);
-                  S::put_vel(o.to_a, va);
-                  S::put_vel(o.to_b, vb);
+                  stage_point((bj >> (hit1 ? 24 : 8)) & 0xff, o.rc.ab, jx, jy, fx, fy, rax, ray, rbx, rby);
                 }
               };
-              direct(oa, a0, a1);
+              own_points(oa, oa_bj, a0, a1);
               if constexpr (K::TWO) {
-                if (any_b) direct(ob, b0, b1);
+                if (any_b) own_points(ob, ob_bj, b0, b1);
               }
-              wave_sync();
-              continue;
-            }
-            unsigned pm = 0u;   // places of the batch taken by this lane's points
-            auto stage_point = [&](int j, int ab, float jx, float jy, float fx, float fy, float rax, float ray,
-                                   float rbx, float rby) {
-              float4* p = reinterpret_cast<float4*>(E + K::X_STAGE + j * K::kManW);
-              p[0] = make_float4(jx, jy, fx, fy);
-              p[1] = make_float4(rax, ray, rbx, rby);
-              reinterpret_cast<int*>(p)[8] = ab & 0xffff;
-              pm |= 1u << j;
-            };
-            auto own_points = [&](Own& o, int bj, int s0, int s1) {
-              const bool hit1 = s1 == b;
-              if (s0 == b || hit1) {
-                float4 va = S::get_vel(o.at_a), vb = S::get_vel(o.at_b);
-                float jx, jy, fx, fy, rax, ray, rbx, rby;
-                S::point_impulses(o.rc, hit1, o.ima, o.iia, o.imb, o.iib, va, vb, jx, jy, fx, fy, rax, ray, rbx, rby);
-                stage_point((bj >> (hit1 ? 24 : 8)) & 0xff, o.rc.ab, jx, jy, fx, fy, rax, ray, rbx, rby);
-              }
-            };
-            own_points(oa, oa_bj, a0, a1);
-            if constexpr (K::TWO) {
-              if (any_b) own_points(ob, ob_bj, b0, b1);
-            }
-            if constexpr (K::LISTED > 0) {
-              if (any_listed) {
-                auto listed_points = [&](auto rp) {
-                  PairRec rc;
-                  rec_load(rp, rc);
-                  const int bj = S::batch_places(rc.ab, n_b);
-                  const bool hit0 = (bj & 0xff) == b;
-                  const bool hit1 = (rc.ab & kTwo) && ((bj >> 16) & 0xff) == b;
-                  if (hit0 || hit1) {
-                    const int a = rc.ab & 0xff, bb = (rc.ab >> 8) & 0xff;
-                    const float4 qa = S::prop4(E, a), qb = S::prop4(E, bb);
-                    float4 va = S::vel4(E, a), vb = S::vel4(E, bb);
-                    float jx, jy, fx, fy, rax, ray, rbx, rby;
-                    S::point_impulses(rc, hit1, qa.x, qa.y, qb.x, qb.y, va, vb, jx, jy, fx, fy, rax, ray, rbx, rby);
-                    stage_point((bj >> (hit1 ? 24 : 8)) & 0xff, rc.ab, jx, jy, fx, fy, rax, ray, rbx, rby);
-                    if (hit1) { rp[15 + 8] = rc.lam_n[1]; rp[15 + 9] = rc.lam_t[1]; }
-                    else { rp[5 + 8] = rc.lam_n[0]; rp[5 + 9] = rc.lam_t[0]; }
-                  }
-                };
-                for (int q = k; __any(q < n_listed); q += G)
-                  if (q < n_listed) {
-                    if (q < K::POOL) listed_points(to_lds(pool + q * kRecW));
-                    else listed_points(spill + (q - K::POOL) * kRecW);
-                  }
-              }
-            }
-            pm = group_or<G>(pm);
-            wave_sync();
-            if (__any(pm != 0u)) {
-#pragma unroll
-              for (int s = 0; s < NS; ++s) {   // lane k applies to shapes k, k + G, ...
-                const int i = k + s * G;
-                if (i < N && !((static_mask >> i) & 1u) && pm != 0u) {
-                  float4 v = S::vel4(E, i);
-                  const float2 q = *reinterpret_cast<const float2*>(E + K::X_PROP + 4 * i);
-                  for (unsigned m = pm; m != 0u; m &= m - 1u) {
-                    const float4* p = reinterpret_cast<const float4*>(E + K::X_STAGE + (__ffs(m) - 1) * K::kManW);
-                    const int ab = reinterpret_cast<const int*>(p)[8];
-                    const float4 j = p[0], r = p[1];
-                    if ((ab & 0xff) == i) {
-                      apply_impulse(v, q.x, q.y, j.x, j.y, r.x, r.y);
-                      apply_impulse(v, q.x, q.y, j.z, j.w, r.x, r.y);
-                    } else if ((ab >> 8) == i) {
-                      apply_impulse(v, q.x, q.y, -j.x, -j.y, r.z, r.w);
-                      apply_impulse(v, q.x, q.y, -j.z, -j.w, r.z, r.w);
+              if constexpr (K::LISTED > 0) {
+                if (any_listed) {
+                  auto listed_points = [&](auto rp) {
+                    PairRec rc;
+                    rec_load(rp, rc);
+                    const int bj = S::batch_places(rc.ab, n_b);
+                    const bool hit0 = (bj & 0xff) == b;
+                    const bool hit1 = (rc.ab & kTwo) && ((bj >> 16) & 0xff) == b;
+                    if (hit0 || hit1) {
+                      const int a = rc.ab & 0xff, bb = (rc.ab >> 8) & 0xff;
+                      const float4 qa = S::prop4(E, a), qb = S::prop4(E, bb);
+                      float4 va = S::vel4(E, a), vb = S::vel4(E, bb);
+                      float jx, jy, fx, fy, rax, ray, rbx, rby;
+                      S::point_impulses(rc, hit1, qa.x, qa.y, qb.x, qb.y, va, vb, jx, jy, fx, fy, rax, ray, rbx, rby);
+                      stage_point((bj >> (hit1 ? 24 : 8)) & 0xff, rc.ab, jx, jy, fx, fy, rax, ray, rbx, rby);
+                      if (hit1) { rp[15 + 8] = rc.lam_n[1]; rp[15 + 9] = rc.lam_t[1]; }
+                      else { rp[5 + 8] = rc.lam_n[0]; rp[5 + 9] = rc.lam_t[0]; }
                     }
-                  }
-                  S::vel4(E, i) = v;
+                  };
+                  for (int q = k; __any(q < n_listed); q += G)
+                    if (q < n_listed) {
+                      if (q < K::POOL) listed_points(to_lds(pool + q * kRecW));
+                      else listed_points(spill + (q - K::POOL) * kRecW);
+                    }
                 }
               }
+              pm = group_or<G>(pm);
               wave_sync();
+              if (__any(pm != 0u)) {
+#pragma unroll
+                for (int s = 0; s < NS; ++s) {   // lane k applies to shapes k, k + G, ...
+                  const int i = k + s * G;
+                  if (i < N && !((static_mask >> i) & 1u) && pm != 0u) {
+                    float4 v = S::vel4(E, i);
+                    const float2 q = *reinterpret_cast<const float2*>(E + K::X_PROP + 4 * i);
+                    for (unsigned m = pm; m != 0u; m &= m - 1u) {
+                      const float4* p = reinterpret_cast<const float4*>(E + K::X_STAGE + (__ffs(m) - 1) * K::kManW);
+                      const int ab = reinterpret_cast<const int*>(p)[8];
+                      const float4 j = p[0], r = p[1];
+                      if ((ab & 0xff) == i) {
+                        apply_impulse(v, q.x, q.y, j.x, j.y, r.x, r.y);
+                        apply_impulse(v, q.x, q.y, j.z, j.w, r.x, r.y);
+                      } else if ((ab >> 8) == i) {
+                        apply_impulse(v, q.x, q.y, -j.x, -j.y, r.z, r.w);
+                        apply_impulse(v, q.x, q.y, -j.z, -j.w, r.z, r.w);
+                      }
+                    }
+                    S::vel4(E, i) = v;
+                  }
+                }
+                wave_sync();
+              }
             }
           }
           K2D_T(kT_SweepPairs);

@@ -171,6 +171,27 @@ def test_batched_schedule_bit_identical(cfg, B, n, steps, lanes):
     assert (os_["pair_count"] > 0).sum() > n
 
 
+@pytest.mark.parametrize("cfg,B,n,lanes", [(cfg, B, n, lanes) for cfg, Bs in ((0, (1, 2)), (1, (1, 2)), (2, (1, 2, 3, 4, 5)))
+                                           for B in Bs for n, lanes in ((67, 0), (67, 16), (67, 8), (TWO_EACH, 0))])
+def test_more_batches_than_lanes_or_bits_of_a_word(cfg, B, n, lanes):
+    """Batches of a few points: a sweep of a Large scene has 240, 120, 80, 60 and 48 of them (72 and 36 Medium, 42 and
+    21 Small), which the wavefront keeps track of with a bit each, 64 to a word.  Piles, so that points fall into the
+    batches of every word; with one point to a batch also the bits of the sequential sweep."""
+    cfg = 3 if cfg == 2 else cfg
+    caps, prm, sc = scenegen.make_scene(cfg, n_envs=n)
+    act = scenegen.make_actions(cfg, 40, n)
+    o = parity.run_oracle(caps, dict(prm, batch_size=B), sc, act)
+    b = parity.run_gpu(caps, dict(prm, batch_size=B), sc, act, lanes=lanes)
+    gs, os_ = b.state_dict(), o.state()
+    for k in parity.FLOAT_KEYS + parity.INT_KEYS:
+        assert np.array_equal(gs[k], os_[k]), k
+    hit = (os_["pair_count"] > 0).any(0)                       # pairs that collide somewhere
+    assert hit.mean() > 0.5
+    if B == 1:
+        seq = parity.run_gpu(caps, prm, sc, act, lanes=lanes)
+        assert np.array_equal(seq.read_state().cpu().numpy(), b.read_state().cpu().numpy())
+
+
 @pytest.mark.parametrize("lanes", [0, 16, 8])
 def test_batched_schedule_on_the_towers_and_with_restarts(lanes):
     import torch
