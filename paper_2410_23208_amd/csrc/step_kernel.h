@@ -62,10 +62,11 @@ struct Cfg {
                                                            // the lanes' 16-byte reads of different polygons spread over the banks
   static constexpr int X_WV = X_BOX + 4 * N;
   static constexpr int X_TAKEN = X_WV;                     // (world polygons are done with) 16-bit [N]: levels taken at a shape
-  static constexpr int X_LVL = X_TAKEN + (N + 1) / 2;      // bytes [LISTED]: level of a pair not held in registers
+  static constexpr int X_LCNT = X_TAKEN + (N + 1) / 2;     // 4 bits [16]: pairs not held in registers, by level
   static constexpr int LCAP = 16;                          // a level holds at most one pair per movable shape
-  static constexpr int X_SCHED = X_LVL + (LISTED + 3) / 4; // bytes [R][LCAP]: the pairs not held in registers, level by level
-  static_assert(X_SCHED + R * LCAP / 4 <= X_WV + WSTRIDE * P, "what shares the world polygons' LDS");
+  static constexpr int X_SCHED = X_LCNT + 2;               // bytes [R][LCAP]: the pairs not held in registers, level by level
+  static constexpr int X_ROUNDS = align_up(X_SCHED + R * LCAP / 4, 4);   // bytes [PPR][16]: pair k of round r at [k][r]
+  static_assert(R <= 16 && PPR <= G && X_ROUNDS + 4 * PPR <= X_WV + WSTRIDE * P, "what shares the world polygons' LDS");
   static constexpr int X_SEEN = X_WV;                      // (no pairs outside the registers) words [2 NP]: shapes met in a batch of A.8
   static_assert(2 * NP <= WSTRIDE * P, "a word for every batch there can be");
   static constexpr int X_LIST = X_WV + WSTRIDE * P;        // 16-bit [NP]: candidate pairs, one shape-type mix after the other
@@ -287,6 +288,13 @@ struct Step {
   // The round a pair (a < b) plays in: a and b add up to twice the round, modulo M - 1 (an odd number, whose
   // inverse of two is M / 2).
   static __device__ __forceinline__ int round_of(int a, int b) { return b == M - 1 ? a : ((a + b) * (M / 2)) % (M - 1); }
+  // ... and which pair of that round it is (the k of sched_pair)
+  static __device__ __forceinline__ int place_in_round(int a, int b, int r) {
+    int k = a - r;
+    if (k < 0) k += M - 1;
+    if (k > M / 2 - 1) k = M - 1 - k;
+    return b == M - 1 ? 0 : k;
+  }
   static __device__ __forceinline__ int pair_index(int a, int b) { return a * (2 * N - a - 1) / 2 + (b - a - 1); }
 
   // ---- A.3.2: circle a, circle b ----
@@ -532,13 +540,7 @@ struct Step {
   // order, are dealt in turn over n_b batches.  Returns batch | place<<8 of slot 0, the same <<16 of slot 1.
   static __device__ __forceinline__ int batch_places(int ab, int n_b) {
     constexpr int odd = N & 1;   // the phantom's pair (place 0 of every round) is not a pair
-    const int a = ab & 0xff, b = (ab >> 8) & 0xff, r = round_of(a, b);
-    int kk = 0;
-    if (b != M - 1) {
-      kk = a - r;
-      if (kk < 0) kk += M - 1;
-      if (kk > M / 2 - 1) kk = M - 1 - kk;
-    }
+    const int a = ab & 0xff, b = (ab >> 8) & 0xff, r = round_of(a, b), kk = place_in_round(a, b, r);
     const int s0 = 2 * (r * (K::PPR - odd) + kk - odd);
     const int j0 = s0 / n_b, b0 = s0 - j0 * n_b;
     int b1 = b0 + 1, j1 = j0;
@@ -699,7 +701,6 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
   unsigned short* cand_list = reinterpret_cast<unsigned short*>(E + K::X_LIST);
   unsigned short* lt = reinterpret_cast<unsigned short*>(E + K::X_LT);
   unsigned short* taken = reinterpret_cast<unsigned short*>(E + K::X_TAKEN);
-  unsigned char* lvl = reinterpret_cast<unsigned char*>(E + K::X_LVL);
   unsigned char* sched = reinterpret_cast<unsigned char*>(E + K::X_SCHED);
   float4* lam_store = reinterpret_cast<float4*>(E + K::X_LAM);
   const float h = prm.h;
@@ -1379,13 +1380,12 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
           if (prm.lowest_free_level)   // (a pair may find a lower level free than the number of pairs it waited for)
             while (wave_clevels > 1 && !__any(oa.lv == wave_clevels - 1)) --wave_clevels;
         } else {
-          // Some lane holds more than one pair: round by round, through the sets of levels taken at every shape
+          // Some lane keeps more than one pair: round by round, through the sets of levels taken at every shape
           // (16-bit words in LDS).  The pairs of a round touch disjoint shapes, so the lanes of a round read and
           // extend those sets without getting in each other's way, and the rounds follow one another.
           int my_levels = 0;
           if (k < (N + 1) / 2) reinterpret_cast<unsigned*>(taken)[k] = 0u;
           if (G < (N + 1) / 2 && k + G < (N + 1) / 2) reinterpret_cast<unsigned*>(taken)[k + G] = 0u;
-          wave_sync();
           auto place = [&](int a, int b) {
             const bool ma = !((static_mask >> a) & 1u), mb = !((static_mask >> b) & 1u);
             const unsigned ta = ma ? (unsigned)taken[a] : 0u, tb = mb ? (unsigned)taken[b] : 0u;
@@ -1395,14 +1395,51 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
             my_levels = max(my_levels, lv + 1);
             return lv;
           };
-          const int ra = oa.have ? S::round_of(oa.pa, oa.pb) : -1, rb = ob.have ? S::round_of(ob.pa, ob.pb) : -1;
-          for (int r = 0; r < R; ++r) {
-            if (ra == r) oa.lv = place(oa.pa, oa.pb);
-            if (rb == r) ob.lv = place(ob.pa, ob.pb);
-            if (any_listed)
-              for (int q = k; __any(q < n_listed); q += G)
-                if (q < n_listed && S::round_of(lt[q] & 15, lt[q] >> 4) == r) lvl[q] = (unsigned char)place(lt[q] & 15, lt[q] >> 4);
+          if (!any_listed) {   // a pair is placed by the lane that keeps it
             wave_sync();
+            const int ra = oa.have ? S::round_of(oa.pa, oa.pb) : -1, rb = ob.have ? S::round_of(ob.pa, ob.pb) : -1;
+            for (int r = 0; r < R; ++r) {
+              if (ra == r) oa.lv = place(oa.pa, oa.pb);
+              if (rb == r) ob.lv = place(ob.pa, ob.pb);
+              wave_sync();
+            }
+          } else if constexpr (K::LISTED > 0) {
+            // With listed pairs besides, that would be a round trip to LDS for each of a lane's pairs in every round.  Here
+            // the lanes enter their pairs in a table by round and place, lane k places pair k of every round, and the
+            // keepers read the levels off.  (An environment with nearly all of its 120 pairs colliding, 16 lanes: 57.8 k
+            // clocks a substep for the levels with every lane placing its own, 15.7 k this way.)
+            unsigned char* rounds = reinterpret_cast<unsigned char*>(E + K::X_ROUNDS);
+            unsigned* lcnt = reinterpret_cast<unsigned*>(E + K::X_LCNT);
+            if (k < 2) lcnt[k] = 0u;
+            if (k < K::PPR) *reinterpret_cast<uint4*>(rounds + 16 * k) = make_uint4(0u, 0u, 0u, 0u);
+            wave_sync();
+            auto entry = [&](int a, int b) {
+              const int r = S::round_of(a, b);
+              return rounds + 16 * S::place_in_round(a, b, r) + r;
+            };
+            if (oa.have) *entry(oa.pa, oa.pb) = 1;
+            if (ob.have) *entry(ob.pa, ob.pb) = 1;
+            const int trips = scalar((wave_max(n_listed) + G - 1) / G);
+            for (int t = 0, q = k; t < trips; ++t, q += G)
+              if (q < n_listed) *entry(lt[q] & 15, lt[q] >> 4) = 1;
+            wave_sync();
+            // (not unrolled: the pairs and masks of all rounds would be kept in registers for the whole launch)
+#pragma unroll 1
+            for (int r = 0; r < R; ++r) {
+              int a, b;
+              if (S::sched_pair(r, k, a, b) && k < K::PPR && rounds[16 * k + r]) rounds[16 * k + r] = (unsigned char)place(a, b);
+              wave_sync();
+            }
+            if (oa.have) oa.lv = *entry(oa.pa, oa.pb);
+            if (ob.have) ob.lv = *entry(ob.pa, ob.pb);
+            // the listed pairs, level by level (in any order: those of a level commute)
+            for (int t = 0, q = k; t < trips; ++t, q += G)
+              if (q < n_listed) {
+                const int lv = *entry(lt[q] & 15, lt[q] >> 4), sh = 4 * (lv & 7);
+                sched[lv * K::LCAP + ((atomicAdd(lcnt + (lv >> 3), 1u << sh) >> sh) & 15u)] = (unsigned char)q;
+              }
+            wave_sync();
+            level_cnt = (unsigned long long)lcnt[1] << 32 | lcnt[0];
           }
           wave_clevels = 0;
           for (int lv = 1; lv <= R; ++lv)
@@ -1410,17 +1447,6 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
         }
         levels_valid = true;
         lv_a = oa.lv; lv_b = ob.lv;
-        // the pairs that are not held in registers are listed level by level (lane s mod G writes entry s)
-        if (any_listed) {
-          for (int q = 0; __any(q < n_listed); ++q)
-            if (q < n_listed) {
-              const int lv = lvl[q];
-              const int slot = (int)((level_cnt >> (4 * lv)) & 15ull);
-              level_cnt += 1ull << (4 * lv);
-              if ((slot & (G - 1)) == k) sched[lv * K::LCAP + slot] = (unsigned char)q;
-            }
-          wave_sync();
-        }
       }
       oa.lv = lv_a; ob.lv = lv_b;
       auto cnt_of = [&](int lv) { return (int)((level_cnt >> (4 * lv)) & 15ull); };
