@@ -1312,7 +1312,7 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
         if (any_b && k + G < n_act && k + G < K::NREG) take(k + G, ob);
       }
       const int n_listed = max(n_act - K::NREG, 0);
-      const bool any_listed = most_act > K::NREG;
+      const bool any_listed = K::LISTED > 0 && most_act > K::NREG;
       in_record = any_listed;
       wave_sync();
       K2D_T(kT_Presolve);
@@ -1329,7 +1329,7 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
       unsigned long long level_cnt = 0ull;   // listed pairs per level, 4 bits each (a level holds fewer than 16)
       if (!levels_valid || !same_list || any_listed || __any(set_changed)) {
         auto movable = [&](int a, int b) { return ((1u << a) | (1u << b)) & ~static_mask; };
-        if (!any_b && most_act <= 32) {
+        if (!any_b && (K::NP <= 32 || most_act <= 32)) {
           // One pair per lane at most: every lane learns which of the environment's pairs come earlier and share
           // a movable shape with its own (a round's pairs are disjoint, so the order of the rounds decides), and a
           // pair can be placed once all of those are.
@@ -1395,7 +1395,7 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
             my_levels = max(my_levels, lv + 1);
             return lv;
           };
-          if (!any_listed) {   // a pair is placed by the lane that keeps it
+          if (K::TWO && !any_listed) {   // a pair is placed by the lane that keeps it
             wave_sync();
             const int ra = oa.have ? S::round_of(oa.pa, oa.pb) : -1, rb = ob.have ? S::round_of(ob.pa, ob.pb) : -1;
             for (int r = 0; r < R; ++r) {
@@ -1403,15 +1403,18 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
               if (rb == r) ob.lv = place(ob.pa, ob.pb);
               wave_sync();
             }
-          } else if constexpr (K::LISTED > 0) {
+          } else if constexpr (K::LISTED > 0 || !K::TWO) {
+            // (Where a lane has one pair, this only runs with more than 32 of them, and stands for both.)
             // With listed pairs besides, that would be a round trip to LDS for each of a lane's pairs in every round.  Here
             // the lanes enter their pairs in a table by round and place, lane k places pair k of every round, and the
             // keepers read the levels off.  (An environment with nearly all of its 120 pairs colliding, 16 lanes: 57.8 k
             // clocks a substep for the levels with every lane placing its own, 15.7 k this way.)
+            int kk = k;   // (k again, of which the compiler does not know: what follows from it is not kept from the launch's start)
+            asm volatile("" : "+v"(kk));
             unsigned char* rounds = reinterpret_cast<unsigned char*>(E + K::X_ROUNDS);
             unsigned* lcnt = reinterpret_cast<unsigned*>(E + K::X_LCNT);
-            if (k < 2) lcnt[k] = 0u;
-            if (k < K::PPR) *reinterpret_cast<uint4*>(rounds + 16 * k) = make_uint4(0u, 0u, 0u, 0u);
+            if (kk < 2) lcnt[kk] = 0u;
+            if (kk < K::PPR) *reinterpret_cast<uint4*>(rounds + 16 * kk) = make_uint4(0u, 0u, 0u, 0u);
             wave_sync();
             auto entry = [&](int a, int b) {
               const int r = S::round_of(a, b);
@@ -1419,21 +1422,21 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
             };
             if (oa.have) *entry(oa.pa, oa.pb) = 1;
             if (ob.have) *entry(ob.pa, ob.pb) = 1;
-            const int trips = scalar((wave_max(n_listed) + G - 1) / G);
-            for (int t = 0, q = k; t < trips; ++t, q += G)
+            const int trips = any_listed ? scalar((wave_max(n_listed) + G - 1) / G) : 0;
+            for (int t = 0, q = kk; t < trips; ++t, q += G)
               if (q < n_listed) *entry(lt[q] & 15, lt[q] >> 4) = 1;
             wave_sync();
             // (not unrolled: the pairs and masks of all rounds would be kept in registers for the whole launch)
 #pragma unroll 1
             for (int r = 0; r < R; ++r) {
               int a, b;
-              if (S::sched_pair(r, k, a, b) && k < K::PPR && rounds[16 * k + r]) rounds[16 * k + r] = (unsigned char)place(a, b);
+              if (S::sched_pair(r, kk, a, b) && kk < K::PPR && rounds[16 * kk + r]) rounds[16 * kk + r] = (unsigned char)place(a, b);
               wave_sync();
             }
             if (oa.have) oa.lv = *entry(oa.pa, oa.pb);
             if (ob.have) ob.lv = *entry(ob.pa, ob.pb);
             // the listed pairs, level by level (in any order: those of a level commute)
-            for (int t = 0, q = k; t < trips; ++t, q += G)
+            for (int t = 0, q = kk; t < trips; ++t, q += G)
               if (q < n_listed) {
                 const int lv = *entry(lt[q] & 15, lt[q] >> 4), sh = 4 * (lv & 7);
                 sched[lv * K::LCAP + ((atomicAdd(lcnt + (lv >> 3), 1u << sh) >> sh) & 15u)] = (unsigned char)q;
