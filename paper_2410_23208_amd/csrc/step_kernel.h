@@ -93,6 +93,7 @@ struct Cfg {
   static constexpr int LDS_STRIDE = align_up(LDS_WORDS - G, 2 * G) + G;
   static_assert(LDS_STRIDE >= LDS_WORDS && (LDS_STRIDE / G) % 2 == 1 && LDS_STRIDE <= MAX_STRIDE, "stride rule");
   static constexpr int LDS_BYTES = LDS_STRIDE * EPW * 4;
+  static constexpr bool CROWDED = N > 12 && G <= 32;       // what a lane keeps does not fit its registers (see the substep loop)
 };
 
 #define K2D_DPP(v, ctrl) __builtin_amdgcn_update_dpp(0, (int)(v), ctrl, 0xf, 0xf, true)
@@ -1009,6 +1010,14 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
 
     K2D_T(kT_Actions);
     for (int sub = 0; sub < prm.n_substeps; ++sub) {
+      // (k again, of which the compiler does not know: addresses that follow from it are worked out where they are used, an
+      // instruction or two each, instead of being kept for the launch.  Large, 16 lanes: 26 -> 8 vector registers of a lane
+      // spilled, 32 lanes 8 -> none; a control loop over 8192 environments 126.3 -> 124.9 us, one step of it 73 us.  Where
+      // registers suffice the instructions are all that is left of it: 64 environments with 64 lanes each 1.70 -> 1.73 ms,
+      // 65536 Small ones 2.58 -> 2.61)
+      int mine = k;
+      if (K::CROWDED) asm volatile("" : "+v"(mine));
+      const int k = mine;
       // ---- gravity (Alg. 1), bounding boxes of the circles ----
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
