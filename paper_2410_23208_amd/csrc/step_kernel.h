@@ -93,7 +93,7 @@ struct Cfg {
   static constexpr int LDS_STRIDE = align_up(LDS_WORDS - G, 2 * G) + G;
   static_assert(LDS_STRIDE >= LDS_WORDS && (LDS_STRIDE / G) % 2 == 1 && LDS_STRIDE <= MAX_STRIDE, "stride rule");
   static constexpr int LDS_BYTES = LDS_STRIDE * EPW * 4;
-  static constexpr bool CROWDED = N > 12 && G <= 32;       // what a lane keeps does not fit its registers (see the substep loop)
+  static constexpr bool ROOMY = LDS_BYTES * 8 > 160 * 1024;   // the images leave one wavefront per SIMD, with 512 registers a lane
 };
 
 #define K2D_DPP(v, ctrl) __builtin_amdgcn_update_dpp(0, (int)(v), ctrl, 0xf, 0xf, true)
@@ -655,7 +655,7 @@ struct Step {
 // record l of `levels` (what k2d_reset does between launches, without leaving the kernel).
 // BATCHED: the collision constraints of a sweep are solved in the batches of A.8 instead of level by level.
 template <class K, bool RESET, bool BATCHED>
-__global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
+__global__ void __launch_bounds__(64, K::ROOMY ? 1 : 2)
     k2d_step_kernel(float* __restrict__ state, const float* __restrict__ actions, int n_envs, int n_steps, Params prm,
                     const float* __restrict__ levels, int n_level_records, const int32_t* __restrict__ reset_level,
                     const int32_t* __restrict__ order
@@ -704,6 +704,15 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
   unsigned short* taken = reinterpret_cast<unsigned short*>(E + K::X_TAKEN);
   unsigned char* sched = reinterpret_cast<unsigned char*>(E + K::X_SCHED);
   float4* lam_store = reinterpret_cast<float4*>(E + K::X_LAM);
+  // Where what a lane keeps does not fit its 256 registers, the substep takes k anew, of which the compiler does not know:
+  // addresses that follow from it are then worked out where they are used, an instruction or two each, instead of being kept
+  // for the launch and spilled.  Nothing hidden against this, ms: Large, 16 lanes (24 -> 7 vector registers of a lane spilled)
+  // one step of 8192 environments 0.0711 -> 0.0698, of 16384 heterogeneous ones 0.1245 -> 0.1216; long launches spread the
+  // spilling over their steps and have the instructions left, 32768 x 64 8.32 -> 8.35 (8.37 with k hidden ahead of gravity
+  // and polygons too), towers 16384 x 64 8.11 -> 8.18.  With batches it is hidden there too, 16384 x 32 2.66 -> 2.60 (2.65
+  // from the cull on only).  Large with 32 lanes spills four registers without restarts or batches and is left alone: 4000
+  // heterogeneous environments x 64 2.69, 2.73 hidden.
+  constexpr bool HIDDEN = N > 12 && !K::ROOMY && (G == 16 || (G == 32 && (RESET || BATCHED)));
   const float h = prm.h;
   // the lane's polygon q; where a class has fewer polygons than the lanes could take, the last one is worked out (and stored)
   // several times over
@@ -1010,18 +1019,12 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
 
     K2D_T(kT_Actions);
     for (int sub = 0; sub < prm.n_substeps; ++sub) {
-      // (k again, of which the compiler does not know: addresses that follow from it are worked out where they are used, an
-      // instruction or two each, instead of being kept for the launch.  Large, 16 lanes: 26 -> 8 vector registers of a lane
-      // spilled, 32 lanes 8 -> none; a control loop over 8192 environments 126.3 -> 124.9 us, one step of it 73 us.  Where
-      // registers suffice the instructions are all that is left of it: 64 environments with 64 lanes each 1.70 -> 1.73 ms,
-      // 65536 Small ones 2.58 -> 2.61)
-      int mine = k;
-      if (K::CROWDED) asm volatile("" : "+v"(mine));
-      const int k = mine;
+      int ks = k;   // k up to the external impulses (HIDDEN says why)
+      if (HIDDEN && BATCHED) asm volatile("" : "+v"(ks));
       // ---- gravity (Alg. 1), bounding boxes of the circles ----
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
-        const int i = k + s * G;
+        const int i = ks + s * G;
         if ((sh_fall >> s) & 1u) {
           float* vy = E + K::X_VEL + 4 * i + 1;
           *vy = *vy + prm.gravity_y * h;
@@ -1039,7 +1042,7 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
         float wx[QT], wy[QT], ex[QT], ey[QT];
 #pragma unroll
         for (int q = 0; q < QT; ++q) {
-          const float4 f = S::pos4(E, polygon_of(q, k));   // x, y, cos, sin
+          const float4 f = S::pos4(E, polygon_of(q, ks));   // x, y, cos, sin
           wx[q] = f.x + fmaf(f.z, lx[q], -(f.w * ly[q]));
           wy[q] = f.y + fmaf(f.w, lx[q], f.z * ly[q]);
           ex[q] = K2D_DPPF(wx[q], kQuadNext) - wx[q];
@@ -1048,7 +1051,7 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
         float4 box[QT];
 #pragma unroll
         for (int q = 0; q < QT; ++q) {
-          const int p = polygon_of(q, k), v = k & 3;
+          const int p = polygon_of(q, ks), v = ks & 3;
           const float len = sqrtf(dot2(ex[q], ey[q], ex[q], ey[q]));
           S::wv(E, v, p) = make_float2(wx[q], wy[q]);
           S::wn(E, v, p) = make_float2(ey[q] / len, -ex[q] / len);
@@ -1059,10 +1062,10 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
           box[q].z = max_raw(box[q].z, K2D_DPPF(box[q].z, kQuadXor2));
           box[q].w = max_raw(box[q].w, K2D_DPPF(box[q].w, kQuadXor2));
         }
-        if ((k & 3) == 0) {
+        if ((ks & 3) == 0) {
 #pragma unroll
           for (int q = 0; q < QT; ++q)
-            S::box4(E, polygon_of(q, k)) = make_float4(box[q].x - kCullMargin, box[q].y - kCullMargin, box[q].z + kCullMargin, box[q].w + kCullMargin);
+            S::box4(E, polygon_of(q, ks)) = make_float4(box[q].x - kCullMargin, box[q].y - kCullMargin, box[q].z + kCullMargin, box[q].w + kCullMargin);
         }
       }
       wave_sync();
@@ -1127,12 +1130,18 @@ __global__ void __launch_bounds__(64, K::LDS_BYTES * 8 <= 160 * 1024 ? 2 : 1)
         wave_sync();
       } else {
         for (int t = 0; t < T; ++t) {
-          if (k == t && t_live) push();
+          if (ks == t && t_live) push();
           wave_sync();
         }
       }
 
       K2D_T(kT_External);
+      int kc = ks;   // ... and from here on; the range is stated, lest k / 4 and the like become signed divisions
+      if (HIDDEN && !BATCHED) {
+        asm volatile("" : "+v"(kc));
+        __builtin_assume(kc >= 0 && kc < G);
+      }
+      const int k = kc;
       // ---- collision manifolds of all eligible pairs (A.3.1-A.3.4) and their substep constants ----
       // 1. the cheap test for all of this lane's pairs: bounding boxes (of the very world vertices and
       //    centres the manifolds use, grown by a margin a thousand times the rounding error of a
