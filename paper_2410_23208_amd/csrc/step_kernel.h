@@ -758,10 +758,14 @@ __global__ void __launch_bounds__(64, K::ROOMY ? 1 : 2)
   // ---- episode set-up ----
   if (fresh) {
     // (k again, of which the compiler does not know: what only the set-up derives from it -- the tournament's pairs, the
-    // addresses of the record -- would be worked out ahead of the episodes and kept in registers through all of them.
-    // Large, 16 lanes: 88 -> 30 vector registers of a lane spilled; 16384 heterogeneous environments x 256 22.6 -> 22.1 ms)
+    // addresses of the record -- would be worked out ahead of the episodes and kept in registers through all of them.  With
+    // restarts Large with 16 lanes spills 17 vector registers of a lane, 96 with neither this nor HIDDEN: 16384 heterogeneous
+    // environments x 64 4.80 -> 4.67 ms.  Where a lane has 512 registers none of it pays, Large 16384 x 32 with batches
+    // 3.61 -> 3.71.  The range is stated again where it gains, without batches: 65536 Small environments x 64 2.73 -> 2.71;
+    // with them Large 1024 x 32, 64 lanes each, 1.19 -> 1.22)
     int own = k;
-    if (RESET) asm volatile("" : "+v"(own));
+    if (RESET && !K::ROOMY) asm volatile("" : "+v"(own));
+    if (!BATCHED) __builtin_assume(own >= 0 && own < G);
     const int k = own;
     const bool first = src == Rg;
     // Everything is read before anything is looked at: one round trip to memory, not one for every kind of entity.

@@ -354,6 +354,13 @@ def test_resets_inside_one_launch(cfg, n, steps, sweep_order, lanes, B, limits):
         assert np.array_equal(gs[k], os_[k]), k
 
 
+@pytest.mark.parametrize("n,steps,lanes", [(67, 16, 0), (TWO_EACH, 8, 0), (67, 16, 8)])
+def test_resets_inside_one_launch_large_and_batched(n, steps, lanes):
+    """Restarts together with the batches of A.8 in Large environments, on the mappings with 64, 32 and 8 lanes: what the
+    episode set-up and the substep derive from the lane's number is kept or worked out anew by mapping and schedule."""
+    test_resets_inside_one_launch(3, n, steps, 0, lanes, 16, False)
+
+
 @pytest.mark.parametrize("cfg,n,steps", [(3, 131, 12), (2, 259, 40), (0, 67, 30)])
 def test_reward_and_termination(cfg, n, steps):
     """k2d_read_outcome after every step against the outcome oracle (Sec. 3.2): flags and floats bit for bit."""
