@@ -711,7 +711,8 @@ __global__ void __launch_bounds__(64, K::ROOMY ? 1 : 2)
   // spilling over their steps and have the instructions left, 32768 x 64 8.32 -> 8.35 (8.37 with k hidden ahead of gravity
   // and polygons too), towers 16384 x 64 8.11 -> 8.18.  With batches it is hidden there too, 16384 x 32 2.66 -> 2.60 (2.65
   // from the cull on only).  Large with 32 lanes spills four registers without restarts or batches and is left alone: 4000
-  // heterogeneous environments x 64 2.69, 2.73 hidden.
+  // heterogeneous environments x 64 2.69, 2.73 hidden.  (Small and Medium spill less, and lose 1 to 2 % where they do not
+  // spill; where they do, with 8 lanes, it was not measured.)
   constexpr bool HIDDEN = N > 12 && !K::ROOMY && (G == 16 || (G == 32 && (RESET || BATCHED)));
   const float h = prm.h;
   // the lane's polygon q; where a class has fewer polygons than the lanes could take, the last one is worked out (and stored)

@@ -428,7 +428,7 @@ _WALLS = [(-2.6, 5.0, 0.1, 5.0), (7.6, 5.0, 0.1, 5.0)]
 
 def make_scene(cfg_id, n_envs=None, env_ids=None, episode=0, seed=SEED):
     """Scene description (dict of per-env float64 / int64 arrays, reals already rounded to fp32) for
-    BASELINE config `cfg_id` (0..4).  Returns (caps, params, scene)."""
+    workload `cfg_id` (0..4).  Returns (caps, params, scene)."""
     cfg = CONFIGS[cfg_id]
     caps = CAPS[cfg["size"]]
     if env_ids is None:
