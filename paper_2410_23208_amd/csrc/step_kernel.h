@@ -706,13 +706,13 @@ __global__ void __launch_bounds__(64, K::ROOMY ? 1 : 2)
   float4* lam_store = reinterpret_cast<float4*>(E + K::X_LAM);
   // Where what a lane keeps does not fit its 256 registers, the substep takes k anew, of which the compiler does not know:
   // addresses that follow from it are then worked out where they are used, an instruction or two each, instead of being kept
-  // for the launch and spilled.  Nothing hidden against this, ms: Large, 16 lanes (24 -> 7 vector registers of a lane spilled)
-  // one step of 8192 environments 0.0711 -> 0.0698, of 16384 heterogeneous ones 0.1245 -> 0.1216; long launches spread the
-  // spilling over their steps and have the instructions left, 32768 x 64 8.32 -> 8.35 (8.37 with k hidden ahead of gravity
-  // and polygons too), towers 16384 x 64 8.11 -> 8.18.  With batches it is hidden there too, 16384 x 32 2.66 -> 2.60 (2.65
-  // from the cull on only).  Large with 32 lanes spills four registers without restarts or batches and is left alone: 4000
-  // heterogeneous environments x 64 2.69, 2.73 hidden.  (Small and Medium spill less, and lose 1 to 2 % where they do not
-  // spill; where they do, with 8 lanes, it was not measured.)
+  // for the launch and spilled.  Nothing hidden against this, ms: Large, 16 lanes (24 -> 4 vector registers of a lane spilled)
+  // one step of 8192 environments 0.0710 -> 0.0698, of 16384 heterogeneous ones 0.1239 -> 0.1211; long launches spread the
+  // spilling over their steps and have the instructions left, 32768 x 64 8.31 -> 8.36, towers 16384 x 64 8.08 -> 8.11.  With
+  // batches 16384 x 32 2.65 -> 2.59, with restarts (the set-up's share among it) 20000 x 64 5.95 -> 5.79.  Large with 32 lanes
+  // spills four registers without restarts or batches and is left alone: 4000 heterogeneous environments x 64 2.69, 2.73
+  // hidden.  (Small and Medium spill less, and lose 1 to 2 % where they do not spill; where they do, with 8 lanes, it was not
+  // measured.)
   constexpr bool HIDDEN = N > 12 && !K::ROOMY && (G == 16 || (G == 32 && (RESET || BATCHED)));
   const float h = prm.h;
   // the lane's polygon q; where a class has fewer polygons than the lanes could take, the last one is worked out (and stored)
@@ -1024,8 +1024,8 @@ __global__ void __launch_bounds__(64, K::ROOMY ? 1 : 2)
 
     K2D_T(kT_Actions);
     for (int sub = 0; sub < prm.n_substeps; ++sub) {
-      int ks = k;   // k up to the external impulses (HIDDEN says why)
-      if (HIDDEN && BATCHED) asm volatile("" : "+v"(ks));
+      int ks = k;   // k up to the external impulses
+      if (HIDDEN) asm volatile("" : "+v"(ks));
       // ---- gravity (Alg. 1), bounding boxes of the circles ----
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
@@ -1141,12 +1141,10 @@ __global__ void __launch_bounds__(64, K::ROOMY ? 1 : 2)
       }
 
       K2D_T(kT_External);
-      int kc = ks;   // ... and from here on; the range is stated, lest k / 4 and the like become signed divisions
-      if (HIDDEN && !BATCHED) {
-        asm volatile("" : "+v"(kc));
-        __builtin_assume(kc >= 0 && kc < G);
-      }
-      const int k = kc;
+      // (k from here on, with its range, lest k / 4 and the like become signed divisions; stated for gravity and polygons too it
+      // makes Large rollouts with 16 lanes 0.5 % slower, and with batches towers with 32 lanes 2.7 %)
+      const int k = ks;
+      if (HIDDEN && !BATCHED) __builtin_assume(k >= 0 && k < G);
       // ---- collision manifolds of all eligible pairs (A.3.1-A.3.4) and their substep constants ----
       // 1. the cheap test for all of this lane's pairs: bounding boxes (of the very world vertices and
       //    centres the manifolds use, grown by a margin a thousand times the rounding error of a
